@@ -1,5 +1,5 @@
 // Bandwidth-bound cache kernels: evict + compact + append (Algorithm 1's append and rolling
-// step, Algorithm 2's eviction, at scale granularity) and the read-back export.
+// step, Algorithm 2's eviction, at scale and at token granularity) and the read-back export.
 // All traffic is 16-byte vector loads/stores, consecutive lanes on consecutive chunks.
 #include "amskv_internal.hpp"
 
@@ -7,155 +7,119 @@ namespace amskv {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kUnroll = 4;  // 16-byte chunks in flight per thread and pass
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+
+// What an iteration does to one (b,h) row of one tensor, as ranges of 16-byte chunks in the order they are carried
+// out: first the survivors that slide toward offset 0 (sources inside the row), then what is kept of the new scale
+// (sources in the caller's tensor).  Range i covers chunks [begin[i], begin[i+1]) of the concatenation of all ranges.
+constexpr int kMaxRanges = AMSKV_MAX_SCALES + 2;
+struct CopyList {
+  int32_t n_moves, n, total;
+  int32_t begin[kMaxRanges];  // chunks
+  int32_t src[kMaxRanges];    // tokens: of the row, or of the new scale
+  int32_t dst[kMaxRanges];    // tokens of the row
+};
 
 __device__ __forceinline__ void wait_all_vector_loads() {
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
-// Eviction in the COMPACT layout: one workgroup owns one (b,h) row of one tensor (blockIdx.y:
-// 0 = K, 1 = V) and slides the surviving segments toward offset 0.  The moved chunks, taken in
-// ascending address order, have strictly increasing source and destination addresses with
-// dst < src, so a pass that first loads all of its chunks, waits for the data, meets at a
-// barrier and only then stores can never overwrite a chunk that a later pass still has to
-// read: a store to address X can only alias the source of an EARLIER chunk.
-__global__ __launch_bounds__(kThreads) void compact_kernel(char* __restrict__ kc, char* __restrict__ vc,
-                                                           int row_bytes, long long cap_tokens, MoveList mv) {
-  const int tid = threadIdx.x;
+// One workgroup owns one (b,h) row of one tensor (blockIdx.y: 0 = K, 1 = V).  Its chunks, taken in list order, are
+// loaded kChunks per thread at a time; once every load of such a pass has returned (the barrier) they are stored.
+// Destinations ascend with the list.  A moved chunk's destination lies below its source, so a store can only hit the
+// source of a chunk of the same or an earlier pass; the new scale lands behind the survivors, perhaps where one of them
+// used to be, and comes last.
+// Bound: HBM.  Most iterations are one pass (up to 256 x 8 or 1024 x 8 chunks, 32 or 128 KB), so all loads of a row --
+// survivors and new scale alike -- are in flight at once and the row pays the memory latency once.  Compaction and
+// append as two launches (and 16 KB passes through LDS, where the compiler had put the staging array) took 4.6 ms of a
+// pass of the ragged 12-layer stack at batch 64, this kernel and append_kernel take 2.7 (63 us for the average step of
+// the last two scales, 1536 (b,h), about 5 TB/s read + write); on one image a step's compaction 6-14 -> 5 us.
+template <int kBlock, int kChunks>
+__global__ __launch_bounds__(kBlock) void roll_kernel(char* __restrict__ kc, char* __restrict__ vc,
+                                                      const char* __restrict__ k_new, const char* __restrict__ v_new,
+                                                      int row_shift, long long cap_tokens, CopyList cl, RowMap src_map,
+                                                      int heads) {
   const long long bh = blockIdx.x;
-  char* base = (blockIdx.y ? vc : kc) + bh * cap_tokens * row_bytes;
-  const int cpr = row_bytes >> 4;  // chunks per token row
+  char* base = (blockIdx.y ? vc : kc) + ((bh * cap_tokens) << row_shift);
+  const char* ext = (blockIdx.y ? v_new : k_new) + unit_offset(src_map, bh, heads);
+  const int cpr_shift = row_shift - 4;
 
-  int total = 0;
-  for (int i = 0; i < mv.n; ++i) total += mv.len[i] * cpr;
-
-  for (int c0 = 0; c0 < total; c0 += kThreads * kUnroll) {
-    uint4 buf[kUnroll];
-    long long dst_byte[kUnroll];
+  for (int c0 = 0; c0 < cl.total; c0 += kBlock * kChunks) {
+    int src_tok[kChunks], dst_tok[kChunks], piece[kChunks], moved_end = cl.n_moves < cl.n ? cl.begin[cl.n_moves] : cl.total;
 #pragma unroll
-    for (int u = 0; u < kUnroll; ++u) {
-      const int c = c0 + u * kThreads + tid;
-      dst_byte[u] = -1;
-      if (c < total) {
-        int rem = c, src_tok = 0, dst_tok = 0;
-        for (int i = 0; i < mv.n; ++i) {
-          const int n = mv.len[i] * cpr;
-          if (rem < n) {
-            src_tok = mv.src[i];
-            dst_tok = mv.dst[i];
-            break;
-          }
-          rem -= n;
+    for (int u = 0; u < kChunks; ++u) src_tok[u] = dst_tok[u] = piece[u] = 0;
+    for (int i = 0; i < cl.n; ++i) {  // the range of every chunk (uniform values, one walk for all chunks of the thread)
+      const int begin = cl.begin[i], src = cl.src[i], dst = cl.dst[i];
+#pragma unroll
+      for (int u = 0; u < kChunks; ++u) {
+        const int rel = c0 + u * kBlock + (int)threadIdx.x - begin;
+        if (rel >= 0) {
+          src_tok[u] = src + (rel >> cpr_shift);
+          dst_tok[u] = dst + (rel >> cpr_shift);
+          piece[u] = (rel & ((1 << cpr_shift) - 1)) << 4;
         }
-        const long long so = (long long)src_tok * row_bytes + ((long long)rem << 4);
-        dst_byte[u] = (long long)dst_tok * row_bytes + ((long long)rem << 4);
-        buf[u] = *reinterpret_cast<const uint4*>(base + so);
       }
     }
-    wait_all_vector_loads();
-    __syncthreads();
+    u32x4 buf[kChunks];
 #pragma unroll
-    for (int u = 0; u < kUnroll; ++u)
-      if (dst_byte[u] >= 0) *reinterpret_cast<uint4*>(base + dst_byte[u]) = buf[u];
+    for (int u = 0; u < kChunks; ++u) {
+      const int c = c0 + u * kBlock + (int)threadIdx.x;
+      if (c < cl.total) {
+        const char* p = c < moved_end ? base + ((long long)src_tok[u] << row_shift) : ext + src_tok[u] * src_map.tok;
+        buf[u] = *reinterpret_cast<const u32x4*>(p + piece[u]);
+      }
+    }
+    if (cl.n_moves > 0) {  // uniform; without moves nothing that is read is ever written
+      wait_all_vector_loads();
+      __syncthreads();
+    }
+#pragma unroll
+    for (int u = 0; u < kChunks; ++u)
+      if (c0 + u * kBlock + (int)threadIdx.x < cl.total)
+        *reinterpret_cast<u32x4*>(base + ((long long)dst_tok[u] << row_shift) + piece[u]) = buf[u];
   }
 }
 
-// Token-granular iteration of Algorithm 1 in one launch: the moves of compact_kernel, then -- the workgroup owns the
-// row, and behind the last pass's barrier every moved chunk has been read -- the kept ranges of the new scale
-// are copied from the caller's tensor to their place behind the survivors (which may overlap where a survivor
-// used to be).
-__global__ __launch_bounds__(kThreads) void roll_kernel(char* __restrict__ kc, char* __restrict__ vc,
-                                                        const char* __restrict__ k_new, const char* __restrict__ v_new,
-                                                        int row_bytes, long long cap_tokens, MoveList mv, NewRanges nr,
-                                                        RowMap src_map, int heads) {
-  const int tid = threadIdx.x;
-  const long long bh = blockIdx.x;
-  char* base = (blockIdx.y ? vc : kc) + bh * cap_tokens * row_bytes;
-  const int cpr = row_bytes >> 4;
-
-  int total = 0;
-  for (int i = 0; i < mv.n; ++i) total += mv.len[i] * cpr;
-  for (int c0 = 0; c0 < total; c0 += kThreads * kUnroll) {
-    uint4 buf[kUnroll];
-    long long dst_byte[kUnroll];
-#pragma unroll
-    for (int u = 0; u < kUnroll; ++u) {
-      const int c = c0 + u * kThreads + tid;
-      dst_byte[u] = -1;
-      if (c < total) {
-        int rem = c, src_tok = 0, dst_tok = 0;
-        for (int i = 0; i < mv.n; ++i) {
-          const int n = mv.len[i] * cpr;
-          if (rem < n) {
-            src_tok = mv.src[i];
-            dst_tok = mv.dst[i];
-            break;
-          }
-          rem -= n;
-        }
-        const long long so = (long long)src_tok * row_bytes + ((long long)rem << 4);
-        dst_byte[u] = (long long)dst_tok * row_bytes + ((long long)rem << 4);
-        buf[u] = *reinterpret_cast<const uint4*>(base + so);
-      }
-    }
-    wait_all_vector_loads();
-    __syncthreads();
-#pragma unroll
-    for (int u = 0; u < kUnroll; ++u)
-      if (dst_byte[u] >= 0) *reinterpret_cast<uint4*>(base + dst_byte[u]) = buf[u];
-  }
-  if (total > 0) __syncthreads();  // the copies below may overwrite sources of the last pass
-
-  const char* src = (blockIdx.y ? v_new : k_new) + unit_offset(src_map, bh, heads);
-#pragma unroll
-  for (int r = 0; r < 2; ++r) {
-    const int n = r < nr.n ? nr.len[r] * cpr : 0;
-    const char* from = src + (long long)nr.src_first[r] * src_map.tok;
-    char* to = base + (long long)nr.dst[r] * row_bytes;
-#pragma unroll 4
-    for (int c = tid; c < n; c += kThreads) {
-      const int tok = c / cpr;
-      *reinterpret_cast<uint4*>(to + ((long long)c << 4)) =
-          *reinterpret_cast<const uint4*>(from + (long long)tok * src_map.tok + ((c - tok * cpr) << 4));
-    }
-  }
-}
-
-// Append: copy t_new tokens of the new scale K_s, V_s (the caller's tensors, rows located by
-// src_map, starting at token src_first of every (b,h)) into their slot of every (b,h) row of the
-// cache.  Flat over all 16-byte chunks of both tensors, so a one-token scale and a 256-token scale
-// both run full workgroups; for a whole head-major scale the source side is one contiguous stream.  The token-granular trim of Algorithm 2 keeps a scale in part, hence the range.
-// Enqueued after compact_kernel: the slot may overlap the old position of a moved segment.
+// Append without compaction: tokens [src_first, src_first + t_new) of every (b,h) row of the new scale (the caller's
+// tensors, rows located by src_map) go to their slot of that row; the token-granular trim of Algorithm 2 keeps a scale
+// in part, hence the range.  blockIdx.y: 0 = K, 1 = V.  A workgroup takes `rows` whole rows where they are short (one
+// token of head dim 64 is 128 bytes), else an equal part of one, so every launch runs full workgroups.
+// Bound: HBM.  The position of a chunk comes from one multiplication (`inv` = 2^32 / chunks of a row, rounded up, exact
+// for the kRowChunks positions of a workgroup) and shifts; with two 64-bit divisions per chunk and the staging array in
+// LDS a launch took 18 us before it moved anything to speak of (1920 rows of 16 tokens: 20.3 us, 7.1 now; of 64 tokens:
+// 25.7, 14.8 now = 4.2 TB/s read + write).
+constexpr int kChunksPerThread = 4;
+constexpr int kRowChunks = kThreads * kChunksPerThread;
 __global__ __launch_bounds__(kThreads) void append_kernel(char* __restrict__ kc, char* __restrict__ vc,
-                                                          const char* __restrict__ k_new,
-                                                          const char* __restrict__ v_new, int row_bytes,
-                                                          long long cap_tokens, int t_new, int dst_new,
-                                                          int src_first, RowMap src_map, int heads,
-                                                          long long chunks_per_tensor) {
-  const int cpr = row_bytes >> 4;
-  const int per_bh = t_new * cpr;  // chunks of one (b,h) row
-  const long long first = (long long)blockIdx.x * (kThreads * kUnroll) + threadIdx.x;
-  uint4 buf[kUnroll];
-  long long dst_off[kUnroll];
-  int which[kUnroll];
+                                                          const char* __restrict__ k_new, const char* __restrict__ v_new,
+                                                          int row_shift, long long cap_tokens, int chunks, unsigned inv,
+                                                          int rows, int parts, int dst_new, int src_first, RowMap src_map,
+                                                          int heads, int n_bh) {
+  char* cache = blockIdx.y ? vc : kc;
+  const char* src = blockIdx.y ? v_new : k_new;
+  const int cpr_shift = row_shift - 4;
+  const unsigned group = parts == 1 ? blockIdx.x : blockIdx.x / (unsigned)parts;
+  const int first = (int)(blockIdx.x - group * parts) * kRowChunks;  // of the row's chunks (0 where rows are taken whole)
+  const int total = parts == 1 ? rows * chunks : chunks - first;     // this workgroup's chunks
+  u32x4 buf[kChunksPerThread];
+  long long to[kChunksPerThread];
 #pragma unroll
-  for (int u = 0; u < kUnroll; ++u) {
-    long long c = first + (long long)u * kThreads;
-    which[u] = -1;
-    if (c < 2 * chunks_per_tensor) {
-      which[u] = c >= chunks_per_tensor;
-      if (which[u]) c -= chunks_per_tensor;
-      const long long bh = c / per_bh;
-      const int rem = (int)(c - bh * per_bh);
-      dst_off[u] = (bh * cap_tokens + dst_new) * row_bytes + ((long long)rem << 4);
-      const int tok = rem / cpr;
-      const long long so = unit_offset(src_map, bh, heads) + (src_first + tok) * src_map.tok + ((rem - tok * cpr) << 4);
-      buf[u] = *reinterpret_cast<const uint4*>((which[u] ? v_new : k_new) + so);
+  for (int u = 0; u < kChunksPerThread; ++u) {
+    const int i = u * kThreads + (int)threadIdx.x;
+    to[u] = -1;
+    if (i < total) {
+      const int row = parts == 1 ? (int)__umulhi((unsigned)i, inv) : 0;
+      const int c = first + i - row * chunks, tok = c >> cpr_shift, piece = (c & ((1 << cpr_shift) - 1)) << 4;
+      const long long bh = (long long)group * rows + row;
+      if (bh < n_bh) {
+        to[u] = ((bh * cap_tokens + dst_new + tok) << row_shift) + piece;
+        buf[u] = *reinterpret_cast<const u32x4*>(src + unit_offset(src_map, bh, heads) + (src_first + tok) * src_map.tok + piece);
+      }
     }
   }
 #pragma unroll
-  for (int u = 0; u < kUnroll; ++u)
-    if (which[u] >= 0) *reinterpret_cast<uint4*>((which[u] ? vc : kc) + dst_off[u]) = buf[u];
+  for (int u = 0; u < kChunksPerThread; ++u)
+    if (to[u] >= 0) *reinterpret_cast<u32x4*>(cache + to[u]) = buf[u];
 }
 
 // Gather the resident segments, ascending and back to back, into [BH][T_kept][row].
@@ -186,28 +150,63 @@ __global__ __launch_bounds__(kThreads) void export_kernel(const char* __restrict
 hipError_t launch_append(void* kc, void* vc, const void* k_new, const void* v_new, int bh, int row_bytes,
                          int64_t cap_tokens, const MoveList& mv, int t_new, int dst_new, int src_first,
                          const RowMap& src_map, int heads, hipStream_t st) {
+  const bool copies = k_new && t_new > 0;  // else the scale is borrowed: compaction only
   if (mv.n > 0) {
-    hipLaunchKernelGGL(compact_kernel, dim3(bh, 2), dim3(kThreads), 0, st, (char*)kc, (char*)vc, row_bytes,
-                       (long long)cap_tokens, mv);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    NewRanges nr{};
+    if (copies) {
+      nr.n = 1;
+      nr.src_first[0] = src_first;
+      nr.dst[0] = dst_new;
+      nr.len[0] = t_new;
+    }
+    return launch_roll(kc, vc, k_new, v_new, bh, row_bytes, cap_tokens, mv, nr, src_map, heads, st);
   }
-  if (!k_new || t_new <= 0) return hipSuccess;  // borrowed scale: compaction only
-  const long long chunks = (long long)bh * t_new * (row_bytes >> 4);
-  const long long per_block = (long long)kThreads * kUnroll;
-  const unsigned grid = (unsigned)((2 * chunks + per_block - 1) / per_block);
-  hipLaunchKernelGGL(append_kernel, dim3(grid), dim3(kThreads), 0, st, (char*)kc, (char*)vc, (const char*)k_new,
-                     (const char*)v_new, row_bytes, (long long)cap_tokens, t_new, dst_new, src_first, src_map, heads,
-                     chunks);
+  if (!copies) return hipSuccess;
+  const int row_shift = __builtin_ctz((unsigned)row_bytes);  // 128, 256 or 512 bytes
+  const int chunks = t_new << (row_shift - 4);               // at most 2^25 (t_new <= 2^20)
+  const int rows = chunks <= kRowChunks ? kRowChunks / chunks : 1;
+  const int parts = (chunks + kRowChunks - 1) / kRowChunks;
+  const unsigned inv = (unsigned)((0x100000000ull + chunks - 1) / chunks);
+  const unsigned grid = (unsigned)((bh + rows - 1) / rows) * (unsigned)parts;
+  hipLaunchKernelGGL(append_kernel, dim3(grid, 2), dim3(kThreads), 0, st, (char*)kc, (char*)vc, (const char*)k_new,
+                     (const char*)v_new, row_shift, (long long)cap_tokens, chunks, inv, rows, parts, dst_new, src_first, src_map,
+                     heads, bh);
   return hipGetLastError();
 }
 
 hipError_t launch_roll(void* kc, void* vc, const void* k_new, const void* v_new, int bh, int row_bytes,
                        int64_t cap_tokens, const MoveList& mv, const NewRanges& nr, const RowMap& src_map, int heads,
                        hipStream_t st) {
-  hipLaunchKernelGGL(roll_kernel, dim3(bh, 2), dim3(kThreads), 0, st, (char*)kc, (char*)vc, (const char*)k_new,
-                     (const char*)v_new, row_bytes, (long long)cap_tokens, mv, nr, src_map, heads);
-  return hipGetLastError();
+  const int row_shift = __builtin_ctz((unsigned)row_bytes);
+  CopyList cl{};
+  auto add = [&](int src, int dst, int len, bool move) {
+    if (len <= 0) return;
+    // survivors that lay back to back and still do are one range
+    const int last = cl.n - 1;
+    const int last_len = last >= 0 ? (cl.total - cl.begin[last]) >> (row_shift - 4) : 0;
+    if (move && last >= 0 && cl.src[last] + last_len == src && cl.dst[last] + last_len == dst) {
+      cl.total += len << (row_shift - 4);
+      return;
+    }
+    cl.begin[cl.n] = cl.total;
+    cl.src[cl.n] = src;
+    cl.dst[cl.n] = dst;
+    ++cl.n;
+    if (move) cl.n_moves = cl.n;
+    cl.total += len << (row_shift - 4);
+  };
+  for (int i = 0; i < mv.n; ++i) add(mv.src[i], mv.dst[i], mv.len[i], true);
+  for (int i = 0; i < nr.n; ++i) add(nr.src_first[i], nr.dst[i], nr.len[i], false);
+  if (cl.total == 0) return hipSuccess;
+  auto go = [&](auto kernel, int threads) {
+    hipLaunchKernelGGL(kernel, dim3(bh, 2), dim3(threads), 0, st, (char*)kc, (char*)vc, (const char*)k_new, (const char*)v_new,
+                       row_shift, (long long)cap_tokens, cl, src_map, heads);
+    return hipGetLastError();
+  };
+  // the smallest workgroup that takes the row in one pass; few rows get the threads of a large one
+  if (cl.total <= 1024 && bh >= 128) return go(roll_kernel<256, 4>, 256);
+  if (cl.total <= 2048 && bh >= 128) return go(roll_kernel<256, 8>, 256);
+  return go(roll_kernel<1024, 8>, 1024);
 }
 
 hipError_t launch_export(const void* kc, const void* vc, void* k_out, void* v_out, int bh, int row_bytes,
