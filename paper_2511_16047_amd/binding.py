@@ -69,10 +69,12 @@ class _Policy(C.Structure):
 
 
 _lib = None
+_lookup = None   # torch's raw stream lookup, once asked for
+_append = _attend = None   # set by load_library
 
 
 def load_library() -> C.CDLL:
-    global _lib
+    global _lib, _append, _attend
     if _lib is not None:
         return _lib
     if not os.path.exists(LIB_PATH):
@@ -132,8 +134,26 @@ def load_library() -> C.CDLL:
     lib.amskv_interscale_similarity_collect.restype = i32
     lib.amskv_interscale_similarity_enqueue_static.argtypes = [vp, i32, i32, i32, vp, vp]
     lib.amskv_interscale_similarity_enqueue_static.restype = i32
+
+    from . import _pycalls
+    _append, _attend = _pycalls.append_scale, _pycalls.attend
+    _pycalls.bind(C.cast(lib.amskv_append_scale, vp).value, C.cast(lib.amskv_attend, vp).value, _raw_stream_lookup)
     _lib = lib
     return lib
+
+
+def _raw_stream_lookup():
+    """torch's current-device and raw current-stream functions (what torch.cuda.current_stream() asks, without the
+    Stream object it builds around the answer), or (None, None) where there is no device."""
+    global _lookup
+    if _lookup is None:
+        import torch
+        if torch.cuda.is_available():
+            torch.cuda.current_stream()   # initialises the runtime
+            _lookup = torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
+        else:
+            _lookup = None, None
+    return _lookup
 
 
 def status_string(status: int) -> str:
@@ -182,10 +202,8 @@ def _stream(stream) -> Optional[int]:
     if isinstance(stream, int):
         return stream or None
     if stream is None:
-        import torch
-        if torch.cuda.is_available():
-            return int(torch.cuda.current_stream().cuda_stream) or None
-        return None
+        device, current = _raw_stream_lookup()
+        return (int(current(device())) or None) if current else None
     return int(getattr(stream, "cuda_stream", stream)) or None
 
 
@@ -216,13 +234,21 @@ def amskv_cache_create(layers, heads, head_dim, sides_h, sides_w, batch, dtype, 
     return h.value
 
 
+# The two calls made for every layer and scale go through the extension module (csrc/pycalls.cpp).
 def amskv_append_scale(cache, layer, s, K=None, V=None, stream=None):
-    _check(load_library().amskv_append_scale(cache, layer, s, _ptr(K), _ptr(V), _stream(stream)),
-           "amskv_append_scale")
+    if _lib is None:
+        load_library()
+    status = _append(cache, layer, s, K, V, stream)
+    if status:
+        _check(status, "amskv_append_scale")
 
 
 def amskv_attend(cache, layer, s, Q, O, stream=None):
-    _check(load_library().amskv_attend(cache, layer, s, _ptr(Q), _ptr(O), _stream(stream)), "amskv_attend")
+    if _lib is None:
+        load_library()
+    status = _attend(cache, layer, s, Q, O, stream)
+    if status:
+        _check(status, "amskv_attend")
 
 
 def amskv_interscale_similarity(cache, layer, s, heads, want_v=True, want_sums=True, stream=None):

@@ -1,4 +1,4 @@
-"""Compile libamskv.so (HIP kernels + C ABI) for gfx950, in-tree.
+"""Compile libamskv.so (HIP kernels + C ABI) for gfx950 and the binding's extension module, in-tree.
 
     python -m paper_2511_16047_amd.build
 
@@ -14,6 +14,7 @@ import os
 import re
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -21,6 +22,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libamskv.so")
 OBJ = os.path.join(HERE, "_build")
+PYCALLS = os.path.join(HERE, "_pycalls.so")   # the binding's extension module (no device code)
 
 SOURCES = ["amskv_api.cpp", "cache_kernels.hip", "similarity_kernels.hip", "attend_f32.hip", "attend_bf16.hip", "attend_bf16_small.hip", "density_kernels.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-x", "hip", "-Wno-inline-asm",
@@ -115,6 +117,8 @@ def build_library(verbose: bool = False) -> str:
                 r.get("lds", 0), r.get("occupancy", 0)))
     check_resources(rows)
     _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs)
+    _run(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-I", sysconfig.get_paths()["include"],
+          os.path.join(CSRC, "pycalls.cpp"), "-o", PYCALLS])
     return LIB
 
 
