@@ -30,6 +30,10 @@
 // accumulator rescale this requires is applied one step later.  The common block takes no maximum.  A unit's
 // first block, which has no reference and nothing to multiply yet, goes straight to the maximum path.
 //
+// Split form (few units): workgroup of eight waves over 128 query rows and 64-key tiles; waves w and w + 4 hold the same
+// rows and take one of the two blocks of every tile each, with statistics of their own, so a SIMD that would have had one
+// wave has two and each runs half the chain.  At the end each hands the other half of its O^T through LDS.
+//
 // Density variant (attend_density_bf16_kernel): the same body with one more running sum per lane, over the keys of
 // the group of cached keys the stream is in; at the end of a group the per-row sum is parked in LDS, and the
 // epilogue turns the parked sums into the softmax mass per group (Section 4.1) next to O.
@@ -292,7 +296,7 @@ struct Flag {
 // The work of one workgroup.  kDensity: also leave, per 32-row query block, the softmax mass that lands on each
 // group of keys (Section 4.1's attention density as a by-product of the step's own attention; `groups` holds the
 // first virtual row past each group, `partial` one float per (b, h, query block, group)).
-template <int D, int NQ, int kWaves, int kTileKeys, bool kDensity>
+template <int D, int NQ, int kWaves, int kTileKeys, bool kDensity, int kSplit = 1>
 __device__ __forceinline__ void attend_unit(
     const __bf16* __restrict__ q, __bf16* __restrict__ o, char* __restrict__ kc, char* __restrict__ vc,
     int t_q, long long cap_tokens, const SegTable& seg, const ExtKV& ext_kv, const CallerIo& io, float scale_log2e, int n_bh,
@@ -301,7 +305,8 @@ __device__ __forceinline__ void attend_unit(
   constexpr int RB = D * 2;   // bytes per token row
   constexpr int KS = D / 16;  // K-steps of the first product
   constexpr int DB = D / 32;  // 32-row blocks of O^T
-  constexpr int BM = kWaves * 32 * NQ;
+  constexpr int kRowGroups = kWaves / kSplit;  // groups of 32*NQ query rows
+  constexpr int BM = kRowGroups * 32 * NQ;
   constexpr int kTileBytes = kTileKeys * RB;
   constexpr int kBlkBytes = 32 * RB;
   constexpr int kBlocksPerTile = kTileKeys / 32;
@@ -309,14 +314,17 @@ __device__ __forceinline__ void attend_unit(
   // multiplied) and kAhead tiles in flight.  Head dim 128 is bound by latency at two waves per SIMD: one tile
   // in flight makes the ring 48 KB, so three workgroups fit a CU -- three waves per SIMD, which measured 15 %
   // faster on the 1024x1024 schedule than two waves with two tiles in flight.
-  constexpr int kAhead = D == 128 ? 1 : 2;
-  constexpr int kStages = kAhead + 2;
+  // (A split workgroup passes the next tile's barrier before it multiplies the V rows of a block of the tile before:
+  // one slot more.)
+  constexpr int kAhead = D == 128 || kSplit > 1 ? 1 : 2;
+  constexpr int kStages = kAhead + (kSplit > 1 ? 3 : 2);
   constexpr int kRing = kStages * kTileBytes;
   constexpr int VM = Loader::kVmPerTile;
   // Fetch the K fragments of block g+1 into registers while the softmax of block g runs (16 registers at head
   // dim 64; the head-dim-128 configuration has none to spare, and one-block tiles would need a fifth ring slot).
   // (the density variant keeps the plain loop: one block at a time, the tile barrier in front of a tile's first block)
-  constexpr bool kPrefetchK = D == 64 && kBlocksPerTile == 2 && !kDensity;
+  constexpr bool kPrefetchK = (D == 64 || kWaves == 8) && kBlocksPerTile == 2 && (!kDensity || kSplit > 1);
+  static_assert(kSplit == 1 || (kSplit == 2 && kPrefetchK && NQ == 1), "a split workgroup deals the two blocks of a tile");
 
   __shared__ __align__(1024) char lds_k[kRing];
   __shared__ __align__(1024) char lds_v[kRing];
@@ -342,7 +350,8 @@ __device__ __forceinline__ void attend_unit(
   }
   const long long bh = bh_i;
   if (bh >= n_bh) return;  // whole workgroup leaves together (n_bh not a multiple of 8)
-  const int q_base = q_tile * BM + wave * (32 * NQ);
+  const int slice = kSplit == 1 ? 0 : wave / kRowGroups;  // waves w and w + kRowGroups share query rows (and a SIMD)
+  const int q_base = q_tile * BM + (wave - slice * kRowGroups) * (32 * NQ);
   const bool wave_active = q_base < t_q;
   const int t_kv = seg.total;
   const int n_tiles = (t_kv + kTileKeys - 1) / kTileKeys;
@@ -443,6 +452,10 @@ __device__ __forceinline__ void attend_unit(
   if (!wave_active) {
     // no query rows (T_q is not a multiple of the workgroup's rows): this wave only fetches its part of every tile
     for (int it = 1; it < n_tiles; ++it) tile_sync(it, no);
+    if (kSplit > 1) {  // the barriers of the merge
+      __syncthreads();
+      __syncthreads();
+    }
     return;
   }
 
@@ -456,7 +469,7 @@ __device__ __forceinline__ void attend_unit(
   float run_mc[NQ], run_sum[NQ];  // softmax reference times c = softmax scale * log2(e); sum of 2^(s*c - reference)
   // density: this lane's sum over the keys of the group being walked, the group, its end, the block's first row
   float seg_acc[NQ];
-  int cur_group = 0, next_end = kDensity ? groups.end[0] : 0, blk_start = 0;
+  int cur_group = 0, next_end = kDensity ? groups.end[0] : 0, blk_start = 32 * slice;
   bf16x8 pf[NQ][2];  // probabilities of the previous block, two K-steps of 16 keys
 #pragma unroll
   for (int n = 0; n < NQ; ++n) {
@@ -489,7 +502,8 @@ __device__ __forceinline__ void attend_unit(
 
   // ring positions of the blocks a step touches: g-1 (V rows of the second product; first step: block 0
   // itself, multiplied by pf = 0), g, and g+1 (K prefetch)
-  int off_prev = 0, off_cur = 0, off_next = kBlkBytes == kRing ? 0 : kBlkBytes;
+  constexpr int kStep = kSplit > 1 ? kTileBytes : kBlkBytes;  // from a wave's block to its next one
+  int off_prev = slice * kBlkBytes, off_cur = off_prev, off_next = off_prev + kStep;
   float alpha[NQ];
   bool any_rescale = false;  // the rescale decided at block g is applied at the top of block g+1
   bool first_block = true;
@@ -502,7 +516,7 @@ __device__ __forceinline__ void attend_unit(
 #pragma unroll
     for (int t = 0; t < KS; ++t) kf[t] = *reinterpret_cast<const bf16x8*>(lds_k + off + k_off[t]);
   };
-  if (kPrefetchK) load_k(0);
+  if (kPrefetchK) load_k(off_cur);
   int next_tile = 1;  // next tile to synchronise on
 
   // One 32-key block g: S^T, its softmax, and O^T += V^T P^T of block g-1, whose probabilities pf were
@@ -647,7 +661,7 @@ __device__ __forceinline__ void attend_unit(
 #pragma unroll
       for (int n = 0; n < NQ; ++n) taken[n] = 0.f;
       while (next_end <= blk_start + 32) {
-        const int cut = next_end - blk_start;  // 1..32, wave-uniform
+        const int cut = next_end - blk_start;  // <= 32, wave-uniform (< 1: ended in a block of the other slice)
 #pragma unroll
         for (int n = 0; n < NQ; ++n) {
           float upto = sum[n][0];
@@ -671,17 +685,24 @@ __device__ __forceinline__ void attend_unit(
       }
 #pragma unroll
       for (int n = 0; n < NQ; ++n) seg_acc[n] += sum[n][0] - taken[n];
-      blk_start += 32;
+      blk_start += 32 * kSplit;
     }
 #pragma unroll
     for (int n = 0; n < NQ; ++n) run_sum[n] += sum[n][0];
     off_prev = off_cur;
     off_cur = off_next;
-    off_next = ring_next(off_next, kBlkBytes);
+    off_next += kStep;
+    if (off_next >= kRing) off_next -= kRing;
   };
 
   const bool ragged = (t_kv & 31) != 0;
-  if (kPrefetchK) {
+  const int n_mine = kSplit == 1 ? n_blocks : (n_blocks - slice + 1) >> 1;  // blocks of this wave
+  if constexpr (kSplit > 1) {
+    // Block `slice` of every tile; the barrier of the next tile sits behind the score products of each block.
+    for (int it = 0; it + 1 < n_mine; ++it) block_step(yes, no, yes, false);
+    if (n_mine > 0) block_step(no, no, no, ragged && 2 * (n_mine - 1) + slice == n_blocks - 1);
+    if (next_tile < n_tiles) tile_sync(next_tile, no);  // the other slice has one block more
+  } else if (kPrefetchK) {
     // two blocks per tile.  First the tiles whose barrier has nothing to test (the tile it requests exists),
     // then the ones near the end of the stream, then the last tile (1 or 2 blocks).
     int it = 0;
@@ -711,6 +732,7 @@ __device__ __forceinline__ void attend_unit(
         for (int v = 0; v < 16; ++v) oacc[n][d][v] *= alpha[n];
   }
   // ---- drain: the last block's O^T += V^T P^T
+  if (kSplit == 1 || n_mine > 0)
 #pragma unroll
   for (int d = 0; d < DB; ++d) {
     const char* vp = lds_v + off_prev + v_base[d];
@@ -728,9 +750,67 @@ __device__ __forceinline__ void attend_unit(
 
   // ---- O[row][d] = O^T[d][row] / l ; lane (r,h) holds d = 32*db + 8*(v/4) + 4h + v%4 of row r
   char* o_unit = (char*)o + unit_offset(io.o, bh, io.heads);
+  int d_begin = 0, other = wave;      // split: first row block of O^T this wave writes, the wave it shares rows with
+  float w_mine = 1.f, w_theirs = 0.f;  // ... and what the two partial results weigh
+  constexpr int kDbOut = DB / kSplit;  // row blocks of O^T this wave writes, from d_begin on
+  if constexpr (kSplit > 1) {
+    // The two slices of a row group meet: each wave hands the other the half of its O^T the other will write, through
+    // the ring (16 bytes per lane, consecutive lanes), with its reference and sum.
+    constexpr int kParkBytes = kDbOut * 4 * 1024;
+    static_assert(kWaves * kParkBytes <= kRing && kWaves * 64 * 8 <= kRing, "the parked halves fit the ring");
+    typedef float f32x4 __attribute__((ext_vector_type(4)));
+    run_sum[0] += __shfl_xor(run_sum[0], 32, 64);
+    if constexpr (kDensity) {  // groups that end behind this slice's last block
+      for (; cur_group < groups.n; ++cur_group) {
+        const float gsum = seg_acc[0] + __shfl_xor(seg_acc[0], 32, 64);
+        if (h == 0) park[wave][cur_group][r] = gsum;
+        seg_acc[0] = 0.f;
+      }
+    }
+    __syncthreads();  // nothing in the ring is read any more
+    char* mine = lds_k + wave * kParkBytes + 16 * lane;
+    auto park = [&](auto second) {
+      constexpr int from = decltype(second)::value ? 0 : kDbOut;
+#pragma unroll
+      for (int i = 0; i < kDbOut; ++i)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          f32x4 x;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) x[e] = oacc[0][from + i][4 * c + e];
+          *reinterpret_cast<f32x4*>(mine + (4 * i + c) * 1024) = x;
+        }
+      if (decltype(second)::value) {
+#pragma unroll
+        for (int i = 0; i < kDbOut; ++i) oacc[0][i] = oacc[0][kDbOut + i];
+      }
+    };
+    if (slice) park(yes);
+    else park(no);
+    float2* stat = reinterpret_cast<float2*>(lds_v);
+    stat[wave * 64 + lane] = make_float2(run_mc[0], run_sum[0]);
+    __syncthreads();
+    other = slice ? wave - kRowGroups : wave + kRowGroups;
+    const float2 theirs = stat[other * 64 + lane];
+    // (a slice without blocks has the reference -inf and weighs 0)
+    const float top = fmaxf(run_mc[0], theirs.x);
+    w_mine = __builtin_amdgcn_exp2f(run_mc[0] - top);
+    w_theirs = __builtin_amdgcn_exp2f(theirs.x - top);
+    const char* parked = lds_k + other * kParkBytes + 16 * lane;
+#pragma unroll
+    for (int i = 0; i < kDbOut; ++i)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const f32x4 x = *reinterpret_cast<const f32x4*>(parked + (4 * i + c) * 1024);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) oacc[0][i][4 * c + e] = fmaf(w_theirs, x[e], w_mine * oacc[0][i][4 * c + e]);
+      }
+    run_sum[0] = fmaf(w_theirs, theirs.y, w_mine * run_sum[0]);
+    d_begin = slice * kDbOut;
+  }
 #pragma unroll
   for (int n = 0; n < NQ; ++n) {
-    const float total = run_sum[n] + __shfl_xor(run_sum[n], 32, 64);
+    const float total = kSplit > 1 ? run_sum[n] : run_sum[n] + __shfl_xor(run_sum[n], 32, 64);
     const float inv = 1.0f / total;
     const int row = q_base + 32 * n + r;
     // The lane halves hold alternate 8-byte pieces of a row (columns 8g + 4h ..); one lane swap per register
@@ -738,7 +818,7 @@ __device__ __forceinline__ void attend_unit(
     // many requests to the L2 as 8-byte stores: 2.4 % of the step at the default shape).
     __bf16* dst = reinterpret_cast<__bf16*>(o_unit + min(row, t_q - 1) * io.o.tok);
 #pragma unroll
-    for (int d = 0; d < DB; ++d)
+    for (int d = 0; d < kDbOut; ++d)
 #pragma unroll
       for (int k = 0; k < 2; ++k) {
         bf16x4 wa, wb;
@@ -751,14 +831,16 @@ __device__ __forceinline__ void attend_unit(
         const auto s0 = __builtin_amdgcn_permlane32_swap(a[0], b[0], false, false);
         const auto s1 = __builtin_amdgcn_permlane32_swap(a[1], b[1], false, false);
         const u32x4 w = {s0[0], s1[0], s0[1], s1[1]};
-        if (row < t_q) *reinterpret_cast<u32x4*>(dst + 32 * d + 16 * k + 8 * h) = w;
+        if (row < t_q) *reinterpret_cast<u32x4*>(dst + 32 * (d_begin + d) + 16 * k + 8 * h) = w;
       }
     if constexpr (kDensity) {
       // mass of the query block on group p = sum over its valid rows of (sum of exp over the group) / (sum over all keys)
       const int n_qblk = (t_q + 31) >> 5;
       const long long qblk = bh * n_qblk + (q_base >> 5) + n;
-      for (int p = 0; p < groups.n; ++p) {
-        float m = h == 0 && row < t_q ? park[wave * NQ + n][p][r] * inv : 0.f;
+      for (int p = slice; p < groups.n; p += kSplit) {
+        float gsum = park[wave * NQ + n][p][r];
+        if (kSplit > 1) gsum = fmaf(w_theirs, park[other][p][r], w_mine * gsum);
+        float m = h == 0 && row < t_q ? gsum * inv : 0.f;
 #pragma unroll
         for (int d = 16; d >= 1; d >>= 1) m += __shfl_xor(m, d, 64);  // over the 32 query rows (lower lane half)
         if (lane == 0) partial[qblk * AMSKV_MAX_SCALES + p] = m;
@@ -767,48 +849,85 @@ __device__ __forceinline__ void attend_unit(
   }
 }
 
-template <int D, int NQ, int kWaves, int kTileKeys, int kMinWavesPerSimd>
+template <int D, int NQ, int kWaves, int kTileKeys, int kMinWavesPerSimd, int kSplit = 1>
 __global__ __launch_bounds__(64 * kWaves, kMinWavesPerSimd) void attend_bf16_kernel(
     const __bf16* __restrict__ q, __bf16* __restrict__ o, char* __restrict__ kc, char* __restrict__ vc,
     int t_q, long long cap_tokens, SegTable seg, ExtKV ext_kv, CallerIo io, float scale_log2e, int n_bh, int n_qtiles) {
-  attend_unit<D, NQ, kWaves, kTileKeys, false>(q, o, kc, vc, t_q, cap_tokens, seg, chosen(ext_kv), io, scale_log2e, n_bh,
+  attend_unit<D, NQ, kWaves, kTileKeys, false, kSplit>(q, o, kc, vc, t_q, cap_tokens, seg, chosen(ext_kv), io, scale_log2e, n_bh,
                                                n_qtiles, GroupEnds{}, nullptr);
 }
 
 // The same step with the attention density of its own queries as a by-product (no second pass over Q and K).
-template <int D, int NQ, int kWaves, int kTileKeys, int kMinWavesPerSimd>
+template <int D, int NQ, int kWaves, int kTileKeys, int kMinWavesPerSimd, int kSplit = 1>
 __global__ __launch_bounds__(64 * kWaves, kMinWavesPerSimd) void attend_density_bf16_kernel(
     const __bf16* __restrict__ q, __bf16* __restrict__ o, char* __restrict__ kc, char* __restrict__ vc,
     int t_q, long long cap_tokens, SegTable seg, ExtKV ext_kv, CallerIo io, float scale_log2e, int n_bh, int n_qtiles,
     GroupEnds groups, float* __restrict__ partial) {
-  attend_unit<D, NQ, kWaves, kTileKeys, true>(q, o, kc, vc, t_q, cap_tokens, seg, chosen(ext_kv), io, scale_log2e, n_bh,
+  attend_unit<D, NQ, kWaves, kTileKeys, true, kSplit>(q, o, kc, vc, t_q, cap_tokens, seg, chosen(ext_kv), io, scale_log2e, n_bh,
                                               n_qtiles, groups, partial);
 }
 
-template <int D, int NQ, int kWaves, int kTileKeys, int kMinWavesPerSimd>
+template <int D, int NQ, int kWaves, int kTileKeys, int kMinWavesPerSimd, int kSplit = 1>
 hipError_t launch(const void* q, void* o, void* kc, void* vc, int bh, int t_q, int64_t cap_tokens,
                   const SegTable& seg, const ExtKV& ext, const CallerIo& io, float c, hipStream_t st) {
-  constexpr int BM = kWaves * 32 * NQ;
+  constexpr int BM = kWaves / kSplit * 32 * NQ;
   const int n_qtiles = (t_q + BM - 1) / BM;
   dim3 grid((unsigned)(((bh + 7) / 8) * 8 * n_qtiles)), block(64 * kWaves);
-  hipLaunchKernelGGL((attend_bf16_kernel<D, NQ, kWaves, kTileKeys, kMinWavesPerSimd>), grid, block, 0, st,
+  hipLaunchKernelGGL((attend_bf16_kernel<D, NQ, kWaves, kTileKeys, kMinWavesPerSimd, kSplit>), grid, block, 0, st,
                      (const __bf16*)q, (__bf16*)o, (char*)kc, (char*)vc, t_q, (long long)cap_tokens, seg, ext, io, c,
                      bh, n_qtiles);
   return hipGetLastError();
 }
 
-template <int D, int NQ, int kWaves, int kTileKeys, int kMinWavesPerSimd>
+template <int D, int NQ, int kWaves, int kTileKeys, int kMinWavesPerSimd, int kSplit = 1>
 hipError_t launch_density_variant(const void* q, void* o, void* kc, void* vc, int bh, int t_q, int64_t cap_tokens,
                                   const SegTable& seg, const ExtKV& ext, const CallerIo& io, float c, const GroupEnds& groups,
                                   float* partial, hipStream_t st) {
-  constexpr int BM = kWaves * 32 * NQ;
+  constexpr int BM = kWaves / kSplit * 32 * NQ;
   const int n_qtiles = (t_q + BM - 1) / BM;
   dim3 grid((unsigned)(((bh + 7) / 8) * 8 * n_qtiles)), block(64 * kWaves);
-  hipLaunchKernelGGL((attend_density_bf16_kernel<D, NQ, kWaves, kTileKeys, kMinWavesPerSimd>), grid, block, 0, st,
+  hipLaunchKernelGGL((attend_density_bf16_kernel<D, NQ, kWaves, kTileKeys, kMinWavesPerSimd, kSplit>), grid, block, 0, st,
                      (const __bf16*)q, (__bf16*)o, (char*)kc, (char*)vc, t_q, (long long)cap_tokens, seg, ext, io, c,
                      bh, n_qtiles, groups, partial);
   return hipGetLastError();
 }
+
+// Which workgroup.  All of them carry 32 query rows per wave and walk the same 32-key blocks:
+//   narrow  4 waves, 128 rows, 32-key tiles   wide   8 waves, 256 rows, 64-key tiles
+//   split   8 waves, 128 rows, 64-key tiles, the two blocks of a tile on different waves
+// The widest one reads K~ and V~ least often, but how long a launch takes is also a matter of how many workgroups the
+// fullest CU gets and of how many waves that puts on its SIMDs: a lone wave overlaps nothing.  The model is what a
+// 32-key block costs a CU that is given 1, 2, ... workgroups (us, measured with 16 to 128 (b,h), 144 to 4096 queries and
+// 229 to 6421 keys; its choice lost 4 % at most against the best of the three).  Head dim 128, 32 (b,h): 256 queries x 421
+// keys 16.8 -> 12.5 us (split), 1024 x 1621 47.7 -> 33.7 (split), 1600 x 2645 86.6 -> 75.5 (wide), 4096 x 6421 423 -> 370
+// (wide); 2304 x 3925 stays narrow (163; wide 206, split 182).  Head dim 64: 16 (b,h), 256 x 680 16.0 -> 12.0 us, 32 (b,h),
+// 1024 x 1621 31.7 -> 22.9.
+enum class Shape { kNarrow, kWide, kSplit };
+
+// time of n workgroups of which `resident` fit a CU: whole rounds, then what the fullest CU still gets
+double rounds(long long n, int resident, double full, const double* part) {
+  const long long per_round = 256LL * resident, rest = n % per_round;
+  return (double)(n / per_round) * full + (rest ? part[(rest - 1) / 256] : 0.0);
+}
+
+Shape choose(int head_dim, int bh, int t_q, bool moves_rows) {
+  const long long n128 = (long long)bh * ((t_q + 127) / 128), n256 = (long long)bh * ((t_q + 255) / 256);
+  if (head_dim == 128) {
+    static const double narrow[] = {0.83, 1.05, 1.35}, wide[] = {0.88}, split[] = {0.53};
+    const double tn = rounds(n128, 3, 1.40, narrow), ts = rounds(n128, 1, 0.53, split);
+    const double tw = t_q > 128 ? rounds(n256, 1, 0.88, wide) : 1e30;
+    return ts < tn && ts <= tw ? Shape::kSplit : tw < tn ? Shape::kWide : Shape::kNarrow;
+  }
+  // Head dim 64 at up to 256 queries lives from reading K~ and V~ once, and a launch that moves cached rows relies on it
+  // (attend_owns_unit); beyond 256 workgroups of the split kind a CU has waves enough (512 of them: 100 queries x 255
+  // keys 12.9 -> 12.6, 64 x 119 7.5 -> 8.1, 169 x 424 13.0 -> 15.0 us; 256 of them: 9.8 -> 8.0, 6.5 -> 5.9, 11.8 -> 10.0).
+  const bool split_owns = t_q <= 128 || !moves_rows;
+  if (split_owns && n128 <= 256) return Shape::kSplit;
+  return t_q > 128 ? Shape::kWide : Shape::kNarrow;
+}
+
+// the launch writes rows of the cached part to other places (token modes), not only the new scale behind it
+bool moves_rows(const SegTable& seg, const ExtKV& ext) { return ext.alt_if != nullptr || ext.wb_from < seg.ext_start || ext.wb_head_end > 0; }
 
 }  // namespace
 
@@ -826,11 +945,15 @@ hipError_t launch_attend_density_bf16(const void* q, void* o, void* kc, void* vc
   // Four waves of 32 rows and 32-key tiles at either head dim (the ring shares LDS with the per-row group sums,
   // and the block step holds its scores a little longer: three and two waves per SIMD); more than 128 query rows
   // are split over workgroups with ids 8 apart, which re-read K~ and V~ from their XCD's L2.
+  // (the split shape goes with the attention's: both leave the same bits in O)
+  const bool split = choose(head_dim, bh, t_q, moves_rows(seg, ext)) == Shape::kSplit;
   hipError_t e;
   if (head_dim == 64)
-    e = launch_density_variant<64, 1, 4, 32, 4>(q, o, kc, vc, bh, t_q, cap_tokens, seg, ext, io, c, groups, partial_ws, st);
+    e = split ? launch_density_variant<64, 1, 8, 64, 2, 2>(q, o, kc, vc, bh, t_q, cap_tokens, seg, ext, io, c, groups, partial_ws, st)
+              : launch_density_variant<64, 1, 4, 32, 4>(q, o, kc, vc, bh, t_q, cap_tokens, seg, ext, io, c, groups, partial_ws, st);
   else
-    e = launch_density_variant<128, 1, 4, 32, 2>(q, o, kc, vc, bh, t_q, cap_tokens, seg, ext, io, c, groups, partial_ws, st);
+    e = split ? launch_density_variant<128, 1, 8, 64, 2, 2>(q, o, kc, vc, bh, t_q, cap_tokens, seg, ext, io, c, groups, partial_ws, st)
+              : launch_density_variant<128, 1, 4, 32, 2>(q, o, kc, vc, bh, t_q, cap_tokens, seg, ext, io, c, groups, partial_ws, st);
   if (e != hipSuccess) return e;
   return launch_density_total(partial_ws, batch, heads, (t_q + 31) / 32, groups.n, out_dev, st);
 }
@@ -841,15 +964,19 @@ hipError_t launch_attend_bf16(const void* q, void* o, void* kc, void* vc, int bh
   // coarse scales: latency-bound, one independent wave per 32 query rows
   if (t_q <= kSmallTq) return launch_attend_bf16_small(q, o, kc, vc, bh, t_q, head_dim, cap_tokens, seg, ext, io, softmax_scale, st);
   const float c = softmax_scale * 1.4426950408889634f;
-  const bool wide = t_q > 128;  // 256 query rows per workgroup keeps K/V single-pass up to T_q = 256
-  if (head_dim == 64)
-    // eight waves of 32 rows: ~110 registers per lane, so two workgroups (16 waves) share a CU
-    return wide ? launch<64, 1, 8, 64, 4>(q, o, kc, vc, bh, t_q, cap_tokens, seg, ext, io, c, st)
-                : launch<64, 1, 4, 32, 4>(q, o, kc, vc, bh, t_q, cap_tokens, seg, ext, io, c, st);
-  // head dim 128: 32 query rows per wave (~160 registers) and a three-slot ring give three waves per SIMD,
-  // i.e. three workgroups of four waves per CU; 64 rows per wave would halve that
-  (void)wide;
-  return launch<128, 1, 4, 32, 3>(q, o, kc, vc, bh, t_q, cap_tokens, seg, ext, io, c, st);
+  switch (choose(head_dim, bh, t_q, moves_rows(seg, ext))) {
+    case Shape::kSplit:
+      return head_dim == 64 ? launch<64, 1, 8, 64, 4, 2>(q, o, kc, vc, bh, t_q, cap_tokens, seg, ext, io, c, st)
+                            : launch<128, 1, 8, 64, 2, 2>(q, o, kc, vc, bh, t_q, cap_tokens, seg, ext, io, c, st);
+    case Shape::kWide:
+      // head dim 64: ~110 registers per lane, so two workgroups (16 waves) share a CU
+      return head_dim == 64 ? launch<64, 1, 8, 64, 4>(q, o, kc, vc, bh, t_q, cap_tokens, seg, ext, io, c, st)
+                            : launch<128, 1, 8, 64, 2>(q, o, kc, vc, bh, t_q, cap_tokens, seg, ext, io, c, st);
+    default:
+      // head dim 128: ~160 registers and a three-slot ring give three workgroups of four waves per CU
+      return head_dim == 64 ? launch<64, 1, 4, 32, 4>(q, o, kc, vc, bh, t_q, cap_tokens, seg, ext, io, c, st)
+                            : launch<128, 1, 4, 32, 3>(q, o, kc, vc, bh, t_q, cap_tokens, seg, ext, io, c, st);
+  }
 }
 
 }  // namespace amskv
