@@ -926,8 +926,16 @@ Shape choose(int head_dim, int bh, int t_q, bool moves_rows) {
   return t_q > 128 ? Shape::kWide : Shape::kNarrow;
 }
 
-// the launch writes rows of the cached part to other places (token modes), not only the new scale behind it
-bool moves_rows(const SegTable& seg, const ExtKV& ext) { return ext.alt_if != nullptr || ext.wb_from < seg.ext_start || ext.wb_head_end > 0; }
+// The launch writes over cached rows that its queries read (token modes: survivors slide down, or the new scale's rows land
+// where older ones were).  Writing the new scale into a free place is not that.
+bool moves_rows(const SegTable& seg, const ExtKV& ext) {
+  if (ext.alt_if != nullptr || ext.wb_from < seg.ext_start || ext.wb_head_end > 0) return true;
+  if (ext.wb_from >= seg.total) return false;
+  const int to = ext.wb_from + ext.wb_delta, to_end = seg.total + ext.wb_delta;
+  for (int i = 0; i < seg.n; ++i)
+    if (seg.virt_start[i] < seg.ext_start && to < seg.phys_off[i] + seg.len[i] && to_end > seg.phys_off[i]) return true;
+  return false;
+}
 
 }  // namespace
 

@@ -4,8 +4,10 @@
 against the oracle (max-abs 2e-2 on unit-variance inputs, as everywhere), cache contents bit-exact."""
 import pytest
 
+import amskv_inputs as inp
 import paper_2511_16047_amd as amskv
 from test_gpu_parity import Runner, _qkv
+from test_gpu_token_window import _run as _run_window
 
 pytestmark = pytest.mark.gpu
 
@@ -27,3 +29,11 @@ def test_few_units(D, B, H, flags):
             r.run_layer(layer, q, k, v, check_cache=True, units=every if len(every) <= 5 else every[:2] + every[len(every) // 2:len(every) // 2 + 2] + every[-1:])
     finally:
         r.close()
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("window,n_sink", [(100, 0), (100, 1), (196, 0)])
+@pytest.mark.parametrize("sides", [(10, 13, 14, 16), (5, 6, 10, 4, 12, 3)])
+def test_window_over_cached_rows(sides, window, n_sink, D):
+    """token window: the step's own rows land on cached rows that its queries still read"""
+    _run_window(sides, 2, 3, D, "bf16", window, n_sink, inp.layer_seed(8, 300 + window), query_between=False)
