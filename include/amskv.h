@@ -319,11 +319,11 @@ int32_t amskv_attention_density_enqueue(amskv_cache* cache, int32_t layer, int32
  * amskv_attend leaves it, and in mass_out_dev / *n_seg / tok_len what amskv_attention_density_enqueue
  * would report when called just before -- the groups are the layer's segments as the step's attention
  * sees them, before the step's own bookkeeping (fused append, Algorithm 1's iteration).
- * bf16 caches and steps of more than 32 tokens: the density is a by-product of the attention launch
+ * bf16 caches: the density is a by-product of the attention launch
  * itself -- its kernel keeps, per query row, the sum of exp over the keys of each group next to
  * the softmax statistics it keeps anyway, so Q, K and V are read once and nothing but the per-block
  * partial masses is written beyond O (and the fused append).  O comes out bit-identical to
- * amskv_attend's.  Steps of at most 32 tokens and fp32 caches: the two calls, density first.
+ * amskv_attend's.  fp32 caches: the two calls, density first.
  * Status codes and residency rules of amskv_attend; workspace and ordering rule of
  * amskv_attention_density_enqueue. */
 int32_t amskv_attend_density(amskv_cache* cache, int32_t layer, int32_t s, const void* Q_dev, void* O_dev,

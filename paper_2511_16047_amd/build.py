@@ -35,8 +35,8 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-x", "hip", "-W
 MIN_OCCUPANCY = [
     (re.compile(r"attend_bf16_kernel<\d+, \d+, \d+, \d+, (\d+)[,>]"), None),     # None: take group 1
     (re.compile(r"attend_density_bf16_kernel<\d+, \d+, \d+, \d+, (\d+)[,>]"), None),
-    (re.compile(r"attend_bf16_small_kernel<64>"), 4),
-    (re.compile(r"attend_bf16_small_kernel<128>"), 2),
+    (re.compile(r"attend_bf16_small_kernel<64(, \d+, 0)?>"), 4),
+    (re.compile(r"attend_bf16_small_kernel<128(, \d+, 0)?>"), 2),
 ]
 
 

@@ -841,7 +841,7 @@ static int attend_step(amskv_cache* c, int32_t layer, int32_t s, const void* Q_d
   const SegTable t = seg_table(L, &ext);
   if (t.ext_start < t.total && !ext.k) return AMSKV_ERR_NO_DEVICE_MEMORY;  // borrowed scale appended without data
   // density: one group per entry of the layer's list; as a by-product of this very launch where the kernel has
-  // that form (bf16, more query rows than the coarse-scale kernel takes), else by the stand-alone kernels first
+  // that form (bf16), else by the stand-alone kernels first
   amskv::GroupEnds groups;
   std::memset(&groups, 0, sizeof(groups));
   bool by_product = false;
@@ -888,7 +888,7 @@ static int attend_step(amskv_cache* c, int32_t layer, int32_t s, const void* Q_d
     const bool cache_it = c->cut_oversize || newest.len <= L.bud.c_max;
     const bool overflow = cache_it && total > bgt;
     const bool wants_test = overflow && bgt == L.bud.c_min && L.bud.c_max > L.bud.c_min;
-    const bool one_owner = c->dtype == AMSKV_DTYPE_BF16 && (by_product ? c->tokens[s] <= 128 : amskv::attend_owns_unit(c->head_dim, c->tokens[s]));
+    const bool one_owner = c->dtype == AMSKV_DTYPE_BF16 && amskv::attend_owns_unit(c->head_dim, c->tokens[s]);
     // what the launch writes under budget b: nothing (the scale is larger than the budget and is not cached), the
     // whole scale behind the cached tokens, or Algorithm 2's survivors
     auto plan = [&](int32_t b, int32_t* from, int32_t* delta, int32_t* head_end) {

@@ -135,7 +135,7 @@ hipError_t launch_attend_bf16(const void* q, void* o, void* kc, void* vc, int bh
                               const ExtKV& ext, const CallerIo& io, float softmax_scale, hipStream_t st);
 // The attention of a step with the attention density of its queries as a by-product: as launch_attend_bf16, plus
 // the per-head masses of the groups in out_dev (heads * AMSKV_MAX_SCALES floats; workspace as for launch_density).
-// Exists for t_q above the coarse-scale kernel's range only: attend_density_fused(t_q) tells.
+// attend_density_fused(t_q) tells whether that form exists for a step of t_q queries.
 bool attend_density_fused(int t_q);
 // launch_attend_bf16 gives every (b,h) to one workgroup (or, on the coarse scales, one wave): the condition for
 // asking it to move cached rows (ExtKV)
@@ -144,9 +144,12 @@ hipError_t launch_attend_density_bf16(const void* q, void* o, void* kc, void* vc
                                       int64_t cap_tokens, const SegTable& seg, const ExtKV& ext, const CallerIo& io,
                                       float softmax_scale, const GroupEnds& groups, float* partial_ws, float* out_dev,
                                       hipStream_t st);
-hipError_t launch_attend_bf16_small(const void* q, void* o, void* kc, void* vc, int bh,
-                                    int t_q, int head_dim, int64_t cap_tokens, const SegTable& seg,
-                                    const ExtKV& ext, const CallerIo& io, float softmax_scale, hipStream_t st);
+// split: how many waves share the key blocks of a 32-row unit (1; 4; 8 at head dim 64); partial: nullptr, or the workspace
+// that takes the masses of `groups`
+hipError_t launch_attend_bf16_small(const void* q, void* o, void* kc, void* vc, int bh, int t_q,
+                                    int head_dim, int64_t cap_tokens, const SegTable& seg,
+                                    const ExtKV& ext, const CallerIo& io, float softmax_scale, int split,
+                                    const GroupEnds& groups, float* partial, hipStream_t st);
 hipError_t launch_attend_f32(const void* q, void* o, void* kc, void* vc, int bh,
                              int t_q, int head_dim, int64_t cap_tokens, const SegTable& seg,
                              const ExtKV& ext, const CallerIo& io, float softmax_scale, hipStream_t st);

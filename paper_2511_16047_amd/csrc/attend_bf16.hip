@@ -63,7 +63,7 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
-// query-token count up to which the latency-oriented kernel of attend_bf16_small.hip is used
+// query-token count up to which the latency-oriented kernel of attend_bf16_small.hip is always used
 constexpr int kSmallTq = 32;
 // the online softmax lets the running max lag by up to this many powers of two before the
 // accumulators are rescaled; probabilities then stay below 2^kMaxLag, far inside fp32/bf16 range
@@ -893,8 +893,10 @@ hipError_t launch_density_variant(const void* q, void* o, void* kc, void* vc, in
 }
 
 // Which workgroup.  All of them carry 32 query rows per wave and walk the same 32-key blocks:
-//   narrow  4 waves, 128 rows, 32-key tiles   wide   8 waves, 256 rows, 64-key tiles
-//   split   8 waves, 128 rows, 64-key tiles, the two blocks of a tile on different waves
+//   streams  one wave per 32 rows, or the waves of a workgroup sharing the blocks of one unit (attend_bf16_small.hip)
+//   narrow   4 waves, 128 rows, 32-key tiles
+//   wide     8 waves, 256 rows, 64-key tiles
+//   split    8 waves, 128 rows, 64-key tiles, the two blocks of a tile on different waves
 // The widest one reads K~ and V~ least often, but how long a launch takes is also a matter of how many workgroups the
 // fullest CU gets and of how many waves that puts on its SIMDs: a lone wave overlaps nothing.  The model is what a
 // 32-key block costs a CU that is given 1, 2, ... workgroups (us, measured with 16 to 128 (b,h), 144 to 4096 queries and
@@ -902,28 +904,16 @@ hipError_t launch_density_variant(const void* q, void* o, void* kc, void* vc, in
 // keys 16.8 -> 12.5 us (split), 1024 x 1621 47.7 -> 33.7 (split), 1600 x 2645 86.6 -> 75.5 (wide), 4096 x 6421 423 -> 370
 // (wide); 2304 x 3925 stays narrow (163; wide 206, split 182).  Head dim 64: 16 (b,h), 256 x 680 16.0 -> 12.0 us, 32 (b,h),
 // 1024 x 1621 31.7 -> 22.9.
-enum class Shape { kNarrow, kWide, kSplit };
+enum class Shape { kStreams, kNarrow, kWide, kSplit };
+struct Choice {
+  Shape shape;
+  int split;  // kStreams: waves that share the keys of a 32-row unit
+};
 
 // time of n workgroups of which `resident` fit a CU: whole rounds, then what the fullest CU still gets
 double rounds(long long n, int resident, double full, const double* part) {
   const long long per_round = 256LL * resident, rest = n % per_round;
   return (double)(n / per_round) * full + (rest ? part[(rest - 1) / 256] : 0.0);
-}
-
-Shape choose(int head_dim, int bh, int t_q, bool moves_rows) {
-  const long long n128 = (long long)bh * ((t_q + 127) / 128), n256 = (long long)bh * ((t_q + 255) / 256);
-  if (head_dim == 128) {
-    static const double narrow[] = {0.83, 1.05, 1.35}, wide[] = {0.88}, split[] = {0.53};
-    const double tn = rounds(n128, 3, 1.40, narrow), ts = rounds(n128, 1, 0.53, split);
-    const double tw = t_q > 128 ? rounds(n256, 1, 0.88, wide) : 1e30;
-    return ts < tn && ts <= tw ? Shape::kSplit : tw < tn ? Shape::kWide : Shape::kNarrow;
-  }
-  // Head dim 64 at up to 256 queries lives from reading K~ and V~ once, and a launch that moves cached rows relies on it
-  // (attend_owns_unit); beyond 256 workgroups of the split kind a CU has waves enough (512 of them: 100 queries x 255
-  // keys 12.9 -> 12.6, 64 x 119 7.5 -> 8.1, 169 x 424 13.0 -> 15.0 us; 256 of them: 9.8 -> 8.0, 6.5 -> 5.9, 11.8 -> 10.0).
-  const bool split_owns = t_q <= 128 || !moves_rows;
-  if (split_owns && n128 <= 256) return Shape::kSplit;
-  return t_q > 128 ? Shape::kWide : Shape::kNarrow;
 }
 
 // The launch writes over cached rows that its queries read (token modes: survivors slide down, or the new scale's rows land
@@ -937,9 +927,38 @@ bool moves_rows(const SegTable& seg, const ExtKV& ext) {
   return false;
 }
 
+Choice choose(int head_dim, int bh, int t_q, const SegTable& seg, const ExtKV& ext) {
+  const bool moves = moves_rows(seg, ext);
+  const long long units = (long long)bh * ((t_q + 31) / 32);
+  const int blocks = (seg.total + 31) / 32;
+  if (t_q <= kSmallTq) {
+    // One wave per unit where the chip is full of them, else as many slices as leave every wave a few blocks.  A launch that
+    // moves cached rows needs one wave to fetch them all.  us, 1 / 4 / 8 slices, head dim 64, 25 queries: 16 units x 55 keys
+    // 6.4 / 5.2 / 5.4, 128 x 625 30.6 / 10.8 / 8.2, 512 x 625 30.4 / 15.8 / 16.0; one block 4.7 / 5.5 / 5.7.  Head dim 128,
+    // 16 queries: 32 units x 37 keys 8.9 / 6.5, 128 x 416 33.0 / 13.3.
+    if (moves || blocks < 2 || units > 512) return {Shape::kStreams, 1};
+    return {Shape::kStreams, head_dim == 128 || blocks == 2 || units > 256 ? 4 : 8};
+  }
+  // More queries, few units, head dim 64: 16 (b,h), 256 x 680 12.1 (split workgroups) -> 9.2 us, 64 units of 100 x 255 7.4 ->
+  // 6.2, 256 units of 256 x 680 12.3 -> 9.5; 512 units 12.6 -> 14.3.  (Head dim 128: four slices never won by 5 %.)
+  if (head_dim == 64 && !moves && units <= 256) return {Shape::kStreams, 8};
+  const long long n128 = (long long)bh * ((t_q + 127) / 128), n256 = (long long)bh * ((t_q + 255) / 256);
+  if (head_dim == 128) {
+    static const double narrow[] = {0.83, 1.05, 1.35}, wide[] = {0.88}, split[] = {0.53};
+    const double tn = rounds(n128, 3, 1.40, narrow), ts = rounds(n128, 1, 0.53, split);
+    const double tw = t_q > 128 ? rounds(n256, 1, 0.88, wide) : 1e30;
+    return {ts < tn && ts <= tw ? Shape::kSplit : tw < tn ? Shape::kWide : Shape::kNarrow, 1};
+  }
+  // Head dim 64 at up to 256 queries lives from reading K~ and V~ once, and a launch that moves cached rows relies on it
+  // (attend_owns_unit); beyond 256 workgroups of the split kind a CU has waves enough (512 of them: 100 queries x 255
+  // keys 12.9 -> 12.6, 64 x 119 7.5 -> 8.1, 169 x 424 13.0 -> 15.0 us; 256 of them: 9.8 -> 8.0, 6.5 -> 5.9, 11.8 -> 10.0).
+  if (n128 <= 256 && (t_q <= 128 || !moves)) return {Shape::kSplit, 1};
+  return {t_q > 128 ? Shape::kWide : Shape::kNarrow, 1};
+}
+
 }  // namespace
 
-bool attend_density_fused(int t_q) { return t_q > kSmallTq; }
+bool attend_density_fused(int) { return true; }
 
 bool attend_owns_unit(int head_dim, int t_q) { return t_q <= (head_dim == 64 ? 256 : 128); }
 
@@ -947,21 +966,22 @@ hipError_t launch_attend_density_bf16(const void* q, void* o, void* kc, void* vc
                                       int64_t cap_tokens, const SegTable& seg, const ExtKV& ext, const CallerIo& io,
                                       float softmax_scale, const GroupEnds& groups, float* partial_ws, float* out_dev,
                                       hipStream_t st) {
-  if (!attend_density_fused(t_q)) return hipErrorInvalidValue;
   const float c = softmax_scale * 1.4426950408889634f;
   const int bh = batch * heads;
-  // Four waves of 32 rows and 32-key tiles at either head dim (the ring shares LDS with the per-row group sums,
-  // and the block step holds its scores a little longer: three and two waves per SIMD); more than 128 query rows
-  // are split over workgroups with ids 8 apart, which re-read K~ and V~ from their XCD's L2.
-  // (the split shape goes with the attention's: both leave the same bits in O)
-  const bool split = choose(head_dim, bh, t_q, moves_rows(seg, ext)) == Shape::kSplit;
+  // The choice is the attention's, so that O comes out with the same bits.  In place of the wide shape (the same bits as
+  // the narrow one) goes the narrow one, whose four workgroups per CU hide the group sums better (the case of profiling
+  // density at batch 64: 1.88 against 1.91 ms), unless cached rows move and one workgroup has to own all query rows.
+  const Choice x = choose(head_dim, bh, t_q, seg, ext);
   hipError_t e;
-  if (head_dim == 64)
-    e = split ? launch_density_variant<64, 1, 8, 64, 2, 2>(q, o, kc, vc, bh, t_q, cap_tokens, seg, ext, io, c, groups, partial_ws, st)
-              : launch_density_variant<64, 1, 4, 32, 4>(q, o, kc, vc, bh, t_q, cap_tokens, seg, ext, io, c, groups, partial_ws, st);
+  if (x.shape == Shape::kStreams)
+    e = launch_attend_bf16_small(q, o, kc, vc, bh, t_q, head_dim, cap_tokens, seg, ext, io, softmax_scale, x.split, groups, partial_ws, st);
+  else if (head_dim == 64)
+    e = x.shape == Shape::kSplit ? launch_density_variant<64, 1, 8, 64, 2, 2>(q, o, kc, vc, bh, t_q, cap_tokens, seg, ext, io, c, groups, partial_ws, st)
+        : x.shape == Shape::kWide && moves_rows(seg, ext) ? launch_density_variant<64, 1, 8, 64, 4>(q, o, kc, vc, bh, t_q, cap_tokens, seg, ext, io, c, groups, partial_ws, st)
+                                : launch_density_variant<64, 1, 4, 32, 4>(q, o, kc, vc, bh, t_q, cap_tokens, seg, ext, io, c, groups, partial_ws, st);
   else
-    e = split ? launch_density_variant<128, 1, 8, 64, 2, 2>(q, o, kc, vc, bh, t_q, cap_tokens, seg, ext, io, c, groups, partial_ws, st)
-              : launch_density_variant<128, 1, 4, 32, 2>(q, o, kc, vc, bh, t_q, cap_tokens, seg, ext, io, c, groups, partial_ws, st);
+    e = x.shape == Shape::kSplit ? launch_density_variant<128, 1, 8, 64, 2, 2>(q, o, kc, vc, bh, t_q, cap_tokens, seg, ext, io, c, groups, partial_ws, st)
+                               : launch_density_variant<128, 1, 4, 32, 2>(q, o, kc, vc, bh, t_q, cap_tokens, seg, ext, io, c, groups, partial_ws, st);
   if (e != hipSuccess) return e;
   return launch_density_total(partial_ws, batch, heads, (t_q + 31) / 32, groups.n, out_dev, st);
 }
@@ -969,10 +989,11 @@ hipError_t launch_attend_density_bf16(const void* q, void* o, void* kc, void* vc
 hipError_t launch_attend_bf16(const void* q, void* o, void* kc, void* vc, int bh, int t_q,
                               int head_dim, int64_t cap_tokens, const SegTable& seg, const ExtKV& ext, const CallerIo& io,
                               float softmax_scale, hipStream_t st) {
-  // coarse scales: latency-bound, one independent wave per 32 query rows
-  if (t_q <= kSmallTq) return launch_attend_bf16_small(q, o, kc, vc, bh, t_q, head_dim, cap_tokens, seg, ext, io, softmax_scale, st);
+  const Choice x = choose(head_dim, bh, t_q, seg, ext);
+  if (x.shape == Shape::kStreams)
+    return launch_attend_bf16_small(q, o, kc, vc, bh, t_q, head_dim, cap_tokens, seg, ext, io, softmax_scale, x.split, GroupEnds{}, nullptr, st);
   const float c = softmax_scale * 1.4426950408889634f;
-  switch (choose(head_dim, bh, t_q, moves_rows(seg, ext))) {
+  switch (x.shape) {
     case Shape::kSplit:
       return head_dim == 64 ? launch<64, 1, 8, 64, 4, 2>(q, o, kc, vc, bh, t_q, cap_tokens, seg, ext, io, c, st)
                             : launch<128, 1, 8, 64, 2, 2>(q, o, kc, vc, bh, t_q, cap_tokens, seg, ext, io, c, st);

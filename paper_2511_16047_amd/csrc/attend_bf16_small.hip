@@ -1,17 +1,21 @@
-// bf16 per-scale attention for the coarse scales (Section 3.1's per-step attention when the
-// step has only a handful of query tokens): at T_q of 1..64 a (b,h) unit is a few kilobytes
-// of work and the launch is bound by memory latency, not by bandwidth or the matrix cores, so
-// the design goal is to have every unit of the launch resident at once.
+// bf16 per-scale attention where a (b,h) has little work or the (b,h) are few (Section 3.1's per-step attention): the
+// launch is bound by memory latency and by the serial chain of a unit's key blocks, not by bandwidth or the matrix cores, so
+// the design goal is to have every unit of the launch resident at once and its chain short.
 //
-// One WAVE owns one unit = (b, h, block of 32 query rows); the four waves of a workgroup are
-// independent (no barrier, no shared data).  K fragments are loaded straight from the cache into
-// registers in the A-operand layout of v_mfma_f32_32x32x16_bf16 (lane (r,h) reads 16 bytes of
-// key row r), so K never touches LDS; the only LDS use is two 32-key blocks of V per wave, which
-// the transposing read ds_read_b64_tr_b16 needs as its source and which direct-to-LDS loads fill
-// without passing through registers (that is what lets four waves per SIMD be resident at head
-// dim 64).  The loads of block g+1 are issued right after the first product of block g has
-// consumed the K registers, so they overlap the softmax and the second product.  Same transposed formulation (S^T = K Q^T, O^T += V^T P^T) and
-// the same segment-table walk as the streaming kernel; plain online softmax.
+// One WAVE owns one unit = (b, h, block of 32 query rows), or (kSplit > 1) the waves of a workgroup share one, each taking
+// every kSplit-th block of 32 keys with softmax statistics of its own; their partial results meet in LDS once, behind one
+// barrier.  Otherwise the waves of a workgroup are independent.  K fragments are loaded straight from the cache into
+// registers in the A-operand layout of v_mfma_f32_32x32x16_bf16 (lane (r,h) reads 16 bytes of key row r), so K never touches
+// LDS; LDS holds two 32-key blocks of V per wave, which the transposing read ds_read_b64_tr_b16 needs as its source and
+// which direct-to-LDS loads fill without passing through registers (that is what lets four waves per SIMD be resident at
+// head dim 64).  The loads of a wave's next block are issued right after the first product has consumed the K registers, so
+// they overlap the softmax and the second product.  Same transposed formulation (S^T = K Q^T, O^T += V^T P^T) and the same
+// segment-table walk as the streaming kernel; plain online softmax.
+//
+// kDensity: the softmax mass on each group of keys (Section 4.1) as a by-product.  A wave sums its probabilities per group in
+// fp32 as the key stream passes; where a group ends it parks (sum, the maximum it refers to) in LDS, and at the end
+// everything parked moves to the common maximum.  (Coarse scales, 1920 units: 8.7 us for the stand-alone density kernel and
+// 8.4 for the attention -> 11.2 for both.)
 #include "amskv_internal.hpp"
 
 namespace amskv {
@@ -21,10 +25,12 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 // 16-byte chunk as a native vector: arrays of it stay in registers (HIP's uint4 struct did not)
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kWavesPerGroup = 4;
+// waves of a workgroup: four units, or the four or eight slices of one
+constexpr int waves_of(int split) { return split == 8 ? 8 : 4; }
 
 #define AMSKV_LDS __attribute__((address_space(3)))
 
@@ -56,26 +62,40 @@ __device__ __forceinline__ void settle_mfma(f32x16& acc) { asm volatile("s_nop 1
 
 // Register budget: four waves per SIMD at head dim 64 and two at 128 are the most that fit without spilling;
 // every step up in resident waves measured faster on these latency-bound launches.
-template <int D>
-__global__ __launch_bounds__(64 * kWavesPerGroup, D == 64 ? 4 : 2) void attend_bf16_small_kernel(
+template <int D, int kSplit, bool kDensity>
+__global__ __launch_bounds__(64 * waves_of(kSplit), !kDensity ? (D == 64 ? 4 : 2) : kSplit > 1 ? 1 : D == 64 ? 3 : 2) void attend_bf16_small_kernel(
     const __bf16* __restrict__ q, __bf16* __restrict__ o, char* __restrict__ kc, char* __restrict__ vc,
-    int t_q, long long cap_tokens, SegTable seg, ExtKV ext_in, CallerIo io, float scale_log2e, int n_qblk, int n_units) {
+    int t_q, long long cap_tokens, SegTable seg, ExtKV ext_in, CallerIo io, float scale_log2e, int n_qblk, int n_bh,
+    GroupEnds groups, float* __restrict__ partial) {
   const ExtKV ext_kv = chosen(ext_in);
+  constexpr int kWaves = waves_of(kSplit);
   constexpr int RB = D * 2;
   constexpr int CPR = D / 8;
   constexpr int KS = D / 16;
   constexpr int DB = D / 32;
   constexpr int VCH = 32 * CPR / 64;  // 16-byte chunks of a 32-key V block per lane
 
-  __shared__ __align__(1024) char lds_v[kWavesPerGroup][2][32 * RB];  // per wave: the block in use and the one in flight
+  __shared__ __align__(1024) char lds_v[kWaves][2][32 * RB];  // per wave: the block in use and the one in flight
+  __shared__ float2 stat[kSplit > 1 ? kWaves : 1][32];        // split: reference and sum of every slice's rows
+  __shared__ float2 park[kDensity ? kWaves : 1][kDensity ? AMSKV_MAX_SCALES : 1][32];  // density: sum and its reference
 
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
-  const int unit = blockIdx.x * kWavesPerGroup + wave;
-  if (unit >= n_units) return;  // waves are independent: nothing below synchronises across waves
+  const int slice = kSplit == 1 ? 0 : wave;
+  int bh_i, q_blk;
+  if (kSplit == 1) {
+    const int unit = blockIdx.x * kWaves + wave;
+    bh_i = unit / n_qblk;
+    q_blk = unit - bh_i * n_qblk;
+  } else {  // the workgroups of one (b,h) get ids 8 apart: they run on one XCD and share its L2
+    const unsigned per_group = 8u * n_qblk, group = blockIdx.x / per_group, within = blockIdx.x - group * per_group;
+    bh_i = group * 8 + (within & 7);
+    q_blk = within >> 3;
+  }
+  if (bh_i >= n_bh) return;  // without a split nothing below synchronises across waves; with one, the whole workgroup leaves
   const int r = lane & 31, h = lane >> 5;
-  const long long bh = unit / n_qblk;
-  const int q_base = (unit % n_qblk) * 32;
+  const long long bh = bh_i;
+  const int q_base = q_blk * 32;
   const int t_kv = seg.total;
   const int n_blocks = (t_kv + 31) / 32;
   char* kb = kc + bh * cap_tokens * RB;
@@ -98,9 +118,9 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, D == 64 ? 4 : 2) void attend_b
   bf16x8 kf[KS];
   // lane i of V load k fills chunk position i % CPR of row k * (64 / CPR) + i / CPR with the global chunk that the
   // XOR swizzle (same as the streaming kernel's at head dim 64) assigns to that position
-  auto load_block = [&](int g) {
+  auto load_block = [&](int g, int buffer) {
     const int j0 = 32 * g;
-    char* dst = lds_v[wave][g & 1];
+    char* dst = lds_v[wave][buffer];
 #pragma unroll
     for (int k = 0; k < VCH; ++k) {
       const int row = k * (64 / CPR) + lane / CPR, c = (lane % CPR) ^ (row & 7);
@@ -114,7 +134,7 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, D == 64 ? 4 : 2) void attend_b
 #pragma unroll
     for (int t = 0; t < KS; ++t) kf[t] = *reinterpret_cast<const bf16x8*>(kp + 32 * t + 16 * h);
   };
-  load_block(0);
+  if (kSplit == 1 || slice < n_blocks) load_block(slice, 0);
 
   f32x16 oacc[DB];
 #pragma unroll
@@ -126,11 +146,23 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, D == 64 ? 4 : 2) void attend_b
   const int tr_key = 4 * h + ((lane & 15) >> 2);
   const int tr_col = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
 
-  for (int g = 0; g < n_blocks; ++g) {
+  // density: group the stream is in, its end, where the part of it that this block holds begins, sum so far
+  int group = 0, next_end = kDensity ? groups.end[0] : 0;
+  float group_sum = 0.f;
+  auto park_group = [&]() {
+    const float x = group_sum + __shfl_xor(group_sum, 32, 64);  // the lane halves hold different keys of a query
+    if (h == 0) park[wave][group][r] = make_float2(x, run_max);
+    group_sum = 0.f;
+    ++group;
+    next_end = group < groups.n ? groups.end[group] : 0x7fffffff;
+  };
+
+  int buffer = 0;
+  for (int g = slice; g < n_blocks; g += kSplit, buffer ^= 1) {
     // every load of block g (the V rows in LDS and the K registers) has landed; an explicit point, because the
     // compiler does not know that the V loads wrote LDS and could otherwise move reads of it above its own wait
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    const char* my_v = lds_v[wave][g & 1];
+    const char* my_v = lds_v[wave][buffer];
     f32x16 sacc;
 #pragma unroll
     for (int v = 0; v < 16; ++v) sacc[v] = 0.f;
@@ -154,7 +186,7 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, D == 64 ? 4 : 2) void attend_b
               *reinterpret_cast<const u32x4*>(my_v + k * 1024 + 16 * lane);
       }
     }
-    if (g + 1 < n_blocks) load_block(g + 1);  // in flight during the softmax and the second product
+    if (g + kSplit < n_blocks) load_block(g + kSplit, buffer ^ 1);  // in flight during the softmax and the second product
 
     if (g == n_blocks - 1 && (t_kv & 31) != 0) {
       const int valid = t_kv & 31;
@@ -177,14 +209,39 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, D == 64 ? 4 : 2) void attend_b
     bf16x8 pf[2];
 #pragma unroll
     for (int v = 0; v < 16; v += 2) {
+      const float p0 = __builtin_amdgcn_exp2f(fmaf(sacc[v], scale_log2e, -mc));
+      const float p1 = __builtin_amdgcn_exp2f(fmaf(sacc[v + 1], scale_log2e, -mc));
+      if constexpr (kDensity) {
+        sacc[v] = p0;
+        sacc[v + 1] = p1;
+      }
       bf16x2 pk;
-      pk[0] = (__bf16)__builtin_amdgcn_exp2f(fmaf(sacc[v], scale_log2e, -mc));
-      pk[1] = (__bf16)__builtin_amdgcn_exp2f(fmaf(sacc[v + 1], scale_log2e, -mc));
+      pk[0] = (__bf16)p0;
+      pk[1] = (__bf16)p1;
       sum = __builtin_amdgcn_fdot2_f32_bf16(pk, ones, sum, false);
       pf[v >> 3][v & 7] = pk[0];
       pf[v >> 3][(v & 7) + 1] = pk[1];
     }
     run_sum = sum;
+    if constexpr (kDensity) {
+      group_sum *= alpha;
+      // keys [from, to) of the block belong to the group
+      auto take = [&](int from, int to) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const int key = 8 * (v >> 2) + 4 * h + (v & 3);
+          group_sum += key >= from && key < to ? sacc[v] : 0.f;
+        }
+      };
+      int from = 0;
+      while (next_end <= 32 * g + 32) {  // (an end in front of this block lies in another slice's block)
+        const int to = max(next_end - 32 * g, 0);
+        take(from, to);
+        park_group();
+        from = to;
+      }
+      take(from, 32);
+    }
 #pragma unroll
     for (int d = 0; d < DB; ++d)
 #pragma unroll
@@ -206,47 +263,121 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, D == 64 ? 4 : 2) void attend_b
     __builtin_amdgcn_wave_barrier();  // ... and are overwritten by the next iteration
   }
 
-  const float total = run_sum + __shfl_xor(run_sum, 32, 64);
-  const float inv = 1.0f / total;
+  if constexpr (kDensity)
+    while (group < groups.n) park_group();
+  float total = run_sum + __shfl_xor(run_sum, 32, 64);
   const int row = q_base + r;
-  // The lane halves hold alternate 8-byte pieces of a row (columns 8g + 4h ..); one lane swap per register pairs
-  // them up, so that every lane stores 16 bytes and the two lanes of a row 32 contiguous bytes.
   __bf16* dst = reinterpret_cast<__bf16*>(o_unit + min(row, t_q - 1) * io.o.tok);
+  float top = run_max, weight[kSplit];
+  if constexpr (kSplit == 1) {
+    const float inv = 1.0f / total;
+    // The lane halves hold alternate 8-byte pieces of a row (columns 8g + 4h ..); one lane swap per register pairs
+    // them up, so that every lane stores 16 bytes and the two lanes of a row 32 contiguous bytes.
 #pragma unroll
-  for (int d = 0; d < DB; ++d)
+    for (int d = 0; d < DB; ++d)
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-      bf16x4 wa, wb;
+      for (int k = 0; k < 2; ++k) {
+        typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+        bf16x4 wa, wb;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        wa[e] = (__bf16)(oacc[d][8 * k + e] * inv);
-        wb[e] = (__bf16)(oacc[d][8 * k + 4 + e] * inv);
+        for (int e = 0; e < 4; ++e) {
+          wa[e] = (__bf16)(oacc[d][8 * k + e] * inv);
+          wb[e] = (__bf16)(oacc[d][8 * k + 4 + e] * inv);
+        }
+        const u32x2 a = __builtin_bit_cast(u32x2, wa), b = __builtin_bit_cast(u32x2, wb);
+        const auto s0 = __builtin_amdgcn_permlane32_swap(a[0], b[0], false, false);
+        const auto s1 = __builtin_amdgcn_permlane32_swap(a[1], b[1], false, false);
+        const u32x4 w = {s0[0], s1[0], s0[1], s1[1]};
+        if (row < t_q) *reinterpret_cast<u32x4*>(dst + 32 * d + 16 * k + 8 * h) = w;
       }
-      const u32x2 a = __builtin_bit_cast(u32x2, wa), b = __builtin_bit_cast(u32x2, wb);
-      const auto s0 = __builtin_amdgcn_permlane32_swap(a[0], b[0], false, false);
-      const auto s1 = __builtin_amdgcn_permlane32_swap(a[1], b[1], false, false);
-      const u32x4 w = {s0[0], s1[0], s0[1], s1[1]};
-      if (row < t_q) *reinterpret_cast<u32x4*>(dst + 32 * d + 16 * k + 8 * h) = w;
+  } else {
+    // Every slice parks its O^T where its V blocks were (the same number of bytes; 16 per lane, consecutive lanes) and then
+    // puts its share of the row pieces together from all slices.
+    constexpr int kChunks = 4 * DB;
+#pragma unroll
+    for (int c = 0; c < kChunks; ++c) {
+      f32x4 x;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x[e] = oacc[c >> 2][4 * (c & 3) + e];
+      *reinterpret_cast<f32x4*>(&lds_v[wave][0][0] + c * 1024 + lane * 16) = x;
     }
+    if (h == 0) stat[wave][r] = make_float2(run_max, total);  // -inf, 0 for a slice without blocks: it weighs 0
+    __syncthreads();
+#pragma unroll
+    for (int p = 0; p < kSplit; ++p) top = fmaxf(top, stat[p][r].x);
+    total = 0.f;
+#pragma unroll
+    for (int p = 0; p < kSplit; ++p) {
+      weight[p] = __builtin_amdgcn_exp2f((stat[p][r].x - top) * scale_log2e);
+      total = fmaf(weight[p], stat[p][r].y, total);
+    }
+    const float inv = 1.0f / total;
+#pragma unroll
+    for (int c0 = 0; c0 < kChunks; c0 += kSplit) {
+      const int c = c0 + slice;
+      f32x4 x = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int p = 0; p < kSplit; ++p) {
+        const f32x4 y = *reinterpret_cast<const f32x4*>(&lds_v[p][0][0] + c * 1024 + lane * 16);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[e] = fmaf(weight[p], y[e], x[e]);
+      }
+      bf16x4 w;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) w[e] = (__bf16)(x[e] * inv);
+      if (row < t_q) *reinterpret_cast<bf16x4*>(dst + 8 * c + 4 * h) = w;  // chunk c: columns 8c + 4h ..
+    }
+  }
+  if constexpr (kDensity) {
+    // mass of the unit on group p = sum over its rows of (sum of exp over the group) / (sum over all groups)
+    auto mass = [&](int p) {
+      float x = 0.f;
+#pragma unroll
+      for (int w = 0; w < kSplit; ++w) {
+        const float2 y = park[kSplit == 1 ? wave : w][p][r];
+        x = fmaf(y.x, __builtin_amdgcn_exp2f((y.y - top) * scale_log2e), x);
+      }
+      return x;
+    };
+    float all = 0.f;
+    for (int p = 0; p < groups.n; ++p) all += mass(p);
+    const float inv_all = h == 0 && row < t_q ? 1.0f / all : 0.f;
+    for (int p = slice; p < groups.n; p += kSplit) {
+      float m = mass(p) * inv_all;
+#pragma unroll
+      for (int d = 16; d >= 1; d >>= 1) m += __shfl_xor(m, d, 64);  // over the 32 query rows (lower lane half)
+      if (lane == 0) partial[(bh * n_qblk + q_blk) * AMSKV_MAX_SCALES + p] = m;
+    }
+  }
+}
+
+template <int D, int kSplit, bool kDensity>
+hipError_t launch_one(const void* q, void* o, void* kc, void* vc, int bh, int t_q, int64_t cap_tokens, const SegTable& seg,
+                      const ExtKV& ext, const CallerIo& io, float c, const GroupEnds& groups, float* partial, hipStream_t st) {
+  const int n_qblk = (t_q + 31) / 32;
+  constexpr int kWaves = waves_of(kSplit);
+  const unsigned grid = kSplit == 1 ? (unsigned)(((long long)bh * n_qblk + kWaves - 1) / kWaves)
+                                    : (unsigned)((bh + 7) / 8 * 8) * (unsigned)n_qblk;
+  hipLaunchKernelGGL((attend_bf16_small_kernel<D, kSplit, kDensity>), dim3(grid), dim3(64 * kWaves), 0, st, (const __bf16*)q,
+                     (__bf16*)o, (char*)kc, (char*)vc, t_q, (long long)cap_tokens, seg, ext, io, c, n_qblk, bh, groups, partial);
+  return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t launch_attend_bf16_small(const void* q, void* o, void* kc, void* vc, int bh, int t_q,
                                     int head_dim, int64_t cap_tokens, const SegTable& seg, const ExtKV& ext,
-                                    const CallerIo& io, float softmax_scale, hipStream_t st) {
+                                    const CallerIo& io, float softmax_scale, int split, const GroupEnds& groups, float* partial,
+                                    hipStream_t st) {
   const float c = softmax_scale * 1.4426950408889634f;
-  const int n_qblk = (t_q + 31) / 32;
-  const long long n_units = (long long)bh * n_qblk;
-  dim3 grid((unsigned)((n_units + kWavesPerGroup - 1) / kWavesPerGroup)), block(64 * kWavesPerGroup);
-  if (head_dim == 64)
-    hipLaunchKernelGGL(attend_bf16_small_kernel<64>, grid, block, 0, st, (const __bf16*)q, (__bf16*)o, (char*)kc,
-                       (char*)vc, t_q, (long long)cap_tokens, seg, ext, io, c, n_qblk, (int)n_units);
-  else
-    hipLaunchKernelGGL(attend_bf16_small_kernel<128>, grid, block, 0, st, (const __bf16*)q, (__bf16*)o, (char*)kc,
-                       (char*)vc, t_q, (long long)cap_tokens, seg, ext, io, c, n_qblk, (int)n_units);
-  return hipGetLastError();
+  auto go = [&](auto f) { return f(q, o, kc, vc, bh, t_q, cap_tokens, seg, ext, io, c, groups, partial, st); };
+  if (head_dim == 64) {
+    if (split == 8) return partial ? go(launch_one<64, 8, true>) : go(launch_one<64, 8, false>);
+    if (split == 4) return partial ? go(launch_one<64, 4, true>) : go(launch_one<64, 4, false>);
+    return partial ? go(launch_one<64, 1, true>) : go(launch_one<64, 1, false>);
+  }
+  if (split > 1) return partial ? go(launch_one<128, 4, true>) : go(launch_one<128, 4, false>);
+  return partial ? go(launch_one<128, 1, true>) : go(launch_one<128, 1, false>);
 }
 
 }  // namespace amskv

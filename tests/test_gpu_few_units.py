@@ -1,8 +1,9 @@
-"""bf16 attention of more than 32 query rows where the (b, h) are few: the dispatch chooses between workgroups of 128 and
-256 rows and the form that deals a unit's key blocks to two waves.  Query and key counts around the 32-row block, the
+"""bf16 attention where the (b, h) are few: the dispatch chooses between workgroups of 128 and 256 rows and the forms that
+deal a unit's key blocks to two, four or eight waves.  Query and key counts around the 32-row block, the
 64-key tile and the 128- and 256-row workgroups -- a last tile without, with a partial and with a whole second block --
 against the oracle (max-abs 2e-2 on unit-variance inputs, as everywhere), cache contents bit-exact."""
 import pytest
+import torch
 
 import amskv_inputs as inp
 import paper_2511_16047_amd as amskv
@@ -37,3 +38,47 @@ def test_few_units(D, B, H, flags):
 def test_window_over_cached_rows(sides, window, n_sink, D):
     """token window: the step's own rows land on cached rows that its queries still read"""
     _run_window(sides, 2, 3, D, "bf16", window, n_sink, inp.layer_seed(8, 300 + window), query_between=False)
+
+
+# few queries, 40 to 900 keys: 1 to 29 blocks for four or eight slices
+COARSE = ((8, 16, 1, 1, 3, 29, 20, 1, 5), (5, 20, 1, 7, 11, 1, 25, 16, 6))
+
+
+@pytest.mark.parametrize("B,H", [(1, 1), (3, 5), (9, 32), (35, 16)])   # eight, four and one wave per unit
+@pytest.mark.parametrize("D", [64, 128])
+def test_few_queries_many_keys(D, B, H):
+    pols = [(0, 0, True), (1, 1, False)]
+    r = Runner(*COARSE, B, H, D, "bf16", pols, **FAST)
+    try:
+        for layer in range(2):
+            q, k, v = _qkv(*COARSE, B, H, D, "bf16", 91 + layer)
+            r.run_layer(layer, q, k, v, check_cache=B * H <= 40, units=[(b, h) for b in (0, B // 2, B - 1) for h in (0, H - 1)])
+    finally:
+        r.close()
+
+
+@pytest.mark.parametrize("B,H", [(1, 2), (9, 32), (35, 16)])
+@pytest.mark.parametrize("D", [64, 128])
+def test_density_of_the_same_forms(D, B, H):
+    """the density by-product on every form: O as amskv_attend leaves it, the masses as the stand-alone kernels do (fp32
+    sums of the same exponentials in another order)"""
+    sides = [tuple(x[i] for i in range(9)) for x in COARSE]
+    pols = [(0, 0, True)]
+    args = (1, H, D, *sides, B, amskv.AMSKV_DTYPE_BF16, pols)
+    arena = torch.empty(amskv.amskv_cache_required_bytes(*args), dtype=torch.uint8, device="cuda")
+    h = amskv.amskv_cache_create(*args, arena=arena)
+    q, k, v = _qkv(*sides, B, H, D, "bf16", 17)
+    try:
+        for s in range(9):
+            amskv.amskv_append_scale(h, 0, s, k[s], v[s])
+            o1, o2 = torch.empty_like(q[s]), torch.empty_like(q[s])
+            m1, m2 = (torch.full((H, amskv.AMSKV_MAX_SCALES), float("nan"), device="cuda") for _ in range(2))
+            lens = amskv.amskv_attend_density(h, 0, s, q[s], o1, m1)
+            amskv.amskv_attend(h, 0, s, q[s], o2)
+            assert amskv.amskv_attention_density_enqueue(h, 0, s, q[s], m2) == lens
+            torch.cuda.synchronize()
+            assert torch.equal(o1.view(torch.int16), o2.view(torch.int16))
+            n = len(lens)
+            assert torch.allclose(m1[:, :n], m2[:, :n], rtol=2e-5, atol=1e-6)
+    finally:
+        amskv.amskv_cache_destroy(h)
