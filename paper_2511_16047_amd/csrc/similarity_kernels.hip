@@ -1,14 +1,13 @@
 // Inter-scale similarity (Eq. 3): scale s-1 is resized bilinearly to the grid of scale s on
 // the fly (never materialised) and compared with scale s, straight from the cache.
-// Bandwidth-bound: each token row is read with 16-byte loads by consecutive lanes.
-// Reduction order is fixed (lanes of a token -> xor tree over a wave -> waves in order -> strided lanes and an xor tree over batch), so the
-// result is deterministic from run to run.
+// Each token row is read with 16-byte loads by consecutive lanes.
+// Reduction order is fixed (lanes of a token -> lanes of a wave -> waves in order -> strided lanes and an xor tree over
+// batch), so the result is deterministic from run to run.
 #include "amskv_internal.hpp"
 
 namespace amskv {
 namespace {
 
-constexpr int kThreads = 256;
 constexpr int kStaticMaxUnits = AMSKV_STATIC_MAX_UNITS;
 constexpr int kMaxDevices = 64;
 
@@ -40,9 +39,9 @@ struct Chunk<false> {
   }
 };
 
-// Source coordinate of the bilinear resize with half-pixel centres, clamped to the grid.
-__device__ __forceinline__ void taps(int dst, int n_in, int n_out, int& i0, int& i1, float& lam) {
-  float src = ((float)dst + 0.5f) * ((float)n_in / (float)n_out) - 0.5f;
+// Source coordinate of the bilinear resize with half-pixel centres, clamped to the grid; scale = n_in / n_out.
+__device__ __forceinline__ void taps(int dst, int n_in, float scale, int& i0, int& i1, float& lam) {
+  float src = ((float)dst + 0.5f) * scale - 0.5f;
   src = fminf(fmaxf(src, 0.f), (float)(n_in - 1));
   const float f = floorf(src);
   i0 = (int)f;
@@ -50,63 +49,101 @@ __device__ __forceinline__ void taps(int dst, int n_in, int n_out, int& i0, int&
   lam = src - f;
 }
 
+// x plus its value in the lane that the cross-lane pattern pairs with this one
+template <int kPattern>
+__device__ __forceinline__ float add_lane(float x) {
+  return x + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), kPattern, 0xf, 0xf, false));
+}
+
+// Sum over the kLanes (8, 16 or 32) consecutive lanes that share a token, in every one of them, on the vector ALU: pairs,
+// quads, then mirrored halves of 8 and of 16 lanes (whose quads, and then halves, already agree).
+template <int kLanes>
+__device__ __forceinline__ float token_sum(float x) {
+  x = add_lane<0xB1>(x);   // quad_perm 1 0 3 2
+  x = add_lane<0x4E>(x);   // quad_perm 2 3 0 1
+  x = add_lane<0x141>(x);  // row_half_mirror
+  if (kLanes >= 16) x = add_lane<0x140>(x);  // row_mirror
+  if (kLanes >= 32) x += __shfl_xor(x, 16, 64);
+  return x;
+}
+
 // grid: (B*H, tensors); one workgroup per (b,h) of one tensor (0 = keys, 1 = values).
 // partial[(tensor*BH + bh)*4 + {0,1,2,3}] = sum_t cos_t, sum a.b, sum |a|^2, sum |b|^2.
-template <bool BF16>
+// Bound: HBM at the fine scales (the rows of scale s once, those of s-1 once and from L2 after that), next to the vector
+// ALU, so what a token costs beside its multiply-adds is kept down: the four bilinear weights are formed once per token,
+// sums over its lanes run on the ALU, and the cosine's square roots and quotient, which every lane of a wave would execute
+// for the one lane that needs them, run once for kLanes passes, each lane of a token keeping the sums of one of them.
+// (di, dj): how far one pass moves a thread's token on the grid.
+template <bool BF16, int kLanes, int kThreads>
 __global__ __launch_bounds__(kThreads) void similarity_partial_kernel(
-    ScaleRef cur_ref, ScaleRef prev_ref, int row_bytes, int heads, int h_cur, int w_cur, int h_prev, int w_prev,
-    float* __restrict__ partial) {
+    ScaleRef cur_ref, ScaleRef prev_ref, int heads, int h_cur, int w_cur, int h_prev, int w_prev, float scale_h, float scale_w,
+    int di, int dj, float* __restrict__ partial) {
   const long long bh = blockIdx.x;
   const char* cur = (const char*)(blockIdx.y ? cur_ref.v : cur_ref.k) + unit_offset(cur_ref.map, bh, heads) +
                     cur_ref.off_tokens * cur_ref.map.tok;
   const char* prev = (const char*)(blockIdx.y ? prev_ref.v : prev_ref.k) + unit_offset(prev_ref.map, bh, heads) +
                      prev_ref.off_tokens * prev_ref.map.tok;
   const long long cur_tok = cur_ref.map.tok, prev_tok = prev_ref.map.tok;
-  const int lpt = row_bytes >> 4;          // lanes per token: 8, 16 or 32
-  const int sub = threadIdx.x % lpt;       // which 16-byte piece of the row
-  const int slot = threadIdx.x / lpt;
-  const int tok_per_pass = kThreads / lpt;
+  const int sub = threadIdx.x % kLanes;    // which 16-byte piece of the row
+  const int slot = threadIdx.x / kLanes;
+  constexpr int kPerPass = kThreads / kLanes;
   const int t_cur = h_cur * w_cur;
+  cur += sub << 4;
+  prev += sub << 4;
 
   float acc_cos = 0.f, acc_ab = 0.f, acc_aa = 0.f, acc_bb = 0.f;
-  for (int t0 = 0; t0 < t_cur; t0 += tok_per_pass) {
+  float kept_ab = 0.f, kept_aa = 0.f, kept_bb = 0.f;  // the token whose cosine this lane takes next
+  auto take_cosine = [&]() {
+    acc_cos += kept_ab / fmaxf(sqrtf(kept_aa) * sqrtf(kept_bb), 1e-12f);  // 0 where nothing is kept
+    kept_ab = kept_aa = kept_bb = 0.f;
+  };
+  int i = slot / w_cur, j = slot - i * w_cur, pass = 0;
+  for (int t0 = 0; t0 < t_cur; t0 += kPerPass) {
     const int t = t0 + slot;
     float ab = 0.f, aa = 0.f, bb = 0.f;
     if (t < t_cur) {
-      const int i = t / w_cur, j = t - i * w_cur;
       int r0, r1, c0, c1;
       float lr, lc;
-      taps(i, h_prev, h_cur, r0, r1, lr);
-      taps(j, w_prev, w_cur, c0, c1, lc);
+      taps(i, h_prev, scale_h, r0, r1, lr);
+      taps(j, w_prev, scale_w, c0, c1, lc);
       Chunk<BF16> a, p00, p01, p10, p11;
-      a.load(cur + t * cur_tok + (sub << 4));
-      p00.load(prev + (r0 * w_prev + c0) * prev_tok + (sub << 4));
-      p01.load(prev + (r0 * w_prev + c1) * prev_tok + (sub << 4));
-      p10.load(prev + (r1 * w_prev + c0) * prev_tok + (sub << 4));
-      p11.load(prev + (r1 * w_prev + c1) * prev_tok + (sub << 4));
+      a.load(cur + t * cur_tok);
+      p00.load(prev + (r0 * w_prev + c0) * prev_tok);
+      p01.load(prev + (r0 * w_prev + c1) * prev_tok);
+      p10.load(prev + (r1 * w_prev + c0) * prev_tok);
+      p11.load(prev + (r1 * w_prev + c1) * prev_tok);
+      const float w00 = (1.f - lr) * (1.f - lc), w01 = (1.f - lr) * lc, w10 = lr * (1.f - lc), w11 = lr * lc;
 #pragma unroll
       for (int e = 0; e < Chunk<BF16>::N; ++e) {
-        const float left = p00.v[e] * (1.f - lr) + p10.v[e] * lr;    // rows first,
-        const float right = p01.v[e] * (1.f - lr) + p11.v[e] * lr;
-        const float b = left * (1.f - lc) + right * lc;              // then columns
-        ab += a.v[e] * b;
-        aa += a.v[e] * a.v[e];
-        bb += b * b;
+        const float b = fmaf(w11, p11.v[e], fmaf(w10, p10.v[e], fmaf(w01, p01.v[e], w00 * p00.v[e])));
+        ab = fmaf(a.v[e], b, ab);
+        aa = fmaf(a.v[e], a.v[e], aa);
+        bb = fmaf(b, b, bb);
       }
     }
-    // sum over the lanes that share a token (lpt is a power of two <= 32)
-    for (int m = 1; m < lpt; m <<= 1) {
-      ab += __shfl_xor(ab, m, 64);
-      aa += __shfl_xor(aa, m, 64);
-      bb += __shfl_xor(bb, m, 64);
+    acc_ab += ab;
+    acc_aa += aa;
+    acc_bb += bb;
+    ab = token_sum<kLanes>(ab);
+    aa = token_sum<kLanes>(aa);
+    bb = token_sum<kLanes>(bb);
+    if (sub == pass) {
+      kept_ab = ab;
+      kept_aa = aa;
+      kept_bb = bb;
     }
-    if (sub == 0 && t < t_cur) {
-      acc_cos += ab / fmaxf(sqrtf(aa) * sqrtf(bb), 1e-12f);
-      acc_ab += ab;
-      acc_aa += aa;
-      acc_bb += bb;
+    if (++pass == kLanes) {
+      take_cosine();
+      pass = 0;
+    }
+    i += di;
+    j += dj;
+    if (j >= w_cur) {
+      j -= w_cur;
+      ++i;
     }
   }
+  take_cosine();
 
   // workgroup sum in a fixed order: xor tree over the lanes of a wave, then the waves in ascending order
   float acc[4] = {acc_cos, acc_ab, acc_aa, acc_bb};
@@ -123,6 +160,16 @@ __global__ __launch_bounds__(kThreads) void similarity_partial_kernel(
     for (int w = 1; w < kThreads / 64; ++w) total += red[w][threadIdx.x];
     partial[((long long)blockIdx.y * gridDim.x + bh) * 4 + threadIdx.x] = total;
   }
+}
+
+template <bool BF16, int kLanes, int kThreads>
+hipError_t launch_partial(const ScaleRef& cur, const ScaleRef& prev, int bh, int heads, int h_cur, int w_cur, int h_prev, int w_prev,
+                          float* partial_ws, hipStream_t st) {
+  constexpr int kPerPass = kThreads / kLanes;
+  hipLaunchKernelGGL((similarity_partial_kernel<BF16, kLanes, kThreads>), dim3(bh, cur.v && prev.v ? 2 : 1), dim3(kThreads), 0, st, cur,
+                     prev, heads, h_cur, w_cur, h_prev, w_prev, (float)h_prev / (float)h_cur, (float)w_prev / (float)w_cur,
+                     kPerPass / w_cur, kPerPass % w_cur, partial_ws);
+  return hipGetLastError();
 }
 
 // totals[(tensor*H + h)*4 + q] = sum over b of partial[(tensor*B*H + b*H + h)*4 + q].
@@ -201,15 +248,18 @@ hipError_t launch_similarity(const ScaleRef& cur, const ScaleRef& prev, int batc
                              float* out_dev, hipStream_t st) {
   const int tensors = (cur.v && prev.v) ? 2 : 1;
   const int bh = batch * heads;
-  dim3 grid(bh, tensors), block(kThreads);
-  if (dtype == AMSKV_DTYPE_BF16) {
-    hipLaunchKernelGGL(similarity_partial_kernel<true>, grid, block, 0, st, cur, prev, head_dim * 2, heads, h_cur,
-                       w_cur, h_prev, w_prev, partial_ws);
-  } else {
-    hipLaunchKernelGGL(similarity_partial_kernel<false>, grid, block, 0, st, cur, prev, head_dim * 4, heads, h_cur,
-                       w_cur, h_prev, w_prev, partial_ws);
-  }
-  hipError_t e = hipGetLastError();
+  // a lone workgroup per CU or less: four times the threads, so that a (b,h) takes a quarter of the passes
+  const bool few = (long long)bh * tensors < 512;
+  auto go = [&](auto f_many, auto f_few) {
+    return (few ? f_few : f_many)(cur, prev, bh, heads, h_cur, w_cur, h_prev, w_prev, partial_ws, st);
+  };
+  hipError_t e;
+  if (dtype == AMSKV_DTYPE_BF16)
+    e = head_dim == 64 ? go(launch_partial<true, 8, 256>, launch_partial<true, 8, 1024>)
+                       : go(launch_partial<true, 16, 256>, launch_partial<true, 16, 1024>);
+  else
+    e = head_dim == 64 ? go(launch_partial<false, 16, 256>, launch_partial<false, 16, 1024>)
+                       : go(launch_partial<false, 32, 256>, launch_partial<false, 32, 1024>);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(similarity_total_kernel, dim3(tensors * heads), dim3(64), 0, st, (const float*)partial_ws, batch,
                      heads, out_dev);
