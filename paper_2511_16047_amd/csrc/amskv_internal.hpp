@@ -107,6 +107,32 @@ struct NewRanges {
 };
 
 #if defined(__HIPCC__)
+// x plus its value in the lane that the cross-lane pattern pairs with this one, on the vector ALU
+template <int kPattern>
+__device__ __forceinline__ float add_lane(float x) {
+  return x + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), kPattern, 0xf, 0xf, false));
+}
+
+// Sum over the kLanes (8, 16 or 32) consecutive lanes of an aligned group, in every one of them: pairs, quads, then
+// mirrored halves of 8 and of 16 lanes (whose quads, and then halves, already agree).
+template <int kLanes>
+__device__ __forceinline__ float group_sum(float x) {
+  x = add_lane<0xB1>(x);   // quad_perm 1 0 3 2
+  x = add_lane<0x4E>(x);   // quad_perm 2 3 0 1
+  x = add_lane<0x141>(x);  // row_half_mirror
+  if (kLanes >= 16) x = add_lane<0x140>(x);  // row_mirror
+  if (kLanes >= 32) x += __shfl_xor(x, 16, 64);
+  return x;
+}
+
+// Sum of x over the two lane halves (lanes l and l^32), in every lane.
+__device__ __forceinline__ float half_sum(float x) {
+  const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_int(x), __float_as_int(x), false, false);
+  return __int_as_float(sw[0]) + __int_as_float(sw[1]);
+}
+#endif
+
+#if defined(__HIPCC__)
 // Byte offset of row 0 of unit bh = b*heads + h inside a caller tensor.
 __device__ __forceinline__ long long unit_offset(const RowMap& m, long long bh, int heads) {
   if (m.batch == m.head * heads) return bh * m.head;  // units back to back (head-major tensors): no division

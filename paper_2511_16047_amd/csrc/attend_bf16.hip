@@ -664,18 +664,22 @@ __device__ __forceinline__ void attend_unit(
         const int cut = next_end - blk_start;  // <= 32, wave-uniform (< 1: ended in a block of the other slice)
 #pragma unroll
         for (int n = 0; n < NQ; ++n) {
+          // (eight keys -- four of either lane half -- are skipped, taken whole or looked at one by one: cut is uniform)
           float upto = sum[n][0];
           if (cut < 32) {
             upto = 0.f;
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-              const int key = 8 * (v >> 2) + 4 * h + (v & 3);
-              const float pv = __builtin_amdgcn_exp2f(fmaf(sacc[n][v], scale_log2e, -run_mc[n]));
-              upto += key < cut ? pv : 0.f;
+            for (int i = 0; i < 4; ++i) {
+              if (8 * i >= cut) break;
+              const int mine = 8 * i + 8 <= cut ? 4 : cut - 8 * i - 4 * h;  // of this lane's four keys
+#pragma unroll
+              for (int e = 0; e < 4; ++e) {
+                const float pv = __builtin_amdgcn_exp2f(fmaf(sacc[n][4 * i + e], scale_log2e, -run_mc[n]));
+                upto += e < mine ? pv : 0.f;
+              }
             }
           }
-          float gsum = seg_acc[n] + (upto - taken[n]);
-          gsum += __shfl_xor(gsum, 32, 64);  // the two lane halves hold different keys of the same query
+          const float gsum = half_sum(seg_acc[n] + (upto - taken[n]));  // the lane halves hold different keys of a query
           if (h == 0) park[wave * NQ + n][cur_group][r] = gsum;
           seg_acc[n] = 0.f;
           taken[n] = upto;
@@ -762,7 +766,7 @@ __device__ __forceinline__ void attend_unit(
     run_sum[0] += __shfl_xor(run_sum[0], 32, 64);
     if constexpr (kDensity) {  // groups that end behind this slice's last block
       for (; cur_group < groups.n; ++cur_group) {
-        const float gsum = seg_acc[0] + __shfl_xor(seg_acc[0], 32, 64);
+        const float gsum = half_sum(seg_acc[0]);
         if (h == 0) park[wave][cur_group][r] = gsum;
         seg_acc[0] = 0.f;
       }
@@ -837,13 +841,12 @@ __device__ __forceinline__ void attend_unit(
       // mass of the query block on group p = sum over its valid rows of (sum of exp over the group) / (sum over all keys)
       const int n_qblk = (t_q + 31) >> 5;
       const long long qblk = bh * n_qblk + (q_base >> 5) + n;
-      for (int p = slice; p < groups.n; p += kSplit) {
-        float gsum = park[wave * NQ + n][p][r];
-        if (kSplit > 1) gsum = fmaf(w_theirs, park[other][p][r], w_mine * gsum);
-        float m = h == 0 && row < t_q ? gsum * inv : 0.f;
-#pragma unroll
-        for (int d = 16; d >= 1; d >>= 1) m += __shfl_xor(m, d, 64);  // over the 32 query rows (lower lane half)
-        if (lane == 0) partial[qblk * AMSKV_MAX_SCALES + p] = m;
+      for (int p0 = 2 * slice; p0 < groups.n; p0 += 2 * kSplit) {  // a group per lane half
+        const int p = p0 + h, at = min(p, groups.n - 1);
+        float gsum = park[wave * NQ + n][at][r];
+        if (kSplit > 1) gsum = fmaf(w_theirs, park[other][at][r], w_mine * gsum);
+        const float m = group_sum<32>(row < t_q ? gsum * inv : 0.f);  // over the 32 query rows
+        if (r == 0 && p < groups.n) partial[qblk * AMSKV_MAX_SCALES + p] = m;
       }
     }
   }

@@ -148,11 +148,11 @@ __global__ __launch_bounds__(64 * waves_of(kSplit), !kDensity ? (D == 64 ? 4 : 2
 
   // density: group the stream is in, its end, where the part of it that this block holds begins, sum so far
   int group = 0, next_end = kDensity ? groups.end[0] : 0;
-  float group_sum = 0.f;
+  float in_group = 0.f;
   auto park_group = [&]() {
-    const float x = group_sum + __shfl_xor(group_sum, 32, 64);  // the lane halves hold different keys of a query
+    const float x = half_sum(in_group);  // the lane halves hold different keys of a query
     if (h == 0) park[wave][group][r] = make_float2(x, run_max);
-    group_sum = 0.f;
+    in_group = 0.f;
     ++group;
     next_end = group < groups.n ? groups.end[group] : 0x7fffffff;
   };
@@ -224,13 +224,13 @@ __global__ __launch_bounds__(64 * waves_of(kSplit), !kDensity ? (D == 64 ? 4 : 2
     }
     run_sum = sum;
     if constexpr (kDensity) {
-      group_sum *= alpha;
+      in_group *= alpha;
       // keys [from, to) of the block belong to the group
       auto take = [&](int from, int to) {
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
           const int key = 8 * (v >> 2) + 4 * h + (v & 3);
-          group_sum += key >= from && key < to ? sacc[v] : 0.f;
+          in_group += key >= from && key < to ? sacc[v] : 0.f;
         }
       };
       int from = 0;
@@ -339,14 +339,13 @@ __global__ __launch_bounds__(64 * waves_of(kSplit), !kDensity ? (D == 64 ? 4 : 2
       }
       return x;
     };
-    float all = 0.f;
-    for (int p = 0; p < groups.n; ++p) all += mass(p);
-    const float inv_all = h == 0 && row < t_q ? 1.0f / all : 0.f;
-    for (int p = slice; p < groups.n; p += kSplit) {
-      float m = mass(p) * inv_all;
-#pragma unroll
-      for (int d = 16; d >= 1; d >>= 1) m += __shfl_xor(m, d, 64);  // over the 32 query rows (lower lane half)
-      if (lane == 0) partial[(bh * n_qblk + q_blk) * AMSKV_MAX_SCALES + p] = m;
+    float all = 0.f;  // (either lane half takes every second group)
+    for (int p = h; p < groups.n; p += 2) all += mass(p);
+    const float inv_all = row < t_q ? 1.0f / half_sum(all) : 0.f;
+    for (int p0 = 2 * slice; p0 < groups.n; p0 += 2 * kSplit) {
+      const int p = p0 + h;
+      const float m = group_sum<32>(mass(min(p, groups.n - 1)) * inv_all);  // over the 32 query rows
+      if (r == 0 && p < groups.n) partial[(bh * n_qblk + q_blk) * AMSKV_MAX_SCALES + p] = m;
     }
   }
 }

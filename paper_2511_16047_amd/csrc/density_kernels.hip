@@ -178,12 +178,12 @@ __global__ __launch_bounds__(64 * kWavesPerGroup) void density_partial_f32_kerne
 
 // out[h][p] = (1/B) * sum over batch and query blocks of partial[(b,h), block][p], fixed order:
 // thread = p + 16*part walks every kParts-th unit of the head, four independent sums at a time (the loads are
-// what the kernel waits for), then a tree over the parts in LDS.
+// what the kernel waits for), then the parts of a wave across its lanes and the waves through LDS.
 constexpr int kParts = 64;
 __global__ __launch_bounds__(16 * kParts) void density_total_kernel(const float* __restrict__ partial, int batch,
                                                                     int heads, int n_qblk, int n_seg,
                                                                     float* __restrict__ out) {
-  __shared__ float red[kParts][16];
+  __shared__ float red[kParts / 4][16];
   const int hd = blockIdx.x;
   const int p = threadIdx.x & 15, part = threadIdx.x >> 4;
   float acc[4] = {0.f, 0.f, 0.f, 0.f};
@@ -202,13 +202,16 @@ __global__ __launch_bounds__(16 * kParts) void density_total_kernel(const float*
     }
     for (; i < per_head; i += kParts) acc[0] += at(i);
   }
-  red[part][p] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+  float sum = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+  sum += __shfl_xor(sum, 16, 64);  // the four parts of a wave, then the waves in ascending order
+  sum += __shfl_xor(sum, 32, 64);
+  if ((part & 3) == 0) red[part >> 2][p] = sum;
   __syncthreads();
-  for (int m = kParts / 2; m > 0; m >>= 1) {
-    if (part < m) red[part][p] += red[part + m][p];
-    __syncthreads();
-  }
-  if (part == 0) out[hd * AMSKV_MAX_SCALES + p] = p < n_seg ? red[0][p] / (float)batch : 0.f;
+  if (part != 0) return;
+  float total = 0.f;
+#pragma unroll
+  for (int w = 0; w < kParts / 4; ++w) total += red[w][p];
+  out[hd * AMSKV_MAX_SCALES + p] = p < n_seg ? total / (float)batch : 0.f;
 }
 
 }  // namespace

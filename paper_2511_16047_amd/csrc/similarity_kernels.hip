@@ -49,24 +49,6 @@ __device__ __forceinline__ void taps(int dst, int n_in, float scale, int& i0, in
   lam = src - f;
 }
 
-// x plus its value in the lane that the cross-lane pattern pairs with this one
-template <int kPattern>
-__device__ __forceinline__ float add_lane(float x) {
-  return x + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), kPattern, 0xf, 0xf, false));
-}
-
-// Sum over the kLanes (8, 16 or 32) consecutive lanes that share a token, in every one of them, on the vector ALU: pairs,
-// quads, then mirrored halves of 8 and of 16 lanes (whose quads, and then halves, already agree).
-template <int kLanes>
-__device__ __forceinline__ float token_sum(float x) {
-  x = add_lane<0xB1>(x);   // quad_perm 1 0 3 2
-  x = add_lane<0x4E>(x);   // quad_perm 2 3 0 1
-  x = add_lane<0x141>(x);  // row_half_mirror
-  if (kLanes >= 16) x = add_lane<0x140>(x);  // row_mirror
-  if (kLanes >= 32) x += __shfl_xor(x, 16, 64);
-  return x;
-}
-
 // grid: (B*H, tensors); one workgroup per (b,h) of one tensor (0 = keys, 1 = values).
 // partial[(tensor*BH + bh)*4 + {0,1,2,3}] = sum_t cos_t, sum a.b, sum |a|^2, sum |b|^2.
 // Bound: HBM at the fine scales (the rows of scale s once, those of s-1 once and from L2 after that), next to the vector
@@ -124,9 +106,9 @@ __global__ __launch_bounds__(kThreads) void similarity_partial_kernel(
     acc_ab += ab;
     acc_aa += aa;
     acc_bb += bb;
-    ab = token_sum<kLanes>(ab);
-    aa = token_sum<kLanes>(aa);
-    bb = token_sum<kLanes>(bb);
+    ab = group_sum<kLanes>(ab);
+    aa = group_sum<kLanes>(aa);
+    bb = group_sum<kLanes>(bb);
     if (sub == pass) {
       kept_ab = ab;
       kept_aa = aa;
