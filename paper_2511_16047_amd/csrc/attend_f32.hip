@@ -3,7 +3,7 @@
 //
 // What bounds it: all query rows of a (b,h) share its keys, so wherever there are enough units the fp32 matrix pipe
 // (v_mfma_f32_32x32x2_f32 and 16x16x4: 157 TFLOP/s nominal, 154 measured on a large product) is the limit, not memory.
-// Measured: 256 (b,h) x 256 queries x 680 keys 264 -> 109 us (43 -> 104 TFLOP/s) against a kernel that kept four lanes
+// Measured: 256 (b,h) x 256 queries x 680 keys 264 -> 108 us (43 -> 105 TFLOP/s) against a kernel that kept four lanes
 // to a query row and fed the vector ALUs from LDS; 16 (b,h), the same lengths: 124 -> 14 us (one image, where that
 // kernel had 64 workgroups with one serial chain of keys each).
 //
@@ -14,12 +14,15 @@
 // The head dim is dealt to the lane groups in runs (group g of H holds channels [g*D/H, (g+1)*D/H) of its K and Q
 // rows), so a lane reads 16-byte pieces; the rows of V are read whole, D/QT channels per lane.
 //
-// Memory.  Every wave streams its own K and V blocks through its own piece of LDS with direct-to-LDS loads (whole rows,
-// coalesced; the 16-byte chunks of K rows are XOR-swizzled on the global side so that 16 lanes reading one chunk of 16
-// rows hit 16 different bank groups).  A block's 64 matrix instructions take 4096 cycles at head dim 64 for 16 KB, so
-// one buffer per tensor is enough: K of the next block is requested behind the score products, V behind the second
-// product, each half a block ahead of its use, and nothing in the loop synchronises waves.  (K straight from memory
-// into registers touches 16 lines per quarter wave and instruction and kept the matrix pipe at half its rate.)
+// Memory.  K and V blocks come through LDS with direct-to-LDS loads (whole rows, coalesced; the 16-byte chunks of K rows are
+// XOR-swizzled on the global side so that 16 lanes reading one chunk of 16 rows hit 16 different bank groups).  (K straight
+// from memory into registers touches 16 lines per quarter wave and instruction and kept the matrix pipe at half its rate.)
+// The four waves of a workgroup that each hold a block of query rows of one (b,h) walk the same keys and fetch each block
+// once, a quarter per wave, into a ring: two blocks on the way, one in use, one whose V is still multiplied, one barrier per
+// block.  Against a stream per wave (four times the traffic from L2 and one block of slack): 256 (b,h), 256 x 680 118 -> 108
+// us, 169 x 424 65 -> 61; 1024 (b,h), 256 x 680 409 -> 383; head dim 128, 32 (b,h), 1024 x 1621 269 -> 241 us (113 TFLOP/s).
+// Where a unit's keys are split over waves every wave has a stream of its own: K of its next block is requested behind the
+// score products, V behind the second product, each half a block ahead of its use, and nothing in the loop synchronises waves.
 //
 // Few units (one image): the keys of a unit are dealt block by block to kSplit waves of a workgroup, each with its
 // own online softmax; their partial results meet in LDS once, behind one barrier.
@@ -55,8 +58,12 @@ struct Mfma<16> {
 };
 
 constexpr int waves_of(int split) { return split == 8 ? 8 : 4; }
-// per wave: a block of K and one of V (the K piece later holds the wave's partial result), and its softmax statistics
-constexpr int lds_bytes(int D, int QT, int split) { return waves_of(split) * (2 * QT * D * 4 + (split > 1 ? QT * 8 : 0)); }
+// split: per wave a block of K and one of V (the K piece later holds the wave's partial result), and its softmax statistics;
+// else a ring of blocks for the workgroup
+constexpr int kRing = 4;
+constexpr int lds_bytes(int D, int QT, int split) {
+  return split > 1 ? waves_of(split) * (2 * QT * D * 4 + QT * 8) : kRing * 2 * QT * D * 4;
+}
 
 #define AMSKV_LDS __attribute__((address_space(3)))
 
@@ -119,9 +126,13 @@ __global__ __launch_bounds__(64 * waves_of(kSplit), 2) void attend_f32_kernel(
   const char* xv = (const char*)ext_kv.v + x_unit;
   // fused append: the blocks of the current scale are dealt to the units of the (b,h), so that none lags behind
   const bool write_back = writes_back(ext_kv, seg.total, seg.ext_start);
-  const int n_qblk = (t_q + QT - 1) / QT, my_qblk = q_base / QT;
-  char* lds_k = lds + wave * 2 * kBlk;
-  char* lds_v = lds_k + kBlk;
+  const int n_qblk = (t_q + QT - 1) / QT, my_qblk = kSplit == 1 ? (int)(within >> 3) : q_base / QT;
+  constexpr bool kShared = kSplit == 1;  // the waves of the workgroup walk the same blocks and fetch them together
+  char* lds_k = lds + (kShared ? 0 : wave * 2 * kBlk);  // shared: ring slot of the block in use
+  char* lds_v = lds_k + kBlk;                           // shared: ring slot of the block whose V is multiplied
+  constexpr int kMyLoads = kShared ? kLoads / kWaves : kLoads;  // direct-to-LDS loads of this wave, per block and tensor
+  static_assert(kMyLoads >= 1 && (!kShared || kMyLoads * kWaves == kLoads), "the waves share a block evenly");
+  const int first_load = kShared ? wave * kMyLoads : 0;
 
   f32x4 qf[NC];
   if (active) {
@@ -133,12 +144,12 @@ __global__ __launch_bounds__(64 * waves_of(kSplit), 2) void attend_f32_kernel(
   // Rows of key block b -> LDS.  Lane i of load k fills chunk position i % CPR of row k * kRowsPerLoad + i / CPR; for K
   // that position holds global chunk position ^ (row & 15).  A block inside one segment (wave-uniform, nearly always)
   // is addressed from one scalar base; elsewhere every lane looks its row up (rows past the end re-read the last one).
-  // Both are left with exactly kLoads loads in flight.
+  // Both are left with exactly kMyLoads loads in flight.
   // The segment looked up last is kept: the table is walked again only when a block begins outside it.
   int seg_lo = 0, seg_end = 0, seg_delta = 0;
   auto load = [&](int b, bool is_v) {
     const int j0 = b * QT;
-    char* dst = is_v ? lds_v : lds_k;
+    char* dst = kShared ? lds + (b % kRing) * 2 * kBlk + (is_v ? kBlk : 0) : is_v ? lds_v : lds_k;
     if (__builtin_expect(j0 < seg_lo || j0 >= seg_end, 0)) {
       seg_lo = seg.virt_start[0], seg_end = seg_lo + seg.len[0], seg_delta = seg.phys_off[0] - seg_lo;
       for (int i = 1; i < seg.n; ++i)
@@ -159,14 +170,14 @@ __global__ __launch_bounds__(64 * waves_of(kSplit), 2) void attend_f32_kernel(
     if (__builtin_expect(j0 + QT <= seg_end && st < (1ll << 24), 1)) {
       const char* base = (in_ext ? (is_v ? xv : xk) : (is_v ? vb : kb)) + (long long)(j0 + seg_delta) * st;
 #pragma unroll
-      for (int k = 0; k < kLoads; ++k) {
+      for (int k = first_load; k < first_load + kMyLoads; ++k) {
         const int row = k * kRowsPerLoad + row0;
         lds_dma16_s(base, row * (unsigned)st + 16 * (is_v ? pos : pos ^ (row & 15)), dst + k * 1024);
       }
       return;
     }
 #pragma unroll
-    for (int k = 0; k < kLoads; ++k) {
+    for (int k = first_load; k < first_load + kMyLoads; ++k) {
       const int row = k * kRowsPerLoad + row0;
       bool ext;
       const long long at = locate_row(seg, min(j0 + row, t_kv - 1), ext);
@@ -179,14 +190,14 @@ __global__ __launch_bounds__(64 * waves_of(kSplit), 2) void attend_f32_kernel(
   // Returns whether it issued exactly kLoads stores (the counted waits behind it then need not wait for them).
   auto store_rows = [&](int b, bool is_v) {
     const int j0 = b * QT;
-    if (j0 + QT <= seg.ext_start || b % n_qblk != my_qblk) return false;
-    const char* src = is_v ? lds_v : lds_k;
+    if (j0 + QT <= seg.ext_start || b % (kShared ? n_parts : n_qblk) != my_qblk) return false;
+    const char* src = kShared ? lds + (b % kRing) * 2 * kBlk + (is_v ? kBlk : 0) : is_v ? lds_v : lds_k;
     char* dst = is_v ? vb : kb;
     const int row0 = lane / CPR, pos = lane % CPR;
     if (__builtin_expect(j0 >= seg.ext_start && j0 >= ext_kv.wb_from && j0 + QT <= t_kv, 1)) {  // every row moves by wb_delta
       dst += (long long)(j0 + ext_kv.wb_delta) * RB;
 #pragma unroll
-      for (int k = 0; k < kLoads; ++k) {
+      for (int k = first_load; k < first_load + kMyLoads; ++k) {
         const int row = k * kRowsPerLoad + row0;
         *reinterpret_cast<f32x4*>(dst + row * RB + 16 * (is_v ? pos : pos ^ (row & 15))) =
             *reinterpret_cast<const f32x4*>(src + k * 1024 + 16 * lane);
@@ -194,7 +205,7 @@ __global__ __launch_bounds__(64 * waves_of(kSplit), 2) void attend_f32_kernel(
       return true;
     }
 #pragma unroll
-    for (int k = 0; k < kLoads; ++k) {
+    for (int k = first_load; k < first_load + kMyLoads; ++k) {
       const int row = k * kRowsPerLoad + row0, j = j0 + row;
       const int to = write_back_row(ext_kv, j, t_kv, seg.ext_start);
       if (j >= seg.ext_start && to >= 0)
@@ -254,7 +265,7 @@ __global__ __launch_bounds__(64 * waves_of(kSplit), 2) void attend_f32_kernel(
     const int j0 = b * QT;
     const bool more = b + kSplit < n_blocks;
     rescale();
-    if (!first) wait_younger(stored_v);  // K of this block; V of the block before may still be on the way
+    if (!kShared && !first) wait_younger(stored_v);  // K of this block; V of the block before may still be on the way
     // Four partial sums per dot product where registers allow: a chain of D products rounds D times.  Error of the result
     // against 64 bits, one chain / four: 16 (b,h), 25 queries x 55 keys 2.5e-7 / 1.5e-7, 256 x 680 3.4e-7 / 2.3e-7, head dim
     // 128, 400 x 677 4.3e-7 / 2.5e-7; the time is the same.
@@ -273,9 +284,12 @@ __global__ __launch_bounds__(64 * waves_of(kSplit), 2) void attend_f32_kernel(
     typename M::Acc s;
 #pragma unroll
     for (int v = 0; v < NV; ++v) s[v] = kChains == 4 ? (part[0][v] + part[1][v]) + (part[2 % kChains][v] + part[3 % kChains][v]) : part[0][v];
-    const bool stored_k = write_back && store_rows(b, false);
-    wait_lds_reads();
-    if (more) load(b + kSplit, false);
+    bool stored_k = false;
+    if constexpr (!kShared) {
+      stored_k = write_back && store_rows(b, false);
+      wait_lds_reads();
+      if (more) load(b + kSplit, false);
+    }
     if (__builtin_expect(j0 + QT > t_kv, 0)) {
 #pragma unroll
       for (int v = 0; v < NV; ++v)
@@ -285,8 +299,10 @@ __global__ __launch_bounds__(64 * waves_of(kSplit), 2) void attend_f32_kernel(
     // enough.  Only where it was not (always in the first block) is the maximum taken.
     float sum = INFINITY;
     if (!first) {
-      if (more) wait_younger(stored_k);  // V of the block before; the next K may still be on the way
-      else wait_vmcnt<0>();
+      if constexpr (!kShared) {
+        if (more) wait_younger(stored_k);  // V of the block before; the next K may still be on the way
+        else wait_vmcnt<0>();
+      }
       sum = 0.f;
 #pragma unroll
       for (int v = 0; v < NV; ++v) {
@@ -294,10 +310,12 @@ __global__ __launch_bounds__(64 * waves_of(kSplit), 2) void attend_f32_kernel(
         pf[v] = __builtin_amdgcn_exp2f((s[v] - run_ref) * scale_log2e);
         sum += pf[v];
       }
-      stored_v = write_back && store_rows(b - kSplit, true);
-      wait_lds_reads();
+      if constexpr (!kShared) {
+        stored_v = write_back && store_rows(b - kSplit, true);
+        wait_lds_reads();
+      }
     }
-    load(b, true);
+    if constexpr (!kShared) load(b, true);
     moved = __builtin_amdgcn_ballot_w64(!(sum <= kTripSum)) != 0;
     if (__builtin_expect(moved, 0)) {
       float mx = s[0];
@@ -319,7 +337,41 @@ __global__ __launch_bounds__(64 * waves_of(kSplit), 2) void attend_f32_kernel(
     }
     run_sum += sum;
   };
-  if (active && slice < n_blocks) {
+  if constexpr (kShared) {
+    // Two blocks are on their way while one is in use and the V of the one before it still is: the barrier of block b
+    // makes it readable and frees the slot of block b - 2, which block b + 2 is requested into.
+    for (int b = 0; b < 2 && b < n_blocks; ++b) {
+      load(b, false);
+      load(b, true);
+    }
+    if (active) {
+#pragma unroll
+      for (int i = 0; i < NC; ++i) asm volatile("" : "+v"(qf[i]));  // the Q rows have landed
+    }
+    for (int b = 0; b < n_blocks; ++b) {
+      if (b + 1 < n_blocks) wait_vmcnt<2 * kMyLoads>();  // (stores in between only make this stricter)
+      else wait_vmcnt<0>();
+      __syncthreads();
+      if (write_back) {
+        store_rows(b, false);
+        store_rows(b, true);
+      }
+      if (b + 2 < n_blocks) {
+        load(b + 2, false);
+        load(b + 2, true);
+      }
+      if (active) {
+        lds_k = lds + (b % kRing) * 2 * kBlk;
+        lds_v = lds + ((b + kRing - 1) % kRing) * 2 * kBlk + kBlk;
+        step(b, b == 0);
+      }
+    }
+    if (!active) return;
+    rescale();
+    lds_v = lds + ((n_blocks - 1) % kRing) * 2 * kBlk + kBlk;
+#pragma unroll
+    for (int v = 0; v < NV; ++v) multiply_v(v);
+  } else if (active && slice < n_blocks) {
     load(slice, false);
 #pragma unroll
     for (int i = 0; i < NC; ++i) asm volatile("" : "+v"(qf[i]));  // the Q rows have landed, and
@@ -413,7 +465,7 @@ hipError_t launch(const void* q, void* o, void* kc, void* vc, int bh, int t_q, i
 // of a wave plus what starting and merging costs.  Two workgroups of 32-row units fit a CU, and the dispatcher fills a
 // CU before it goes to the next, so a last round of them counts double.  A 16-row block is a quarter of a 32-row one's
 // work at nine tenths of its rate.  Against the best of the eight variants on 24 shapes (16 to 1024 (b,h), 9 to 2000
-// queries, 14 to 4000 keys) the choice lost 5 % at most.
+// queries, 14 to 4000 keys) the choice lost 9 % at most, 2 % on average.
 struct Choice {
   int qt, split;
 };
