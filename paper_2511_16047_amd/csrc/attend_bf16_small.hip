@@ -83,10 +83,9 @@ __global__ __launch_bounds__(64 * waves_of(kSplit), !kDensity ? (D == 64 ? 4 : 2
   const int lane = threadIdx.x & 63;
   const int slice = kSplit == 1 ? 0 : wave;
   int bh_i, q_blk;
-  if (kSplit == 1) {
-    const int unit = blockIdx.x * kWaves + wave;
-    bh_i = unit / n_qblk;
-    q_blk = unit - bh_i * n_qblk;
+  if (kSplit == 1) {  // launched with one block of queries only
+    bh_i = blockIdx.x * kWaves + wave;
+    q_blk = 0;
   } else {  // the workgroups of one (b,h) get ids 8 apart: they run on one XCD and share its L2
     const unsigned per_group = 8u * n_qblk, group = blockIdx.x / per_group, within = blockIdx.x - group * per_group;
     bh_i = group * 8 + (within & 7);
@@ -121,16 +120,30 @@ __global__ __launch_bounds__(64 * waves_of(kSplit), !kDensity ? (D == 64 ? 4 : 2
   auto load_block = [&](int g, int buffer) {
     const int j0 = 32 * g;
     char* dst = lds_v[wave][buffer];
+    // The rows this lane fetches -- VCH of V, one of K -- and where they sit: one walk of the segment table for all of them,
+    // four entries per step.  (One walk per row and one entry at a time was a chain of up to 25 scalar-load waits in front of
+    // the first load: 16-layer stack on one image 1003 -> 928 us a pass.)
+    int at[VCH + 1], delta[VCH + 1];
+#pragma unroll
+    for (int k = 0; k <= VCH; ++k) {
+      at[k] = min(j0 + (k < VCH ? k * (64 / CPR) + lane / CPR : r), t_kv - 1);
+      delta[k] = 0;
+    }
+    for (int i0 = 0; i0 < seg.n; i0 += 4) {
+#pragma unroll
+      for (int i = i0; i < i0 + 4; ++i) {
+        const int from = i < seg.n ? seg.virt_start[i] : 0x7fffffff, by = seg.phys_off[i] - seg.virt_start[i];
+#pragma unroll
+        for (int k = 0; k <= VCH; ++k) delta[k] = at[k] >= from ? by : delta[k];
+      }
+    }
 #pragma unroll
     for (int k = 0; k < VCH; ++k) {
       const int row = k * (64 / CPR) + lane / CPR, c = (lane % CPR) ^ (row & 7);
-      bool vext;
-      const long long vrow = locate_row(seg, min(j0 + row, t_kv - 1), vext);
-      lds_dma16((vext ? xv + vrow * x_tok : vb + vrow * RB) + 16 * c, dst + k * 1024);
+      const char* p = at[k] >= seg.ext_start ? xv + (at[k] - seg.ext_start) * x_tok : vb + (long long)(at[k] + delta[k]) * RB;
+      lds_dma16(p + 16 * c, dst + k * 1024);
     }
-    bool kext;
-    const long long krow = locate_row(seg, min(j0 + r, t_kv - 1), kext);
-    const char* kp = kext ? xk + krow * x_tok : kb + krow * RB;
+    const char* kp = at[VCH] >= seg.ext_start ? xk + (at[VCH] - seg.ext_start) * x_tok : kb + (long long)(at[VCH] + delta[VCH]) * RB;
 #pragma unroll
     for (int t = 0; t < KS; ++t) kf[t] = *reinterpret_cast<const bf16x8*>(kp + 32 * t + 16 * h);
   };
@@ -355,6 +368,7 @@ hipError_t launch_one(const void* q, void* o, void* kc, void* vc, int bh, int t_
                       const ExtKV& ext, const CallerIo& io, float c, const GroupEnds& groups, float* partial, hipStream_t st) {
   const int n_qblk = (t_q + 31) / 32;
   constexpr int kWaves = waves_of(kSplit);
+  if (kSplit == 1 && n_qblk != 1) return hipErrorInvalidValue;  // (the dispatch splits wherever a unit has more queries)
   const unsigned grid = kSplit == 1 ? (unsigned)(((long long)bh * n_qblk + kWaves - 1) / kWaves)
                                     : (unsigned)((bh + 7) / 8 * 8) * (unsigned)n_qblk;
   hipLaunchKernelGGL((attend_bf16_small_kernel<D, kSplit, kDensity>), dim3(grid), dim3(64 * kWaves), 0, st, (const __bf16*)q,
