@@ -234,11 +234,18 @@ def amskv_cache_create(layers, heads, head_dim, sides_h, sides_w, batch, dtype, 
     return h.value
 
 
-# The two calls made for every layer and scale go through the extension module (csrc/pycalls.cpp).
+# The two calls made for every layer and scale go through the extension module (csrc/pycalls.cpp); what it does not know
+# how to pass (it says so before it calls anything) goes through ctypes, as in all other calls.
+_UNUSUAL = (TypeError, AttributeError, OverflowError)
+
+
 def amskv_append_scale(cache, layer, s, K=None, V=None, stream=None):
     if _lib is None:
         load_library()
-    status = _append(cache, layer, s, K, V, stream)
+    try:
+        status = _append(cache, layer, s, K, V, stream)
+    except _UNUSUAL:
+        status = _lib.amskv_append_scale(cache, layer, s, _ptr(K), _ptr(V), _stream(stream))
     if status:
         _check(status, "amskv_append_scale")
 
@@ -246,7 +253,10 @@ def amskv_append_scale(cache, layer, s, K=None, V=None, stream=None):
 def amskv_attend(cache, layer, s, Q, O, stream=None):
     if _lib is None:
         load_library()
-    status = _attend(cache, layer, s, Q, O, stream)
+    try:
+        status = _attend(cache, layer, s, Q, O, stream)
+    except _UNUSUAL:
+        status = _lib.amskv_attend(cache, layer, s, _ptr(Q), _ptr(O), _stream(stream))
     if status:
         _check(status, "amskv_attend")
 
