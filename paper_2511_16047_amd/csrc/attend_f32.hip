@@ -3,7 +3,7 @@
 //
 // What bounds it: all query rows of a (b,h) share its keys, so wherever there are enough units the fp32 matrix pipe
 // (v_mfma_f32_32x32x2_f32 and 16x16x4: 157 TFLOP/s nominal, 154 measured on a large product) is the limit, not memory.
-// Measured: 256 (b,h) x 256 queries x 680 keys 264 -> 108 us (43 -> 105 TFLOP/s) against a kernel that kept four lanes
+// Measured: 256 (b,h) x 256 queries x 680 keys 264 -> 113 us (43 -> 101 TFLOP/s) against a kernel that kept four lanes
 // to a query row and fed the vector ALUs from LDS; 16 (b,h), the same lengths: 124 -> 14 us (one image, where that
 // kernel had 64 workgroups with one serial chain of keys each).
 //
@@ -266,24 +266,38 @@ __global__ __launch_bounds__(64 * waves_of(kSplit), 2) void attend_f32_kernel(
     const bool more = b + kSplit < n_blocks;
     rescale();
     if (!kShared && !first) wait_younger(stored_v);  // K of this block; V of the block before may still be on the way
-    // Four partial sums per dot product where registers allow: a chain of D products rounds D times.  Error of the result
-    // against 64 bits, one chain / four: 16 (b,h), 25 queries x 55 keys 2.5e-7 / 1.5e-7, 256 x 680 3.4e-7 / 2.3e-7, head dim
-    // 128, 400 x 677 4.3e-7 / 2.5e-7; the time is the same.
-    constexpr int kChains = QT == 16 ? 4 : 1;
-    typename M::Acc part[kChains];
-#pragma unroll
-    for (int c = 0; c < kChains; ++c)
-#pragma unroll
-      for (int v = 0; v < NV; ++v) part[c][v] = 0.f;
-#pragma unroll
-    for (int i = 0; i < NC; ++i) {
-      const f32x4 kv = *reinterpret_cast<const f32x4*>(lds_k + r * RB + 16 * ((NC * g + i) ^ (r & 15)));
-#pragma unroll
-      for (int e = 0; e < 4; ++e) part[e % kChains] = M::mul(kv[e], qf[i][e], part[e % kChains]);
-    }
+    // A dot product is 16 partial sums (eight in a 32-row unit) that meet in additions: an accumulator that takes all D
+    // products rounds D times, and at the size the sum has by then.  So the error is no larger than that of a kernel whose
+    // four lanes per query summed fours on the vector ALU.  rel against 64 bits, one accumulator (16-row units: four) / these
+    // / the four lanes: 32-row units 32 x 32 keys 2.40e-7 / 1.53e-7 / 1.65e-7, 256 x 424 4.66 / 3.93 / 3.97, 1024 x 1621 7.83 /
+    // 7.39 / 7.44; 16-row units 25 x 55 1.48 / 1.38 / 1.83, head dim 128 2 x 4 0.97 / 0.85 / 0.85, 256 x 680 5.00 / 4.89 / 4.94.
+    // us, before / now: 256 (b,h), 256 x 680 105 / 113 (16 sums in the 32-row unit too: 120), head dim 128 209 / 221; 16 (b,h)
+    // 13.5 / 14.5; 64 (b,h), 1024 x 1621 348 / 387.
+    constexpr int kChain = QT == 32 ? 4 : D / 16 / H;  // matrix instructions of one partial sum (two or four products each)
     typename M::Acc s;
 #pragma unroll
-    for (int v = 0; v < NV; ++v) s[v] = kChains == 4 ? (part[0][v] + part[1][v]) + (part[2 % kChains][v] + part[3 % kChains][v]) : part[0][v];
+    for (int i = 0; i < NC; i += kChain) {
+      f32x4 kv[kChain];
+#pragma unroll
+      for (int u = 0; u < kChain; ++u) kv[u] = *reinterpret_cast<const f32x4*>(lds_k + r * RB + 16 * ((NC * g + i + u) ^ (r & 15)));
+      typename M::Acc four;
+#pragma unroll
+      for (int e0 = 0; e0 < 4; e0 += 2) {
+        typename M::Acc part[2];
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+#pragma unroll
+          for (int v = 0; v < NV; ++v) part[e][v] = 0.f;
+#pragma unroll
+          for (int u = 0; u < kChain; ++u) part[e] = M::mul(kv[u][e0 + e], qf[i + u][e0 + e], part[e]);
+        }
+#pragma unroll
+        for (int v = 0; v < NV; ++v) four[v] = e0 == 0 ? part[0][v] + part[1][v] : four[v] + (part[0][v] + part[1][v]);
+      }
+#pragma unroll
+      for (int v = 0; v < NV; ++v) s[v] = i == 0 ? four[v] : s[v] + four[v];
+      asm volatile("" : "+v"(s));  // added here, not where the scores are used: 16 partial sums would not fit the registers
+    }
     bool stored_k = false;
     if constexpr (!kShared) {
       stored_k = write_back && store_rows(b, false);
@@ -330,7 +344,7 @@ __global__ __launch_bounds__(64 * waves_of(kSplit), 2) void attend_f32_kernel(
       sum = 0.f;
 #pragma unroll
       for (int v = 0; v < NV; ++v) {
-        pf[v] = __builtin_amdgcn_exp2f((s[v] - run_ref) * scale_log2e);  // the key at the reference weighs exactly 1
+        pf[v] = __builtin_amdgcn_exp2f((s[v] - run_ref) * scale_log2e);
         sum += pf[v];
       }
       if (first) moved = false;  // the accumulators are zero

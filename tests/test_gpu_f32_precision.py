@@ -1,0 +1,72 @@
+"""fp32 attention against 64 bits where one kind of rounding is all there is to see.
+
+Scores: two keys whose exact scores agree to the last bit, one a dot product of D - 2 random terms, the other a single exact
+product; every other key weighs nothing.  O is then the logistic function of what the dot product lost in rounding.
+"""
+import numpy as np
+import pytest
+import torch
+
+import paper_2511_16047_amd as amskv
+
+pytestmark = pytest.mark.gpu
+
+
+def _four_lanes(q, k):
+    """q . k in fp32 as four lanes that hold every fourth run of four channels sum it: fours by fused multiply-adds, the
+    fours one after the other, the lanes pairwise.  (64-bit products of fp32 numbers are exact.)"""
+    f = np.float32
+    p = q.astype(np.float64) * k.astype(np.float64)[:, None, :]
+    p = p.reshape(*p.shape[:-1], -1, 4, 4)          # [.., run, lane, channel]
+    lane = np.zeros(p.shape[:-3] + (4,), f)
+    for m in range(p.shape[-3]):
+        four = p[..., m, :, 0].astype(f)
+        for e in range(1, 4):
+            four = (four.astype(np.float64) + p[..., m, :, e]).astype(f)
+        lane = lane + four
+    return (lane[..., 0] + lane[..., 1]) + (lane[..., 2] + lane[..., 3])
+
+
+# 16- and 32-row units, their keys on one wave or dealt to two, four or eight
+@pytest.mark.parametrize("D,bh,tq,prev", [
+    (64, 512, 9, 2), (64, 256, 16, 2), (64, 64, 64, 2), (64, 16, 256, 200),
+    (64, 1024, 25, 2), (64, 128, 256, 60), (64, 128, 64, 60), (64, 256, 32, 200),
+    (128, 512, 9, 2), (128, 256, 16, 2), (128, 64, 64, 2), (128, 16, 256, 200)])
+def test_rounding_of_the_scores(D, bh, tq, prev):
+    scale = 16.0
+    rng = np.random.default_rng(D + bh + tq)
+    q = rng.standard_normal((bh, tq, D)).astype(np.float32)
+    k0 = rng.standard_normal((bh, D)).astype(np.float32)
+    k0[:, :2] = 0
+    exact = np.einsum("btd,bd->bt", q.astype(np.float64), k0.astype(np.float64))
+    q[..., 0] = exact                                # the second key's score, rounded once
+    q[..., 1] = 1
+    k = [np.zeros((bh, n, D), np.float32) for n in (prev, tq)]
+    v = [np.zeros((bh, n, D), np.float32) for n in (prev, tq)]
+    for x in k:
+        x[..., 1] = -1000                            # far below any score here
+    k[0][:, 0], k[0][:, 1] = k0, 0
+    k[0][:, 1, 0] = 1
+    v[0][:, 0] = 1
+    dev = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda()[:, None]
+    args = (1, 1, D, (1, 1), (prev, tq), bh, amskv.AMSKV_DTYPE_F32, [(0, 0, True)], scale)
+    arena = torch.empty(amskv.amskv_cache_required_bytes(*args), dtype=torch.uint8, device="cuda")
+    h = amskv.amskv_cache_create(*args, arena=arena)
+    try:
+        for s in range(2):
+            amskv.amskv_append_scale(h, 0, s, dev(k[s]), dev(v[s]))
+            torch.cuda.synchronize()
+        o = torch.empty(bh, 1, tq, D, device="cuda")
+        amskv.amskv_attend(h, 0, 1, dev(q), o)
+        p = o[:, 0, :, 0].double().cpu().numpy()
+    finally:
+        amskv.amskv_cache_destroy(h)
+    lost = np.log(p / (1 - p)) / scale - (exact - q[..., 0].astype(np.float64))
+    bar = _four_lanes(q * (np.arange(D) > 0), k0) - exact
+    rms = lambda x: float(np.sqrt(np.mean(x * x)))
+    print("rms error of a score: %.3e, four lanes %.3e, ratio %.3f" % (rms(lost), rms(bar), rms(lost) / rms(bar)))
+    # With partial sums of variance n after n terms, a rounding after every addition gives 432 (D = 64) and 1136 (128)
+    # for the four lanes; 16 partial sums 432 and 1120; eight (32-row units) 480, a ratio of 1.054 in rms.  Four partial
+    # sums would be at 672 (1.25) and 2368 (1.44), a single one at 2080 (2.2).  Over the 4000 rows or more of a case the
+    # ratio is known to 2 %.
+    assert rms(lost) <= 1.12 * rms(bar)
