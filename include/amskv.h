@@ -241,7 +241,10 @@ int32_t amskv_append_scale(amskv_cache* cache, int32_t layer, int32_t s,
  * with K~,V~ the concatenation of the resident scales of the layer (scale s included).
  * s must be the scale appended last to this layer (else AMSKV_ERR_ORDER).
  * Q_dev, O_dev: device, [B][H][T_s][D].  bf16: fp32 accumulation and softmax, P rounded
- * to bf16 before the PV product, O rounded to bf16.  Asynchronous on `stream`. */
+ * to bf16 before the PV product, O rounded to bf16.  Asynchronous on `stream`.
+ * Values: fp32 takes infinities as the formula does (an infinite V makes its channel of O infinite, a score of -inf weighs
+ * nothing); bf16 expects finite Q, K and V.  The sums over the keys are kept with weights of up to 2^10 until they are
+ * normalised, so |V| has to stay below the largest float by a factor of 2^10 times the number of keys. */
 int32_t amskv_attend(amskv_cache* cache, int32_t layer, int32_t s,
                      const void* Q_dev, void* O_dev, void* stream);
 

@@ -231,8 +231,9 @@ __global__ __launch_bounds__(64 * waves_of(kSplit), 2) void attend_f32_kernel(
     if (stored) wait_vmcnt<2 * kLoads>();
     else wait_vmcnt<kLoads>();
   };
-  // O^T += V^T P^T of the block whose V is in LDS and whose probabilities are pf
-  auto multiply_v = [&](int v) {
+  // O^T += V^T P^T of the block whose V is in LDS and whose probabilities are pf.  `valid` (the last block only): how many of
+  // its rows are keys; the others hold the last key again and weigh 0, which would make NaN of an infinity there.
+  auto multiply_v = [&](int v, int valid = QT) {
     const char* vp = lds_v + M::row(v, g) * RB + (NDB == 2 ? 8 : 16) * r;
     float a[NDB];
     if constexpr (NDB == 2) {
@@ -246,6 +247,10 @@ __global__ __launch_bounds__(64 * waves_of(kSplit), 2) void attend_f32_kernel(
 #pragma unroll
         for (int e = 0; e < 4; ++e) a[4 * i + e] = x[e];
       }
+    }
+    if (__builtin_expect(valid < QT, 0)) {
+#pragma unroll
+      for (int d = 0; d < NDB; ++d) a[d] = M::row(v, g) < valid ? a[d] : 0.f;
     }
 #pragma unroll
     for (int d = 0; d < NDB; ++d) oacc[d] = M::mul(a[d], pf[v], oacc[d]);
@@ -337,14 +342,15 @@ __global__ __launch_bounds__(64 * waves_of(kSplit), 2) void attend_f32_kernel(
       for (int v = 1; v < NV; ++v) mx = fmaxf(mx, s[v]);
 #pragma unroll
       for (int m = QT; m < 64; m <<= 1) mx = fmaxf(mx, __shfl_xor(mx, m, 64));
-      const bool move = (mx - run_ref) * scale_log2e > kMaxLag;  // mx is finite: the first key of a block is valid
+      const bool move = (mx - run_ref) * scale_log2e > kMaxLag;
       alpha = move ? __builtin_amdgcn_exp2f((run_ref - mx) * scale_log2e) : 1.f;  // 0 on the first block
       run_sum *= alpha;
       run_ref = move ? mx : run_ref;
+      const float ref = run_ref == -INFINITY ? 0.f : run_ref;  // no reference yet: every score so far is -inf and weighs 0
       sum = 0.f;
 #pragma unroll
       for (int v = 0; v < NV; ++v) {
-        pf[v] = __builtin_amdgcn_exp2f((s[v] - run_ref) * scale_log2e);
+        pf[v] = __builtin_amdgcn_exp2f((s[v] - ref) * scale_log2e);  // the key at the reference weighs exactly 1
         sum += pf[v];
       }
       if (first) moved = false;  // the accumulators are zero
@@ -384,7 +390,7 @@ __global__ __launch_bounds__(64 * waves_of(kSplit), 2) void attend_f32_kernel(
     rescale();
     lds_v = lds + ((n_blocks - 1) % kRing) * 2 * kBlk + kBlk;
 #pragma unroll
-    for (int v = 0; v < NV; ++v) multiply_v(v);
+    for (int v = 0; v < NV; ++v) multiply_v(v, t_kv - (n_blocks - 1) * QT);
   } else if (active && slice < n_blocks) {
     load(slice, false);
 #pragma unroll
@@ -396,7 +402,7 @@ __global__ __launch_bounds__(64 * waves_of(kSplit), 2) void attend_f32_kernel(
     rescale();
     wait_vmcnt<0>();
 #pragma unroll
-    for (int v = 0; v < NV; ++v) multiply_v(v);
+    for (int v = 0; v < NV; ++v) multiply_v(v, t_kv - (b - kSplit) * QT);
     if (write_back) store_rows(b - kSplit, true);
   }
 

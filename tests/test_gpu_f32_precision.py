@@ -70,3 +70,43 @@ def test_rounding_of_the_scores(D, bh, tq, prev):
     # sums would be at 672 (1.25) and 2368 (1.44), a single one at 2080 (2.2).  Over the 4000 rows or more of a case the
     # ratio is known to 2 %.
     assert rms(lost) <= 1.12 * rms(bar)
+
+
+# one key past a block of 16 or 32, one short of it, and a few in between; 16- and 32-row units, split and not
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("bh,tq,prev", [(512, 9, 24), (256, 16, 3), (64, 65, 2), (16, 257, 200), (1024, 25, 8), (128, 257, 60), (128, 65, 66),
+                                        (256, 31, 200), (2, 1, 78)])
+@pytest.mark.parametrize("fuse", [False, True], ids=["copied", "fused"])
+def test_infinities(D, bh, tq, prev, fuse):
+    """A value that is infinite makes its channel infinite and nothing else; keys whose score is -inf weigh nothing."""
+    g = torch.Generator().manual_seed(bh + tq)
+    q, k, v = [torch.randn(bh, 1, n, D, generator=g) for n in (tq, prev + tq, prev + tq)]
+    q[..., 0] = q[..., 0].abs() + 0.5
+    k[:, :, 32:80, 0] = -float("inf")                # whole blocks of them, the first of a slice among them
+    k[0, :, :16, 0] = -float("inf")
+    k[:, :, 16], k[:, :, -1] = 0.1, 0.1              # (never all)
+    v[:, :, -1, 3], v[:, :, -1, 5], v[:, :, 16, 60] = float("inf"), -float("inf"), float("inf")
+    layout = amskv.AMSKV_LAYOUT_PLANNED if fuse else amskv.AMSKV_LAYOUT_COMPACT
+    args = (1, 1, D, (1, 1), (prev, tq), bh, amskv.AMSKV_DTYPE_F32, [(0, 0, True)], 0.0, layout)
+    kw = dict(borrow_unretained=fuse, fuse_append=fuse)
+    arena = torch.empty(amskv.amskv_cache_required_bytes(*args, **kw), dtype=torch.uint8, device="cuda").fill_(0xFF)
+    h = amskv.amskv_cache_create(*args, arena=arena, **kw)
+    try:
+        kd, vd = [x.cuda().contiguous() for x in k.split((prev, tq), 2)], [x.cuda().contiguous() for x in v.split((prev, tq), 2)]
+        qd, o = q.cuda(), torch.empty(bh, 1, tq, D, device="cuda")
+        for s in range(2):
+            amskv.amskv_append_scale(h, 0, s, kd[s], vd[s])
+            if s == 0:
+                amskv.amskv_attend(h, 0, 0, torch.zeros_like(kd[0]), torch.empty_like(kd[0]))
+        amskv.amskv_attend(h, 0, 1, qd, o)
+        got = o.cpu()
+    finally:
+        amskv.amskv_cache_destroy(h)
+    p = torch.softmax(q.double() @ k.double().transpose(-1, -2) / D ** 0.5, -1)
+    finite = v.double().clone()
+    finite[torch.isinf(finite)] = 0
+    want = p @ finite
+    want[..., 3], want[..., 5], want[..., 60] = float("inf"), -float("inf"), float("inf")
+    assert torch.equal(torch.isnan(got), torch.isnan(want)) and torch.equal(torch.isinf(got), torch.isinf(want))
+    fin = torch.isfinite(want)
+    assert (got.double()[fin] - want[fin]).abs().max() <= 1e-4 and torch.equal(got[~fin].sign().double(), want[~fin].sign())
