@@ -74,6 +74,9 @@ __global__ __launch_bounds__(64 * waves_of(kSplit), !kDensity ? (D == 64 ? 4 : 2
   constexpr int KS = D / 16;
   constexpr int DB = D / 32;
   constexpr int VCH = 32 * CPR / 64;  // 16-byte chunks of a 32-key V block per lane
+  // The form that also takes steps of more than 32 queries sums the probabilities in fp32 as they are, like the streaming
+  // kernel it stands in for there.  The others sum the bf16 values that the second product multiplies, two at a time.
+  constexpr bool kSumUnrounded = kSplit == 8;
 
   __shared__ __align__(1024) char lds_v[kWaves][2][32 * RB];  // per wave: the block in use and the one in flight
   __shared__ float2 stat[kSplit > 1 ? kWaves : 1][32];        // split: reference and sum of every slice's rows
@@ -218,7 +221,7 @@ __global__ __launch_bounds__(64 * waves_of(kSplit), !kDensity ? (D == 64 ? 4 : 2
     const float mc = new_max * scale_log2e;
     run_max = new_max;
     const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
-    float sum = run_sum * alpha;
+    float sum = run_sum * alpha, sum2 = 0.f;
     bf16x8 pf[2];
 #pragma unroll
     for (int v = 0; v < 16; v += 2) {
@@ -231,11 +234,16 @@ __global__ __launch_bounds__(64 * waves_of(kSplit), !kDensity ? (D == 64 ? 4 : 2
       bf16x2 pk;
       pk[0] = (__bf16)p0;
       pk[1] = (__bf16)p1;
-      sum = __builtin_amdgcn_fdot2_f32_bf16(pk, ones, sum, false);
+      if constexpr (kSumUnrounded) {
+        sum += p0;
+        sum2 += p1;
+      } else {
+        sum = __builtin_amdgcn_fdot2_f32_bf16(pk, ones, sum, false);
+      }
       pf[v >> 3][v & 7] = pk[0];
       pf[v >> 3][(v & 7) + 1] = pk[1];
     }
-    run_sum = sum;
+    run_sum = kSumUnrounded ? sum + sum2 : sum;
     if constexpr (kDensity) {
       in_group *= alpha;
       // keys [from, to) of the block belong to the group

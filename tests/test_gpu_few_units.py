@@ -82,3 +82,36 @@ def test_density_of_the_same_forms(D, B, H):
             assert torch.allclose(m1[:, :n], m2[:, :n], rtol=2e-5, atol=1e-6)
     finally:
         amskv.amskv_cache_destroy(h)
+
+
+@pytest.mark.parametrize("bh", [1, 4, 100, 300])     # eight waves per unit, split, wide and narrow workgroups
+@pytest.mark.parametrize("tq,prev", [(33, 31), (64, 100), (100, 155), (256, 424)])
+@pytest.mark.parametrize("D", [64, 128])
+def test_row_sums_are_of_unrounded_probabilities(D, tq, prev, bh):
+    """More than 32 queries: P is rounded to bf16 for the second product only.  Every 32nd key has the largest score and
+    probability 1 exactly, all others 2^-2.994 = 0.12551, which bf16 takes to 0.12598 (+0.37 %); only the former have a V.
+    A sum over the rounded values would leave O 0.27 % or more too small.  O's own rounding (0.2 % at most, 0.11 % rms, of
+    64 or 128 different values) leaves 0.02 % of their mean."""
+    n = prev + tq
+    top = torch.arange(n) % 32 == 0
+    k, v = torch.zeros(2, bh, 1, n, D)
+    k[..., ~top, 0], k[..., ~top, 1] = -3.0, 0.0059
+    v[..., top, :] = 1 + torch.arange(D) / D
+    q = torch.zeros(bh, 1, tq, D)
+    q[..., :2] = 1
+    q, k, v = [x.bfloat16() for x in (q, k, v)]
+    args = (1, 1, D, (1, 1), (prev, tq), bh, amskv.AMSKV_DTYPE_BF16, [(0, 0, True)], float(torch.tensor(2.0).log()))
+    arena = torch.empty(amskv.amskv_cache_required_bytes(*args), dtype=torch.uint8, device="cuda")
+    h = amskv.amskv_cache_create(*args, arena=arena)
+    try:
+        held = [(a.cuda().contiguous(), b.cuda().contiguous()) for a, b in zip(k.split((prev, tq), 2), v.split((prev, tq), 2))]
+        for s in range(2):
+            amskv.amskv_append_scale(h, 0, s, *held[s])
+        o = torch.empty(bh, 1, tq, D, dtype=torch.bfloat16, device="cuda")
+        amskv.amskv_attend(h, 0, 1, q.cuda(), o)
+        got = o.double().cpu()
+    finally:
+        amskv.amskv_cache_destroy(h)
+    p = torch.softmax(q.double() @ k.double().transpose(-1, -2) * args[8], -1)
+    off = (got / (p @ v.double()) - 1).mean().item()
+    assert abs(off) < 1e-3, off
