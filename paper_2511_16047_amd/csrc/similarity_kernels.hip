@@ -230,8 +230,13 @@ hipError_t launch_similarity(const ScaleRef& cur, const ScaleRef& prev, int batc
                              float* out_dev, hipStream_t st) {
   const int tensors = (cur.v && prev.v) ? 2 : 1;
   const int bh = batch * heads;
-  // a lone workgroup per CU or less: four times the threads, so that a (b,h) takes a quarter of the passes
-  const bool few = (long long)bh * tensors < 512;
+  // Few (b,h) with rows of some length: four times the threads, so that a row takes a quarter of the passes.  The sums of the
+  // keys keep their bits whether the values are asked for or not, so the rule looks at the (b,h) alone.  1024 over 256
+  // threads, time, keys / keys and values, by KB of scale s per (b,h): 12 KB 0.95 / 0.95-1.08 up to 240 (b,h), 1.07 / 1.2 at 448;
+  // 16-25 KB 0.84-0.97 / 0.84-1.1 up to 240, 1.0-1.1 / 1.05-1.24 at 448; 32-64 KB 0.67-0.88 / 0.67-0.99 up to 240, 0.8-0.98 /
+  // 0.93-1.1 at 448; 128 KB and more 0.4-0.65 / 0.4-0.84, 0.7-0.83 / 0.9-1.0; up to 8 KB 1.07-1.3 / 1.07-1.7 everywhere.
+  const long long row = (long long)h_cur * w_cur * head_dim * (dtype == AMSKV_DTYPE_BF16 ? 2 : 4);
+  const bool few = bh < (row >= 32 << 10 ? 512 : row >= 16 << 10 ? 256 : 0);
   auto go = [&](auto f_many, auto f_few) {
     return (few ? f_few : f_many)(cur, prev, bh, heads, h_cur, w_cur, h_prev, w_prev, partial_ws, st);
   };
