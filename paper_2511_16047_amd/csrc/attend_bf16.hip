@@ -901,22 +901,28 @@ hipError_t launch_density_variant(const void* q, void* o, void* kc, void* vc, in
 //   wide     8 waves, 256 rows, 64-key tiles
 //   split    8 waves, 128 rows, 64-key tiles, the two blocks of a tile on different waves
 // The widest one reads K~ and V~ least often, but how long a launch takes is also a matter of how many workgroups the
-// fullest CU gets and of how many waves that puts on its SIMDs: a lone wave overlaps nothing.  The model is what a
-// 32-key block costs a CU that is given 1, 2, ... workgroups (us, measured with 16 to 128 (b,h), 144 to 4096 queries and
-// 229 to 6421 keys; its choice lost 4 % at most against the best of the three).  Head dim 128, 32 (b,h): 256 queries x 421
-// keys 16.8 -> 12.5 us (split), 1024 x 1621 47.7 -> 33.7 (split), 1600 x 2645 86.6 -> 75.5 (wide), 4096 x 6421 423 -> 370
-// (wide); 2304 x 3925 stays narrow (163; wide 206, split 182).  Head dim 64: 16 (b,h), 256 x 680 16.0 -> 12.0 us, 32 (b,h),
-// 1024 x 1621 31.7 -> 22.9.
+// fullest CU gets and of how many waves that puts on its SIMDs: a lone wave overlaps nothing.  The model is what a CU that is
+// given 1, 2, ... workgroups takes: per 32-key block, and beside the blocks (fetching Q, the first tiles, the merge, the
+// stores), us, measured with 1 to 4096 (b,h), 33 to 2500 queries and 33 to 6421 keys.  Narrow is left only for 3 % or more: over 700
+// such shapes the choice then takes 0.880 of narrow's time on average and 1.01 at most, and 1.003 of the best of the three
+// (without what the blocks do not account for: 1.62 of narrow's at 1024 (b,h), 37 x 37 keys, 20.4 for 12.6 us).  Head dim 128, 32
+// (b,h): 256 queries x 421 keys 16.8 -> 12.5 us (split), 1024 x 1621 47.7 -> 33.7 (split), 1600 x 2645 86.6 -> 75.5 (wide), 4096 x
+// 6421 423 -> 370 (wide); 2304 x 3925 stays narrow (163; wide 206, split 182).  Head dim 64: 16 (b,h), 256 x 680 16.0 -> 12.0 us,
+// 32 (b,h), 1024 x 1621 31.7 -> 22.9.
 enum class Shape { kStreams, kNarrow, kWide, kSplit };
 struct Choice {
   Shape shape;
   int split;  // kStreams: waves that share the keys of a 32-row unit
 };
 
-// time of n workgroups of which `resident` fit a CU: whole rounds, then what the fullest CU still gets
-double rounds(long long n, int resident, double full, const double* part) {
+struct Cost {
+  double block, start;
+};
+// time of n workgroups over `blocks` key blocks where `resident` fit a CU: whole rounds, then what the fullest CU still gets
+double rounds(long long n, int resident, int blocks, const Cost& full, const Cost* part) {
   const long long per_round = 256LL * resident, rest = n % per_round;
-  return (double)(n / per_round) * full + (rest ? part[(rest - 1) / 256] : 0.0);
+  const Cost& last = part[rest ? (rest - 1) / 256 : 0];
+  return (double)(n / per_round) * (full.block * blocks + full.start) + (rest ? last.block * blocks + last.start : 0.0);
 }
 
 // The launch writes over cached rows that its queries read (token modes: survivors slide down, or the new scale's rows land
@@ -947,10 +953,10 @@ Choice choose(int head_dim, int bh, int t_q, const SegTable& seg, const ExtKV& e
   if (head_dim == 64 && !moves && units <= 256) return {Shape::kStreams, 8};
   const long long n128 = (long long)bh * ((t_q + 127) / 128), n256 = (long long)bh * ((t_q + 255) / 256);
   if (head_dim == 128) {
-    static const double narrow[] = {0.83, 1.05, 1.35}, wide[] = {0.88}, split[] = {0.53};
-    const double tn = rounds(n128, 3, 1.40, narrow), ts = rounds(n128, 1, 0.53, split);
-    const double tw = t_q > 128 ? rounds(n256, 1, 0.88, wide) : 1e30;
-    return {ts < tn && ts <= tw ? Shape::kSplit : tw < tn ? Shape::kWide : Shape::kNarrow, 1};
+    static const Cost narrow[] = {{0.83, 3}, {1.05, 5}, {1.35, 7}}, three{1.40, 6}, wide{0.88, 6}, split{0.53, 4};
+    const double tn = rounds(n128, 3, blocks, three, narrow), ts = rounds(n128, 1, blocks, split, &split);
+    const double tw = t_q > 128 ? rounds(n256, 1, blocks, wide, &wide) : 1e30;
+    return {fmin(ts, tw) >= 0.97 * tn ? Shape::kNarrow : ts <= tw ? Shape::kSplit : Shape::kWide, 1};
   }
   // Head dim 64 at up to 256 queries lives from reading K~ and V~ once, and a launch that moves cached rows relies on it
   // (attend_owns_unit); beyond 256 workgroups of the split kind a CU has waves enough (512 of them: 100 queries x 255

@@ -115,3 +115,39 @@ def test_row_sums_are_of_unrounded_probabilities(D, tq, prev, bh):
     p = torch.softmax(q.double() @ k.double().transpose(-1, -2) * args[8], -1)
     off = (got / (p @ v.double()) - 1).mean().item()
     assert abs(off) < 1e-3, off
+
+
+def _microseconds(D, bh, tq, prev):
+    """shortest of several replays of ten attention launches"""
+    args = (1, bh // 16, D, (1, 1), (prev, tq), 16, amskv.AMSKV_DTYPE_BF16, [(0, 0, True)])
+    arena = torch.empty(amskv.amskv_cache_required_bytes(*args), dtype=torch.uint8, device="cuda")
+    h = amskv.amskv_cache_create(*args, arena=arena)
+    st, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    try:
+        with torch.cuda.stream(st):
+            for s, t in enumerate((prev, tq)):
+                q, k, v, o = [torch.randn(16, bh // 16, t, D, device="cuda").bfloat16() for _ in range(4)]
+                amskv.amskv_append_scale(h, 0, s, k, v)
+            amskv.amskv_attend(h, 0, 1, q, o)
+            st.synchronize()
+            with torch.cuda.graph(graph, stream=st):
+                for _ in range(10):
+                    amskv.amskv_attend(h, 0, 1, q, o)
+        best = float("inf")
+        for _ in range(12):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record(), graph.replay(), b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b) * 100)
+        return best
+    finally:
+        torch.cuda.synchronize()
+        amskv.amskv_cache_destroy(h)
+
+
+@pytest.mark.parametrize("tq,prev", [(37, 3), (64, 38), (100, 16)])
+def test_fewer_units_do_not_take_longer(tq, prev):
+    """What a shape costs beside its key blocks counts where the blocks are few: 1024 (b,h) take no longer than 1280 (they
+    did by a third where the choice between the shapes went by the blocks alone; a fifth fewer units leave room for noise)."""
+    few, more = _microseconds(128, 1024, tq, prev), _microseconds(128, 1280, tq, prev)
+    assert few <= 1.1 * more, (few, more)
