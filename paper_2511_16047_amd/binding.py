@@ -2,7 +2,8 @@
 
 Device buffers are torch tensors (PyTorch is used for device memory and streams, nothing
 else); every step of the path runs in the library's HIP kernels.  There is no fallback: if
-the shared library is missing, loading raises.
+the shared library is missing, loading raises.  (The extension module that passes the arguments of the two
+most frequent calls is a shorter way into the same library; without it they go through ctypes like the rest.)
 """
 from __future__ import annotations
 
@@ -135,11 +136,19 @@ def load_library() -> C.CDLL:
     lib.amskv_interscale_similarity_enqueue_static.argtypes = [vp, i32, i32, i32, vp, vp]
     lib.amskv_interscale_similarity_enqueue_static.restype = i32
 
-    from . import _pycalls
-    _append, _attend = _pycalls.append_scale, _pycalls.attend
-    _pycalls.bind(C.cast(lib.amskv_append_scale, vp).value, C.cast(lib.amskv_attend, vp).value, _raw_stream_lookup)
+    try:
+        from . import _pycalls
+    except ImportError:   # not built for this interpreter: the same calls, 3 us slower each
+        _append, _attend = _by_ctypes(lib.amskv_append_scale), _by_ctypes(lib.amskv_attend)
+    else:
+        _append, _attend = _pycalls.append_scale, _pycalls.attend
+        _pycalls.bind(C.cast(lib.amskv_append_scale, vp).value, C.cast(lib.amskv_attend, vp).value, _raw_stream_lookup)
     _lib = lib
     return lib
+
+
+def _by_ctypes(call):
+    return lambda cache, layer, s, a, b, stream: call(cache, layer, s, _ptr(a), _ptr(b), _stream(stream))
 
 
 def _raw_stream_lookup():

@@ -12,6 +12,7 @@ from __future__ import annotations
 
 import os
 import re
+import shutil
 import subprocess
 import sys
 import sysconfig
@@ -22,7 +23,8 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libamskv.so")
 OBJ = os.path.join(HERE, "_build")
-PYCALLS = os.path.join(HERE, "_pycalls.so")   # the binding's extension module (no device code)
+# the binding's extension module (no device code), for the interpreter that builds it
+PYCALLS = os.path.join(HERE, "_pycalls" + sysconfig.get_config_var("EXT_SUFFIX"))
 
 SOURCES = ["amskv_api.cpp", "cache_kernels.hip", "similarity_kernels.hip", "attend_f32.hip", "attend_bf16.hip", "attend_bf16_small.hip", "density_kernels.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-x", "hip", "-Wno-inline-asm",
@@ -117,8 +119,11 @@ def build_library(verbose: bool = False) -> str:
                 r.get("lds", 0), r.get("occupancy", 0)))
     check_resources(rows)
     _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs)
-    _run(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-I", sysconfig.get_paths()["include"],
-          os.path.join(CSRC, "pycalls.cpp"), "-o", PYCALLS])
+    include = sysconfig.get_paths()["include"]
+    if shutil.which("g++") and os.path.exists(os.path.join(include, "Python.h")):
+        _run(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-I", include, os.path.join(CSRC, "pycalls.cpp"), "-o", PYCALLS])
+    else:
+        print("no g++ or no Python.h: %s is not built, the binding uses ctypes alone" % os.path.basename(PYCALLS))
     return LIB
 
 
