@@ -153,13 +153,17 @@ def _by_ctypes(call):
 
 def _raw_stream_lookup():
     """torch's current-device and raw current-stream functions (what torch.cuda.current_stream() asks, without the
-    Stream object it builds around the answer), or (None, None) where there is no device."""
+    Stream object it builds around the answer), or (None, None) where there is no device.  The two are not part of torch's
+    public interface: a torch without them is asked the public way."""
     global _lookup
     if _lookup is None:
         import torch
         if torch.cuda.is_available():
             torch.cuda.current_stream()   # initialises the runtime
-            _lookup = torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
+            device, current = (getattr(torch._C, x, None) for x in ("_cuda_getDevice", "_cuda_getCurrentRawStream"))
+            if device is None or current is None:
+                device, current = torch.cuda.current_device, lambda d: torch.cuda.current_stream(d).cuda_stream
+            _lookup = device, current
         else:
             _lookup = None, None
     return _lookup

@@ -60,3 +60,16 @@ def test_without_the_extension_module_the_calls_go_through_ctypes():
 def test_the_extension_module_is_named_for_its_interpreter():
     assert os.path.basename(build.PYCALLS) == "_pycalls" + sysconfig.get_config_var("EXT_SUFFIX")
     assert os.path.exists(build.PYCALLS)
+
+
+def test_a_torch_without_the_raw_stream_functions_is_asked_the_public_way(monkeypatch):
+    import types
+    import torch
+    from paper_2511_16047_amd import binding
+    for name in ("_cuda_getDevice", "_cuda_getCurrentRawStream"):
+        monkeypatch.delattr(torch._C, name, raising=False)
+    monkeypatch.setattr(torch.cuda, "is_available", lambda: True)
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda d=None: types.SimpleNamespace(cuda_stream=0 if d is None else 100 + d))
+    monkeypatch.setattr(binding, "_lookup", None)
+    assert binding._stream(None) == 103
