@@ -480,27 +480,35 @@ hipError_t launch(const void* q, void* o, void* kc, void* vc, int bh, int t_q, i
   return hipGetLastError();
 }
 
-// Which variant: the one with the least modelled time.  The matrix pipe sets the pace, a workgroup puts one wave (two
-// with eight-fold splitting) on every SIMD of its CU, so the launch takes the waves of the fullest SIMD times the blocks
-// of a wave plus what starting and merging costs.  Two workgroups of 32-row units fit a CU, and the dispatcher fills a
-// CU before it goes to the next, so a last round of them counts double.  A 16-row block is a quarter of a 32-row one's
-// work at nine tenths of its rate.  Against the best of the eight variants on 24 shapes (16 to 1024 (b,h), 9 to 2000
-// queries, 14 to 4000 keys) the choice lost 9 % at most, 2 % on average.
+// Which variant: the one with the least modelled time.  A workgroup serves one (b,h), so a launch has as many of them per (b,h) as
+// its query blocks fill, and they go to the CUs in rounds of what fits there (LDS).  A round takes a start, and per key block
+// that a wave walks either the latency of one block's chain or, with more waves on a SIMD, what the matrix pipe needs for
+// all of theirs, whichever is longer (a wave without query rows counts too: it fetches and waits at the barriers).  us, fitted to the
+// eight variants on 1600 shapes (1 to 4096 (b,h), 1 to 2500 queries, 1 to 6000 keys): the choice loses 0.5 % against the best
+// of the eight on average and 21 % at most.  (Counted as though several (b,h) shared a workgroup it lost 4.4 % and 92 %: 4096 (b,h), 64
+// x 65 keys 134 us against 75.)
+struct Cost {
+  double base, start, start_split, latency, work;
+  int resident;  // workgroups of four waves on a CU
+};
 struct Choice {
   int qt, split;
 };
 Choice choose(int head_dim, long long bh, int t_q, int t_kv) {
+  static const Cost rows16{2.2, 0.55, 2.0, 1.5, 0.65, 4}, rows32{1.55, 2.45, 5.5, 2.65, 2.2, 2}, rows16_d128{1.1, 1.1, 4.6, 2.05, 1.5, 2};
   Choice best{16, 1};
   double least = 1e300;
   for (int qt = head_dim == 64 ? 32 : 16; qt >= 16; qt /= 2)
     for (int split = 1; split <= 8; split *= 2) {
-      const long long units = bh * ((t_q + qt - 1) / qt), blocks = (t_kv + qt - 1) / qt;
-      const long long waves = split == 8 ? 8 : 4, groups = (units * split + waves - 1) / waves;
-      double per_simd = (double)((groups + 255) / 256) * (waves / 4);
-      if (qt == 32 && split < 8 && groups > 512) per_simd = 2.0 * (groups / 512) + (groups % 512 == 0 ? 0.0 : groups % 512 <= 256 ? 1.5 : 2.0);
-      const double block = qt == 32 ? 1.0 : 0.28, start = split > 1 ? 0.5 : 0.3;
-      const double alone = per_simd == 1.0 ? 1.3 : 1.0;  // one wave per SIMD overlaps nothing
-      const double t = per_simd * ((double)((blocks + split - 1) / split) * block + start) * alone;
+      const Cost& c = head_dim == 128 ? rows16_d128 : qt == 32 ? rows32 : rows16;
+      const int waves = waves_of(split), units = waves / split, blocks = (t_kv + qt - 1) / qt;
+      const long long groups = bh * (((t_q + qt - 1) / qt + units - 1) / units);
+      const int resident = c.resident * 4 / waves, walk = (blocks + split - 1) / split;
+      auto round = [&](long long n) {
+        return (split == 1 ? c.start : c.start_split) + walk * fmax(c.latency, (double)(n * waves / 4) * c.work);
+      };
+      const long long per_round = 256LL * resident, rest = groups % per_round;
+      const double t = c.base + (double)(groups / per_round) * round(resident) + (rest ? round((rest + 255) / 256) : 0.0);
       if (t < least) {
         least = t;
         best = Choice{qt, split};
