@@ -32,13 +32,17 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-x", "hip", "-W
          "-Rpass-analysis=kernel-resource-usage",
          "-I", os.path.join(ROOT, "include"), "-I", CSRC]
 
-# Waves per SIMD a kernel must reach (the last template argument of the streaming attention kernel is that
-# promise; the coarse-scale and density kernels state theirs in __launch_bounds__).
+# Waves per SIMD a kernel must reach (an argument of the streaming attention kernels is that promise; the others state
+# theirs in __launch_bounds__).  A build in which no kernel matches one of these fails too.
 MIN_OCCUPANCY = [
     (re.compile(r"attend_bf16_kernel<\d+, \d+, \d+, \d+, (\d+)[,>]"), None),     # None: take group 1
     (re.compile(r"attend_density_bf16_kernel<\d+, \d+, \d+, \d+, (\d+)[,>]"), None),
-    (re.compile(r"attend_bf16_small_kernel<64(, \d+, 0)?>"), 4),
-    (re.compile(r"attend_bf16_small_kernel<128(, \d+, 0)?>"), 2),
+    (re.compile(r"attend_bf16_small_kernel<64, \d+, 0>"), 4),
+    (re.compile(r"attend_bf16_small_kernel<128, \d+, 0>"), 2),
+    (re.compile(r"attend_bf16_small_kernel<64, 1, 1>"), 3),
+    (re.compile(r"attend_bf16_small_kernel<128, 1, 1>"), 2),
+    (re.compile(r"attend_bf16_small_kernel<\d+, [48], 1>"), 1),
+    (re.compile(r"attend_f32_kernel<\d+, \d+, \d+>"), 2),
 ]
 
 
@@ -52,6 +56,16 @@ def _run(cmd):
         out = "\n".join(l for l in p.stdout.splitlines() if "packed-fp32-ops' is not a recognized feature" not in l)
         raise RuntimeError("command failed: %s\n%s" % (" ".join(cmd), out))
     return p.stdout
+
+
+def kernel_name(demangled: str) -> str:
+    """What a demangler made of a kernel's symbol, without its namespaces, type and parameters; truth values as 0 and 1."""
+    n = demangled
+    m = re.search(r"N_1\d+([A-Za-z_]\w*?)I((?:L[ib]\d+E)+)E", n)
+    if n.startswith("_Z") and m:     # a type this c++filt does not know (__bf16): template arguments by hand
+        n = "%s<%s>" % (m.group(1), ", ".join(re.findall(r"L[ib](\d+)E", m.group(2))))
+    n = n.replace("(anonymous namespace)::", "").replace("void ", "").replace("amskv::", "").split("(")[0]
+    return re.sub(r"\b(true|false)\b", lambda b: str(int(b.group() == "true")), n)
 
 
 def kernel_resources(compiler_output: str):
@@ -76,16 +90,15 @@ def kernel_resources(compiler_output: str):
         filt = filt if os.path.exists(filt) else "c++filt"
         names = subprocess.run([filt] + [r["name"] for r in rows], stdout=subprocess.PIPE, text=True).stdout.splitlines()
         for r, n in zip(rows, names):
-            m = re.search(r"N_1\d+([A-Za-z_]\w*?)I((?:L[ib]\d+E)+)E", n)
-            if n.startswith("_Z") and m:     # a type this c++filt does not know (__bf16): integer template arguments by hand
-                n = "%s<%s>" % (m.group(1), ", ".join(re.findall(r"L[ib](\d+)E", m.group(2))))
-            n = n.replace("(anonymous namespace)::", "").replace("void ", "").replace("amskv::", "")
-            r["name"] = n.split("(")[0]
+            r["name"] = kernel_name(n)
     return rows
 
 
-def check_resources(rows):
+def check_resources(rows, whole_build=False):
     problems = []
+    if whole_build:
+        problems = ["no kernel is named like %s: its occupancy goes unchecked" % pat.pattern for pat, _ in MIN_OCCUPANCY
+                    if not any(pat.search(r["name"]) for r in rows)]
     for r in rows:
         if r.get("scratch", 0) != 0:
             problems.append("%s spills %d bytes per lane to scratch memory" % (r["name"], r["scratch"]))
@@ -117,7 +130,7 @@ def build_library(verbose: bool = False) -> str:
             print("%-64s vgpr %3d agpr %3d sgpr %3d scratch %3d lds %6d occupancy %d" % (
                 r["name"][-64:], r.get("vgprs", 0), r.get("agprs", 0), r.get("sgprs", 0), r.get("scratch", 0),
                 r.get("lds", 0), r.get("occupancy", 0)))
-    check_resources(rows)
+    check_resources(rows, whole_build=True)
     _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs)
     include = sysconfig.get_paths()["include"]
     if shutil.which("g++") and os.path.exists(os.path.join(include, "Python.h")):

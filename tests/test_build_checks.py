@@ -26,13 +26,25 @@ def test_resource_remarks_are_parsed():
 @pytest.mark.parametrize("row,word", [
     ({"name": "attend_bf16_kernel<64, 1, 8, 64, 4>", "scratch": 0, "occupancy": 3}, "promise 4"),
     ({"name": "attend_bf16_kernel<128, 1, 4, 32, 3>", "scratch": 12, "occupancy": 3}, "scratch"),
-    ({"name": "attend_bf16_small_kernel<64>", "scratch": 0, "occupancy": 3}, "promise 4"),
+    ({"name": build.kernel_name("void amskv::(anonymous namespace)::attend_bf16_small_kernel<64, 4, false>(__bf16 const*, int)"),
+      "scratch": 0, "occupancy": 3}, "promise 4"),
+    ({"name": build.kernel_name("_ZN5amskv12_GLOBAL__N_124attend_bf16_small_kernelILi64ELi4ELb0EEEvPKDF16bPDF16bPcS5_i"),
+      "scratch": 0, "occupancy": 3}, "promise 4"),
+    ({"name": "attend_bf16_small_kernel<64, 1, 1>", "scratch": 0, "occupancy": 2}, "promise 3"),
+    ({"name": "attend_f32_kernel<64, 32, 1>", "scratch": 0, "occupancy": 1}, "promise 2"),
     ({"name": "compact_kernel", "scratch": 4, "occupancy": 8}, "scratch"),
 ])
 def test_a_spill_or_a_missed_occupancy_fails_the_build(row, word):
     with pytest.raises(build.ResourceError) as e:
         build.check_resources([row])
     assert word in str(e.value)
+
+
+def test_a_pattern_that_no_kernel_matches_fails_the_build():
+    rows = build.kernel_resources(REMARKS)
+    with pytest.raises(build.ResourceError) as e:
+        build.check_resources(rows, whole_build=True)
+    assert "attend_f32_kernel" in str(e.value) and "attend_bf16_kernel" not in str(e.value)
 
 
 def test_public_header_is_plain_c():
