@@ -76,7 +76,7 @@ def test_rounding_of_the_scores(D, bh, tq, prev):
 # one key past a block of 16 or 32, one short of it, and a few in between; 16- and 32-row units, split and not
 @pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("bh,tq,prev", [(512, 9, 24), (256, 16, 3), (64, 65, 2), (16, 257, 200), (1024, 25, 8), (128, 257, 60), (128, 65, 66),
-                                        (256, 31, 200), (2, 1, 78), (256, 255, 3), (48, 577, 2), (64, 257, 200), (2, 2051, 4)])
+                                        (256, 31, 200), (2, 1, 78), (256, 255, 3), (48, 577, 2), (64, 257, 200), (64, 256, 200), (2, 2051, 4)])
 @pytest.mark.parametrize("fuse", [False, True], ids=["copied", "fused"])
 def test_infinities(D, bh, tq, prev, fuse):
     """A value that is infinite makes its channel infinite and nothing else; keys whose score is -inf weigh nothing."""
