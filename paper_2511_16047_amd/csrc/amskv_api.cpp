@@ -840,14 +840,14 @@ static int attend_step(amskv_cache* c, int32_t layer, int32_t s, const void* Q_d
   ExtKV ext;
   const SegTable t = seg_table(L, &ext);
   if (t.ext_start < t.total && !ext.k) return AMSKV_ERR_NO_DEVICE_MEMORY;  // borrowed scale appended without data
-  // density: one group per entry of the layer's list; as a by-product of this very launch where the kernel has
-  // that form (bf16), else by the stand-alone kernels first
+  // density: one group per entry of the layer's list; as a by-product of this very launch on a bf16
+  // cache, else by the stand-alone kernels first
   amskv::GroupEnds groups;
   std::memset(&groups, 0, sizeof(groups));
   bool by_product = false;
   if (mass_out_dev) {
     if (L.segs.size() > (size_t)AMSKV_MAX_SCALES) return AMSKV_ERR_INVALID_ARG;
-    by_product = c->dtype == AMSKV_DTYPE_BF16 && amskv::attend_density_fused(c->tokens[s]);
+    by_product = c->dtype == AMSKV_DTYPE_BF16;
     int32_t v = 0;
     for (const Segment& g : L.segs) {
       v += g.len;

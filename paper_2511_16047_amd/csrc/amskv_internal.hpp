@@ -159,13 +159,11 @@ __device__ __forceinline__ int locate_row(const SegTable& seg, int j, bool& ext)
 hipError_t launch_attend_bf16(const void* q, void* o, void* kc, void* vc, int bh,
                               int t_q, int head_dim, int64_t cap_tokens, const SegTable& seg,
                               const ExtKV& ext, const CallerIo& io, float softmax_scale, hipStream_t st);
+// The launch gives every (b,h) to one workgroup (or, on the coarse scales, one wave) where it writes over cached rows: the
+// condition for asking it to move any (ExtKV).  The dispatch sees from the tables whether a launch does; others may share a (b,h).
+bool attend_owns_unit(int head_dim, int t_q);
 // The attention of a step with the attention density of its queries as a by-product: as launch_attend_bf16, plus
 // the per-head masses of the groups in out_dev (heads * AMSKV_MAX_SCALES floats; workspace as for launch_density).
-// attend_density_fused(t_q) tells whether that form exists for a step of t_q queries.
-bool attend_density_fused(int t_q);
-// launch_attend_bf16 gives every (b,h) to one workgroup (or, on the coarse scales, one wave): the condition for
-// asking it to move cached rows (ExtKV)
-bool attend_owns_unit(int head_dim, int t_q);
 hipError_t launch_attend_density_bf16(const void* q, void* o, void* kc, void* vc, int batch, int heads, int t_q, int head_dim,
                                       int64_t cap_tokens, const SegTable& seg, const ExtKV& ext, const CallerIo& io,
                                       float softmax_scale, const GroupEnds& groups, float* partial_ws, float* out_dev,

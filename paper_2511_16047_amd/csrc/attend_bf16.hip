@@ -320,9 +320,10 @@ __device__ __forceinline__ void attend_unit(
   constexpr int kStages = kAhead + (kSplit > 1 ? 3 : 2);
   constexpr int kRing = kStages * kTileBytes;
   constexpr int VM = Loader::kVmPerTile;
-  // Fetch the K fragments of block g+1 into registers while the softmax of block g runs (16 registers at head
-  // dim 64; the head-dim-128 configuration has none to spare, and one-block tiles would need a fifth ring slot).
-  // (the density variant keeps the plain loop: one block at a time, the tile barrier in front of a tile's first block)
+  // Fetch the K fragments of block g+1 into registers while the softmax of block g runs (16 registers at head dim 64, 32 at
+  // 128, where the eight-wave shapes have them: two waves per SIMD).  Not in the narrow shape, whose one-block tiles would need
+  // a fifth ring slot, nor in the unsplit density forms, which keep the plain loop: one block at a time, the tile barrier in
+  // front of a tile's first block.
   constexpr bool kPrefetchK = (D == 64 || kWaves == 8) && kBlocksPerTile == 2 && (!kDensity || kSplit > 1);
   static_assert(kSplit == 1 || (kSplit == 2 && kPrefetchK && NQ == 1), "a split workgroup deals the two blocks of a tile");
 
@@ -972,8 +973,6 @@ Choice choose(int head_dim, int bh, int t_q, const SegTable& seg, const ExtKV& e
 }
 
 }  // namespace
-
-bool attend_density_fused(int) { return true; }
 
 bool attend_owns_unit(int head_dim, int t_q) { return t_q <= (head_dim == 64 ? 256 : 128); }
 
