@@ -984,7 +984,7 @@ hipError_t launch_attend_density_bf16(const void* q, void* o, void* kc, void* vc
   const int bh = batch * heads;
   // The choice is the attention's, so that O comes out with the same bits.  In place of the wide shape (the same bits as
   // the narrow one) goes the narrow one, whose four workgroups per CU hide the group sums better (the case of profiling
-  // density at batch 64: 1.88 against 1.91 ms), unless cached rows move and one workgroup has to own all query rows.
+  // density at batch 64: 1.75 against 1.76 ms), unless cached rows move and one workgroup has to own all query rows.
   const Choice x = choose(head_dim, bh, t_q, seg, ext);
   hipError_t e;
   if (x.shape == Shape::kStreams)

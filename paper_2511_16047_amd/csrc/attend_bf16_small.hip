@@ -125,7 +125,7 @@ __global__ __launch_bounds__(64 * waves_of(kSplit), !kDensity ? (D == 64 ? 4 : 2
     char* dst = lds_v[wave][buffer];
     // The rows this lane fetches -- VCH of V, one of K -- and where they sit: one walk of the segment table for all of them,
     // four entries per step.  (One walk per row and one entry at a time was a chain of up to 25 scalar-load waits in front of
-    // the first load: 16-layer stack on one image 1003 -> 928 us a pass.)
+    // the first load: 16-layer stack on one image 1076 -> 1016 us a pass.)
     int at[VCH + 1], delta[VCH + 1];
 #pragma unroll
     for (int k = 0; k <= VCH; ++k) {

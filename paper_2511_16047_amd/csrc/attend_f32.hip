@@ -20,7 +20,8 @@
 // The four waves of a workgroup that each hold a block of query rows of one (b,h) walk the same keys and fetch each block
 // once, a quarter per wave, into a ring: two blocks on the way, one in use, one whose V is still multiplied, one barrier per
 // block.  Against a stream per wave (four times the traffic from L2 and one block of slack): 256 (b,h), 256 x 680 118 -> 108
-// us, 169 x 424 65 -> 61; 1024 (b,h), 256 x 680 409 -> 383; head dim 128, 32 (b,h), 1024 x 1621 269 -> 241 us (113 TFLOP/s).
+// us, 169 x 424 65 -> 61; 1024 (b,h), 256 x 680 409 -> 383; head dim 128, 32 (b,h), 1024 x 1621 269 -> 241 (all before a dot product
+// was 16 partial sums, which cost 5 to 10 %).
 // Where a unit's keys are split over waves every wave has a stream of its own: K of its next block is requested behind the
 // score products, V behind the second product, each half a block ahead of its use, and nothing in the loop synchronises waves.
 //
@@ -277,7 +278,7 @@ __global__ __launch_bounds__(64 * waves_of(kSplit), 2) void attend_f32_kernel(
     // / the four lanes: 32-row units 32 x 32 keys 2.40e-7 / 1.53e-7 / 1.65e-7, 256 x 424 4.66 / 3.93 / 3.97, 1024 x 1621 7.83 /
     // 7.39 / 7.44; 16-row units 25 x 55 1.48 / 1.38 / 1.83, head dim 128 2 x 4 0.97 / 0.85 / 0.85, 256 x 680 5.00 / 4.89 / 4.94.
     // us, before / now: 256 (b,h), 256 x 680 105 / 113 (16 sums in the 32-row unit too: 120), head dim 128 209 / 221; 16 (b,h)
-    // 13.5 / 14.5; 64 (b,h), 1024 x 1621 348 / 387.
+    // 13.5 / 14.5; 64 (b,h), 1024 x 2645 348 / 387.
     constexpr int kChain = QT == 32 ? 4 : D / 16 / H;  // matrix instructions of one partial sum (two or four products each)
     typename M::Acc s;
 #pragma unroll

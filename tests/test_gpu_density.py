@@ -269,9 +269,9 @@ def _bits(t):
 @pytest.mark.parametrize("D,dtype", [(64, "bf16"), (128, "bf16"), (64, "f32")])
 def test_attend_density_in_one_call(D, dtype, flags):
     """amskv_attend_density: O bit-identical to amskv_attend on a twin cache, the masses against the oracle, the
-    caches bit-identical afterwards.  The schedule covers the by-product form (more than 32 queries; two workgroups
-    per unit from 169 queries on at head dim 64, at 169 and 256 at head dim 128) and the two-call form (coarse
-    scales; the whole fp32 case); groups of 1 and 4 keys end inside the first 32-key block."""
+    caches bit-identical afterwards.  Six (b,h): at bf16 every step is the by-product of a launch whose waves share a unit (at
+    head dim 128 beyond 32 queries, of split workgroups or narrow ones; the other forms: test_gpu_density_forms.py), at fp32 every
+    step is the two calls; groups of 1 and 4 keys end inside the first 32-key block."""
     B, H = 2, 3
     DT = amskv.AMSKV_DTYPE_BF16 if dtype == "bf16" else amskv.AMSKV_DTYPE_F32
     tokens = [x * x for x in VAR]

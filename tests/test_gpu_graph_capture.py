@@ -53,7 +53,7 @@ def test_captured_steps_replay_like_the_eager_calls(flags):
     sums = torch.full((L, H * 4), float("nan"), dtype=torch.float32, device="cuda")
     O_eager = [[torch.empty_like(Q[l][s]) for s in range(S)] for l in range(L)]
     sums_eager = torch.empty_like(sums)
-    # attention density of layer 0 at a coarse step (stand-alone kernels inside the call) and at a later one (by-product)
+    # attention density of layer 0 at a coarse step and at a later one (a by-product of either one's attention launch)
     mass = torch.full((S, H * amskv.AMSKV_MAX_SCALES), float("nan"), dtype=torch.float32, device="cuda")
     mass_eager = torch.empty_like(mass)
 
