@@ -26,7 +26,7 @@ OBJ = os.path.join(HERE, "_build")
 # the binding's extension module (no device code), for the interpreter that builds it
 PYCALLS = os.path.join(HERE, "_pycalls" + sysconfig.get_config_var("EXT_SUFFIX"))
 
-SOURCES = ["amskv_api.cpp", "cache_kernels.hip", "similarity_kernels.hip", "attend_f32.hip", "attend_bf16.hip", "attend_bf16_small.hip", "density_kernels.hip"]
+SOURCES = ["amskv_api.cpp", "cache_kernels.hip", "similarity_kernels.hip", "attend_f32.hip", "attend_f32_parts.hip", "attend_bf16.hip", "attend_bf16_small.hip", "density_kernels.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-x", "hip", "-Wno-inline-asm",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Rpass-analysis=kernel-resource-usage",
@@ -43,6 +43,7 @@ MIN_OCCUPANCY = [
     (re.compile(r"attend_bf16_small_kernel<128, 1, 1>"), 2),
     (re.compile(r"attend_bf16_small_kernel<\d+, [48], 1>"), 1),
     (re.compile(r"attend_f32_kernel<\d+, \d+, \d+>"), 2),
+    (re.compile(r"attend_f32_parts_kernel<\d+, \d+, \d+, (\d+)>"), None),
 ]
 
 

@@ -177,6 +177,11 @@ hipError_t launch_attend_bf16_small(const void* q, void* o, void* kc, void* vc, 
 hipError_t launch_attend_f32(const void* q, void* o, void* kc, void* vc, int bh,
                              int t_q, int head_dim, int64_t cap_tokens, const SegTable& seg,
                              const ExtKV& ext, const CallerIo& io, float softmax_scale, hipStream_t st);
+// the same in bf16 parts (attend_f32_parts.hip); row_waves: waves of 32 query rows per workgroup (8 or 4), split: waves that share
+// their key blocks (1; 2 with 4 row waves); head dim 128 has 4 and 1
+hipError_t launch_attend_f32_parts(int row_waves, int split, const void* q, void* o, void* kc, void* vc, int bh, int t_q, int head_dim,
+                                   int64_t cap_tokens, const SegTable& seg, const ExtKV& ext, const CallerIo& io, float softmax_scale,
+                                   hipStream_t st);
 // k_new == nullptr: compaction only (the new scale is borrowed, nothing to copy); otherwise tokens
 // [src_first, src_first + t_new) of the new scale (rows located by src_map) go to offset dst_new
 hipError_t launch_append(void* kc, void* vc, const void* k_new, const void* v_new, int bh,

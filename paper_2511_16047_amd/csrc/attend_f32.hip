@@ -1,5 +1,6 @@
 // fp32 per-scale attention over the resident segments (Section 3.1: the queries of scale s attend to the cached
-// scales and to their own scale; no mask inside a step), everything in fp32.
+// scales and to their own scale; no mask inside a step), everything in fp32.  Launches with little work; the others go to
+// attend_f32_parts.hip (choose(), below).
 //
 // What bounds it: all query rows of a (b,h) share its keys, so wherever there are enough units the fp32 matrix pipe
 // (v_mfma_f32_32x32x2_f32 and 16x16x4: 157 TFLOP/s nominal, 154 measured on a large product) is the limit, not memory.
@@ -494,10 +495,16 @@ struct Cost {
 };
 struct Choice {
   int qt, split;
+  int parts;  // > 0: the kernel of attend_f32_parts.hip, with that many waves of 32 query rows
+};
+// attend_f32_parts.hip, per key block: `latency` at least, or `per` and `work` for each active wave on a SIMD
+struct PartsCost {
+  int rows, split, resident;
+  double base, start, latency, per, work;
 };
 Choice choose(int head_dim, long long bh, int t_q, int t_kv) {
   static const Cost rows16{2.2, 0.55, 2.0, 1.5, 0.65, 4}, rows32{1.55, 2.45, 5.5, 2.65, 2.2, 2}, rows16_d128{1.1, 1.1, 4.6, 2.05, 1.5, 2};
-  Choice best{16, 1};
+  Choice best{16, 1, 0};
   double least = 1e300;
   for (int qt = head_dim == 64 ? 32 : 16; qt >= 16; qt /= 2)
     for (int split = 1; split <= 8; split *= 2) {
@@ -512,9 +519,27 @@ Choice choose(int head_dim, long long bh, int t_q, int t_kv) {
       const double t = c.base + (double)(groups / per_round) * round(resident) + (rest ? round((rest + 255) / 256) : 0.0);
       if (t < least) {
         least = t;
-        best = Choice{qt, split};
+        best = Choice{qt, split, 0};
       }
     }
+  // The kernel of bf16 parts, where it is modelled to win by 5 %: roughly from 500 blocks of 32 queries on.  Fitted to 1200 shapes (4 to
+  // 4096 (b,h), 10 to 2500 queries, 10 to 6000 keys): the choice then takes 0.86 of the time without it at head dim 64 (0.85 if it were
+  // always right; 1.00 at most), 0.92 at head dim 128 (0.92; 1.11 at most).
+  static const PartsCost parts64[] = {{8, 1, 1, 0.2, 4.4, 1.15, 0.95, 0.85}, {4, 1, 2, 0.15, 5.45, 0.85, 0.95, 0.82}, {4, 2, 1, 0.0, 6.6, 2.4, 0.0, 1.25}};
+  static const PartsCost parts128{4, 1, 1, 0.0, 8.2, 2.9, 0.0, 3.06};
+  least *= 0.95;
+  for (int i = 0; i < (head_dim == 64 ? 3 : 1); ++i) {
+    const PartsCost& c = head_dim == 64 ? parts64[i] : parts128;
+    const int q_blocks = (t_q + 31) / 32, tiles = (q_blocks + c.rows - 1) / c.rows, walk = ((t_kv + 31) / 32 + c.split - 1) / c.split;
+    const double on_simd = (double)q_blocks / tiles * c.split / 4;  // active waves of a workgroup
+    auto round = [&](long long n) { return c.start + walk * fmax(c.latency, c.per + (double)n * on_simd * c.work); };
+    const long long groups = bh * tiles, per_round = 256LL * c.resident, rest = groups % per_round;
+    const double t = c.base + (double)(groups / per_round) * round(c.resident) + (rest ? round((rest + 255) / 256) : 0.0);
+    if (t < least) {
+      least = t;
+      best = Choice{32, c.split, c.rows};
+    }
+  }
   return best;
 }
 
@@ -536,6 +561,7 @@ hipError_t launch_attend_f32(const void* q, void* o, void* kc, void* vc, int bh,
                              const CallerIo& io, float softmax_scale, hipStream_t st) {
   const float c = softmax_scale * 1.4426950408889634f;
   const Choice x = choose(head_dim, bh, t_q, seg.total);
+  if (x.parts) return launch_attend_f32_parts(x.parts, x.split, q, o, kc, vc, bh, t_q, head_dim, cap_tokens, seg, ext, io, softmax_scale, st);
   if (head_dim == 128) return launch_split<128, 16>(x.split, q, o, kc, vc, bh, t_q, cap_tokens, seg, ext, io, c, st);
   return x.qt == 32 ? launch_split<64, 32>(x.split, q, o, kc, vc, bh, t_q, cap_tokens, seg, ext, io, c, st)
                     : launch_split<64, 16>(x.split, q, o, kc, vc, bh, t_q, cap_tokens, seg, ext, io, c, st);

@@ -1,0 +1,72 @@
+"""fp32 attention on the bf16 matrix pipe (three parts per operand): launches large enough that the dispatch takes it, in all of its
+workgroup shapes -- 8 or 4 row groups, 4 of them with the keys dealt to two -- at query counts around 32, 128 and 256, key counts that end
+inside a block and a tile, and segments that end inside one fetch.  Against the oracle; cache contents bit-exact."""
+import math
+
+import pytest
+import torch
+
+import paper_2511_16047_amd as amskv
+from test_gpu_parity import Runner, _qkv
+
+pytestmark = pytest.mark.gpu
+
+FAST = dict(layout=amskv.AMSKV_LAYOUT_PLANNED, borrow=True, fuse=True)
+
+
+@pytest.mark.parametrize("flags", [{}, FAST], ids=["plain", "fast"])
+@pytest.mark.parametrize("tokens", [(31, 97, 129, 64, 256, 255, 33, 160, 1), (127, 65, 225, 257, 63)])
+@pytest.mark.parametrize("B,H", [(13, 8), (19, 8), (19, 16)])
+@pytest.mark.parametrize("D", [64, 128])
+def test_forms(D, B, H, tokens, flags):
+    sides = ((1,) * len(tokens), tokens)
+    r = Runner(*sides, B, H, D, "f32", [(0, 0, True), (1, 1, False)], **flags)
+    try:
+        for layer in range(2):
+            q, k, v = _qkv(*sides, B, H, D, "f32", 31 + layer)
+            _, worst = r.run_layer(layer, q, k, v, check_cache=B == 13, units=[(0, 0), (B // 2, 1), (B - 1, H - 1)])
+            # A score is off by at most 2 D / 16 + 4 roundings of a sum of D products (below 6 sqrt(D) on these inputs), times 1/sqrt(D)
+            # and the slope of the exponential, and that moves O by at most the error times max |v|, which is below 6.
+            assert worst <= (D / 8 + 4) * 2 ** -24 * 6 * 6
+    finally:
+        r.close()
+
+
+def _attend(q, k, v):
+    B, H, t, D = q.shape
+    args = (1, H, D, (1, 1), (k[0].shape[2], t), B, amskv.AMSKV_DTYPE_F32, [(0, 0, True)])
+    arena = torch.empty(amskv.amskv_cache_required_bytes(*args), dtype=torch.uint8, device="cuda")
+    h = amskv.amskv_cache_create(*args, arena=arena)
+    try:
+        for s in range(2):
+            amskv.amskv_append_scale(h, 0, s, k[s], v[s])
+        o = torch.empty_like(q)
+        amskv.amskv_attend(h, 0, 1, q, o)
+        torch.cuda.synchronize()
+    finally:
+        amskv.amskv_cache_destroy(h)
+    return o
+
+
+# magnitudes whose parts leave bf16's range on either side: powers of two on Q, K, V; one value that rounds to infinity in bf16
+@pytest.mark.parametrize("eq,ek,ev,huge", [(0, 0, 0, False), (0, 0, 0, True), (0, 0, -118, False), (-118, 118, 0, False), (118, -118, 0, False),
+                                           (-90, 90, 90, False), (0, 0, -118, True)])
+@pytest.mark.parametrize("D,bh,tq,prev", [(64, 256, 255, 66), (64, 300, 127, 1), (64, 48, 577, 2), (128, 256, 200, 63)])
+def test_magnitudes(D, bh, tq, prev, eq, ek, ev, huge):
+    g = torch.Generator(device="cuda").manual_seed(tq)
+    mk = lambda t, e: torch.randn(bh // 4, 4, t, D, device="cuda", generator=g) * 2.0 ** e
+    q, k, v = mk(tq, eq), [mk(prev, ek), mk(tq, ek)], [mk(prev, ev), mk(tq, ev)]
+    if huge:
+        v[1][:, :, 7, 3] = 3.4e38
+    o = _attend(q, k, v).view(bh, tq, D)
+    n = prev + tq
+    kk, vv = torch.cat(k, 2).view(bh, n, D), torch.cat(v, 2).view(bh, n, D)
+    off, size = torch.zeros(D, dtype=torch.float64, device="cuda"), torch.zeros(D, dtype=torch.float64, device="cuda")
+    for u in range(0, bh, bh // 16):
+        p = torch.softmax(q.view(bh, tq, D)[u].double() @ kk[u].double().t().contiguous() / math.sqrt(D), -1) @ vv[u].double()
+        off += (o[u].double() - p).pow(2).sum(0)
+        size += p.pow(2).sum(0)
+    rel = (off / size).sqrt().max().item()           # the worst channel: the huge value leaves the others as they are
+    # a rounding is 0.43 * 2^-24 of a value in rms; n / 2 of them in a sum of n terms of either sign, about 30 in the scores (a
+    # channel with one huge value has its error there alone); and a channel's figure scatters by a tenth around the whole's
+    assert rel <= 1.25 * 1.25 * 0.43 * 2 ** -24 * math.sqrt(n / 2 + 30)
