@@ -607,6 +607,10 @@ __device__ __forceinline__ void attend_unit(
             sum[n][1] += p1;
             pf[n][u][v & 7] = (__bf16)p0;
             pf[n][u][(v & 7) + 1] = (__bf16)p1;
+            if constexpr (kDensity) {  // kept for the groups that end in this block
+              sacc[n][v] = p0;
+              sacc[n][v + 1] = p1;
+            }
           }
       }
       // ---- was the reference good enough?  (NaN -- a masked key against the initial reference of -inf -- and
@@ -624,6 +628,24 @@ __device__ __forceinline__ void attend_unit(
       // is taken, per query over both lane halves; a query moves its reference to it only if it lies more than
       // kMaxLag powers of two above the old one (every lane that tripped does: its largest probability
       // exceeded kTripSum / 16 = 2^kMaxLag).  Then the block's probabilities are formed again.
+      if constexpr (kDensity) {
+        if (!first) {  // the probabilities stand where the scores were: those are formed again first
+          load_k(off_cur);
+#pragma unroll
+          for (int n = 0; n < NQ; ++n) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) sacc[n][v] = 0.f;
+#pragma unroll
+            for (int t = 0; t < KS; ++t) sacc[n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[t], qf[n][t], sacc[n], 0, 0, 0);
+            if (ragged) {
+#pragma unroll
+              for (int v = 0; v < 16; ++v)
+                if (8 * (v >> 2) + 4 * h + (v & 3) >= (t_kv & 31)) sacc[n][v] = -INFINITY;
+            }
+          }
+          if (kPrefetchK && decltype(has_next)::value) load_k(off_next);
+        }
+      }
 #pragma unroll
       for (int n = 0; n < NQ; ++n) {
         settle_mfma(sacc[n]);
@@ -650,14 +672,18 @@ __device__ __forceinline__ void attend_unit(
           s1 += p1;
           pf[n][v >> 3][v & 7] = (__bf16)p0;
           pf[n][v >> 3][(v & 7) + 1] = (__bf16)p1;
+          if constexpr (kDensity) {
+            sacc[n][v] = p0;
+            sacc[n][v + 1] = p1;
+          }
         }
         sum[n][0] = s0 + s1;
       }
     }
     if constexpr (kDensity) {
       // Groups of keys that end inside (or with) this block: the lane's sum over the group = what it gathered in
-      // the blocks before + its probabilities of this block up to the cut (formed again, exactly, for the keys
-      // below the cut; the whole block's sum when the cut is the block's end) - what earlier cuts of this block took.
+      // the blocks before + its probabilities of this block up to the cut (the whole block's sum when the cut is the
+      // block's end) - what earlier cuts of this block took.
       float taken[NQ];
 #pragma unroll
       for (int n = 0; n < NQ; ++n) taken[n] = 0.f;
@@ -675,8 +701,7 @@ __device__ __forceinline__ void attend_unit(
               const int mine = 8 * i + 8 <= cut ? 4 : cut - 8 * i - 4 * h;  // of this lane's four keys
 #pragma unroll
               for (int e = 0; e < 4; ++e) {
-                const float pv = __builtin_amdgcn_exp2f(fmaf(sacc[n][4 * i + e], scale_log2e, -run_mc[n]));
-                upto += e < mine ? pv : 0.f;
+                upto += e < mine ? sacc[n][4 * i + e] : 0.f;
               }
             }
           }
