@@ -322,9 +322,8 @@ __device__ __forceinline__ void attend_unit(
   constexpr int VM = Loader::kVmPerTile;
   // Fetch the K fragments of block g+1 into registers while the softmax of block g runs (16 registers at head dim 64, 32 at
   // 128, where the eight-wave shapes have them: two waves per SIMD).  Not in the narrow shape, whose one-block tiles would need
-  // a fifth ring slot, nor in the unsplit density forms, which keep the plain loop: one block at a time, the tile barrier in
-  // front of a tile's first block.
-  constexpr bool kPrefetchK = (D == 64 || kWaves == 8) && kBlocksPerTile == 2 && (!kDensity || kSplit > 1);
+  // a fifth ring slot: it keeps the plain loop, one block at a time, the tile barrier in front of a tile's first block.
+  constexpr bool kPrefetchK = (D == 64 || kWaves == 8) && kBlocksPerTile == 2;
   static_assert(kSplit == 1 || (kSplit == 2 && kPrefetchK && NQ == 1), "a split workgroup deals the two blocks of a tile");
 
   __shared__ __align__(1024) char lds_k[kRing];
@@ -1007,20 +1006,25 @@ hipError_t launch_attend_density_bf16(const void* q, void* o, void* kc, void* vc
                                       hipStream_t st) {
   const float c = softmax_scale * 1.4426950408889634f;
   const int bh = batch * heads;
-  // The choice is the attention's, so that O comes out with the same bits.  In place of the wide shape (the same bits as
-  // the narrow one) goes the narrow one, whose four workgroups per CU hide the group sums better (the case of profiling
-  // density at batch 64: 1.75 against 1.76 ms), unless cached rows move and one workgroup has to own all query rows.
+  // The shape is the attention's, so that O comes out with the same bits.  Wide against narrow, which has them too, us: 1920 (b,h),
+  // 256 x 680 147 / 159, 169 x 424 92 / 102; 512 (b,h), 256 x 680 41 / 46; head dim 128, 512 (b,h), 256 x 680 66 / 71, 32 (b,h), 1600 x
+  // 2645 78 / 91, 128 (b,h), 4096 x 6421 1533 / 1658.  (Without K prefetch wide was the slower one.)
   const Choice x = choose(head_dim, bh, t_q, seg, ext);
+  auto go = [&](auto f) { return f(q, o, kc, vc, bh, t_q, cap_tokens, seg, ext, io, c, groups, partial_ws, st); };
   hipError_t e;
-  if (x.shape == Shape::kStreams)
-    e = launch_attend_bf16_small(q, o, kc, vc, bh, t_q, head_dim, cap_tokens, seg, ext, io, softmax_scale, x.split, groups, partial_ws, st);
-  else if (head_dim == 64)
-    e = x.shape == Shape::kSplit ? launch_density_variant<64, 1, 8, 64, 2, 2>(q, o, kc, vc, bh, t_q, cap_tokens, seg, ext, io, c, groups, partial_ws, st)
-        : x.shape == Shape::kWide && moves_rows(seg, ext) ? launch_density_variant<64, 1, 8, 64, 4>(q, o, kc, vc, bh, t_q, cap_tokens, seg, ext, io, c, groups, partial_ws, st)
-                                : launch_density_variant<64, 1, 4, 32, 4>(q, o, kc, vc, bh, t_q, cap_tokens, seg, ext, io, c, groups, partial_ws, st);
-  else
-    e = x.shape == Shape::kSplit ? launch_density_variant<128, 1, 8, 64, 2, 2>(q, o, kc, vc, bh, t_q, cap_tokens, seg, ext, io, c, groups, partial_ws, st)
-                               : launch_density_variant<128, 1, 4, 32, 2>(q, o, kc, vc, bh, t_q, cap_tokens, seg, ext, io, c, groups, partial_ws, st);
+  switch (x.shape) {
+    case Shape::kStreams:
+      e = launch_attend_bf16_small(q, o, kc, vc, bh, t_q, head_dim, cap_tokens, seg, ext, io, softmax_scale, x.split, groups, partial_ws, st);
+      break;
+    case Shape::kSplit:
+      e = head_dim == 64 ? go(launch_density_variant<64, 1, 8, 64, 2, 2>) : go(launch_density_variant<128, 1, 8, 64, 2, 2>);
+      break;
+    case Shape::kWide:
+      e = head_dim == 64 ? go(launch_density_variant<64, 1, 8, 64, 4>) : go(launch_density_variant<128, 1, 8, 64, 2>);
+      break;
+    default:
+      e = head_dim == 64 ? go(launch_density_variant<64, 1, 4, 32, 4>) : go(launch_density_variant<128, 1, 4, 32, 2>);
+  }
   if (e != hipSuccess) return e;
   return launch_density_total(partial_ws, batch, heads, (t_q + 31) / 32, groups.n, out_dev, st);
 }

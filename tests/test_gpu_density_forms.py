@@ -157,3 +157,32 @@ def test_token_budget_decided_on_the_device(D, theta):
     finally:
         amskv.amskv_cache_destroy(one)
         amskv.amskv_cache_destroy(two)
+
+
+# keys that grow from scale to scale, so that the softmax reference moves in blocks that groups end in: wide, narrow, split
+@pytest.mark.parametrize("bh,tq", [(256, 250), (512, 100), (128, 97)])
+@pytest.mark.parametrize("D", [64, 128])
+def test_moving_references(D, bh, tq):
+    H, tokens = 8, (1, 6, 36, 64, 200, tq)
+    B, pols = bh // H, [(0, 0, True)]
+    _, (one, two) = _twins(1, H, D, (1,) * 6, tokens, B, pols, **FAST)
+    g = torch.Generator(device="cuda").manual_seed(bh)
+    mk = lambda t, a: (torch.randn(B, H, t, D, device="cuda", generator=g) * a).bfloat16()
+    k = [mk(t, 1 + 1.2 * s) for s, t in enumerate(tokens)]
+    v, q = [mk(t, 1) for t in tokens], [mk(t, 1) for t in tokens]
+    mass = torch.full((H, amskv.AMSKV_MAX_SCALES), float("nan"), device="cuda")
+    try:
+        for s in range(6):
+            for h in (one, two):
+                amskv.amskv_append_scale(h, 0, s, k[s], v[s])
+            o1, o2 = torch.full_like(q[s], float("nan")), torch.full_like(q[s], float("nan"))
+            lens = amskv.amskv_attend_density(one, 0, s, q[s], o1, mass)
+            amskv.amskv_attend(two, 0, s, q[s], o2)
+            torch.cuda.synchronize()
+            assert torch.equal(o1.view(torch.int16), o2.view(torch.int16)), s
+            p = torch.softmax(q[s].double() @ torch.cat(k[: s + 1], 2).double().transpose(2, 3).contiguous() / D ** 0.5, -1)
+            want = torch.stack([x.sum((2, 3)).mean(0) for x in p.split(lens, 3)], 1)
+            assert torch.allclose(mass[:, : len(lens)].double(), want, rtol=2e-4, atol=1e-5), s
+    finally:
+        amskv.amskv_cache_destroy(one)
+        amskv.amskv_cache_destroy(two)
