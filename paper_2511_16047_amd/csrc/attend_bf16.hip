@@ -336,20 +336,11 @@ __device__ __forceinline__ void attend_unit(
   const int lane = tid & 63;
   const int r = lane & 31;  // column (query) / row (key or head-dim) index inside a block
   const int h = lane >> 5;  // which half of the K-step this lane feeds
-  // XCD-aware unit mapping: consecutive workgroup ids go round-robin to the 8 XCDs, each with its own L2,
-  // so the query tiles of one (b,h) are given ids 8 apart: they land on the same XCD back to back and the
-  // second one finds K~/V~ in that L2 instead of fetching them from HBM again.
-  int bh_i, q_tile;
-  if (n_qtiles == 1) {  // the common case, spelled out: it needs no division
-    bh_i = blockIdx.x;
-    q_tile = 0;
-  } else {
-    const unsigned per_group = 8u * n_qtiles, group = blockIdx.x / per_group, within = blockIdx.x - group * per_group;
-    bh_i = group * 8 + (within & 7);
-    q_tile = within >> 3;
-  }
-  const long long bh = bh_i;
-  if (bh >= n_bh) return;  // whole workgroup leaves together (n_bh not a multiple of 8)
+  Place at{(int)blockIdx.x, 0};
+  if (n_qtiles != 1) at = place(blockIdx.x, n_bh, n_qtiles);  // (one tile is the common case and needs no division)
+  const int q_tile = at.tile;
+  const long long bh = at.bh;
+  if (bh >= n_bh) return;  // whole workgroup leaves together
   const int slice = kSplit == 1 ? 0 : wave / kRowGroups;  // waves w and w + kRowGroups share query rows (and a SIMD)
   const int q_base = q_tile * BM + (wave - slice * kRowGroups) * (32 * NQ);
   const bool wave_active = q_base < t_q;
@@ -906,7 +897,7 @@ hipError_t launch(const void* q, void* o, void* kc, void* vc, int bh, int t_q, i
                   const SegTable& seg, const ExtKV& ext, const CallerIo& io, float c, hipStream_t st) {
   constexpr int BM = kWaves / kSplit * 32 * NQ;
   const int n_qtiles = (t_q + BM - 1) / BM;
-  dim3 grid((unsigned)(((bh + 7) / 8) * 8 * n_qtiles)), block(64 * kWaves);
+  dim3 grid(placed_grid(bh, n_qtiles)), block(64 * kWaves);
   hipLaunchKernelGGL((attend_bf16_kernel<D, NQ, kWaves, kTileKeys, kMinWavesPerSimd, kSplit>), grid, block, 0, st,
                      (const __bf16*)q, (__bf16*)o, (char*)kc, (char*)vc, t_q, (long long)cap_tokens, seg, ext, io, c,
                      bh, n_qtiles);
@@ -919,7 +910,7 @@ hipError_t launch_density_variant(const void* q, void* o, void* kc, void* vc, in
                                   float* partial, hipStream_t st) {
   constexpr int BM = kWaves / kSplit * 32 * NQ;
   const int n_qtiles = (t_q + BM - 1) / BM;
-  dim3 grid((unsigned)(((bh + 7) / 8) * 8 * n_qtiles)), block(64 * kWaves);
+  dim3 grid(placed_grid(bh, n_qtiles)), block(64 * kWaves);
   hipLaunchKernelGGL((attend_density_bf16_kernel<D, NQ, kWaves, kTileKeys, kMinWavesPerSimd, kSplit>), grid, block, 0, st,
                      (const __bf16*)q, (__bf16*)o, (char*)kc, (char*)vc, t_q, (long long)cap_tokens, seg, ext, io, c,
                      bh, n_qtiles, groups, partial);

@@ -85,18 +85,12 @@ __global__ __launch_bounds__(64 * waves_of(kSplit), !kDensity ? (D == 64 ? 4 : 2
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   const int slice = kSplit == 1 ? 0 : wave;
-  int bh_i, q_blk;
-  if (kSplit == 1) {  // launched with one block of queries only
-    bh_i = blockIdx.x * kWaves + wave;
-    q_blk = 0;
-  } else {  // the workgroups of one (b,h) get ids 8 apart: they run on one XCD and share its L2
-    const unsigned per_group = 8u * n_qblk, group = blockIdx.x / per_group, within = blockIdx.x - group * per_group;
-    bh_i = group * 8 + (within & 7);
-    q_blk = within >> 3;
-  }
-  if (bh_i >= n_bh) return;  // without a split nothing below synchronises across waves; with one, the whole workgroup leaves
+  // without a split: launched with one block of queries only
+  const Place place_of = kSplit == 1 ? Place{(int)(blockIdx.x * kWaves) + wave, 0} : place(blockIdx.x, n_bh, n_qblk);
+  const int q_blk = place_of.tile;
+  const long long bh = place_of.bh;
+  if (bh >= n_bh) return;  // without a split nothing below synchronises across waves; with one, the whole workgroup leaves
   const int r = lane & 31, h = lane >> 5;
-  const long long bh = bh_i;
   const int q_base = q_blk * 32;
   const int t_kv = seg.total;
   const int n_blocks = (t_kv + 31) / 32;
@@ -378,7 +372,7 @@ hipError_t launch_one(const void* q, void* o, void* kc, void* vc, int bh, int t_
   constexpr int kWaves = waves_of(kSplit);
   if (kSplit == 1 && n_qblk != 1) return hipErrorInvalidValue;  // (the dispatch splits wherever a unit has more queries)
   const unsigned grid = kSplit == 1 ? (unsigned)(((long long)bh * n_qblk + kWaves - 1) / kWaves)
-                                    : (unsigned)((bh + 7) / 8 * 8) * (unsigned)n_qblk;
+                                    : placed_grid(bh, n_qblk);
   hipLaunchKernelGGL((attend_bf16_small_kernel<D, kSplit, kDensity>), dim3(grid), dim3(64 * kWaves), 0, st, (const __bf16*)q,
                      (__bf16*)o, (char*)kc, (char*)vc, t_q, (long long)cap_tokens, seg, ext, io, c, n_qblk, bh, groups, partial);
   return hipGetLastError();

@@ -112,12 +112,11 @@ __global__ __launch_bounds__(64 * waves_of(kSplit), 2) void attend_f32_kernel(
   const int lane = threadIdx.x & 63;
   const int r = lane % QT, g = lane / QT;
   const int slice = wave % kSplit;
-  // the workgroups of one (b,h) get ids 8 apart: they run on one XCD and share its L2
-  const unsigned per_group = 8u * n_parts, group = blockIdx.x / per_group, within = blockIdx.x - group * per_group;
-  const int bh_i = group * 8 + (within & 7);
-  if (bh_i >= n_bh) return;  // whole workgroup
-  const long long bh = bh_i;
-  const int q_base = ((int)(within >> 3) * kUnits + wave / kSplit) * QT;
+  const Place place_of = place(blockIdx.x, n_bh, n_parts);
+  const int part = place_of.tile;
+  const long long bh = place_of.bh;
+  if (bh >= n_bh) return;  // whole workgroup
+  const int q_base = (part * kUnits + wave / kSplit) * QT;
   const bool active = q_base < t_q;
   const int t_kv = seg.total;
   const int n_blocks = (t_kv + QT - 1) / QT;
@@ -128,7 +127,7 @@ __global__ __launch_bounds__(64 * waves_of(kSplit), 2) void attend_f32_kernel(
   const char* xv = (const char*)ext_kv.v + x_unit;
   // fused append: the blocks of the current scale are dealt to the units of the (b,h), so that none lags behind
   const bool write_back = writes_back(ext_kv, seg.total, seg.ext_start);
-  const int n_qblk = (t_q + QT - 1) / QT, my_qblk = kSplit == 1 ? (int)(within >> 3) : q_base / QT;
+  const int n_qblk = (t_q + QT - 1) / QT, my_qblk = kSplit == 1 ? part : q_base / QT;
   constexpr bool kShared = kSplit == 1;  // the waves of the workgroup walk the same blocks and fetch them together
   char* lds_k = lds + (kShared ? 0 : wave * 2 * kBlk);  // shared: ring slot of the block in use
   char* lds_v = lds_k + kBlk;                           // shared: ring slot of the block whose V is multiplied
@@ -476,7 +475,7 @@ hipError_t launch(const void* q, void* o, void* kc, void* vc, int bh, int t_q, i
                   const ExtKV& ext, const CallerIo& io, float c, hipStream_t st) {
   constexpr int kWaves = waves_of(kSplit), kUnits = kWaves / kSplit;
   const int n_parts = ((t_q + QT - 1) / QT + kUnits - 1) / kUnits;
-  dim3 grid((unsigned)((bh + 7) / 8 * 8) * n_parts), block(64 * kWaves);
+  dim3 grid(placed_grid(bh, n_parts)), block(64 * kWaves);
   hipLaunchKernelGGL((attend_f32_kernel<D, QT, kSplit>), grid, block, 0, st, (const float*)q, (float*)o, (float*)kc, (float*)vc,
                      t_q, (long long)cap_tokens, seg, ext, io, c, bh, n_parts);
   return hipGetLastError();

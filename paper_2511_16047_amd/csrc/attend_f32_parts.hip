@@ -600,9 +600,8 @@ __global__ __launch_bounds__(64 * kRowWaves * kSplit, kOcc) void attend_f32_part
   __shared__ __align__(1024) char lds[lds_bytes(D, kSplit)];
   __shared__ float2 stat[kSplit > 1 ? kRowWaves * kSplit : 1][32];
   __shared__ int wide_flag;
-  // the workgroups of one (b,h) get ids 8 apart: they run on one XCD and share its L2
-  const unsigned per_group = 8u * n_qtiles, group = blockIdx.x / per_group, within = blockIdx.x - group * per_group;
-  const int bh_i = group * 8 + (within & 7), q_tile = within >> 3;
+  const Place at = place(blockIdx.x, n_bh, n_qtiles);
+  const int bh_i = at.bh, q_tile = at.tile;
   if (bh_i >= n_bh) return;  // whole workgroup
   if (threadIdx.x == 0) wide_flag = 0;  // (read and written again behind barriers only)
   const Call call{q, o, (char*)kc, (char*)vc, t_q, cap_tokens, scale_log2e, n_qtiles};
@@ -614,7 +613,7 @@ template <int D, int kRowWaves, int kSplit, int kOcc>
 hipError_t launch(const void* q, void* o, void* kc, void* vc, int bh, int t_q, int64_t cap_tokens, const SegTable& seg,
                   const ExtKV& ext, const CallerIo& io, float c, hipStream_t st) {
   const int n_qtiles = (t_q + 32 * kRowWaves - 1) / (32 * kRowWaves);
-  dim3 grid((unsigned)((bh + 7) / 8 * 8) * n_qtiles), block(64 * kRowWaves * kSplit);
+  dim3 grid(placed_grid(bh, n_qtiles)), block(64 * kRowWaves * kSplit);
   hipLaunchKernelGGL((attend_f32_parts_kernel<D, kRowWaves, kSplit, kOcc>), grid, block, 0, st, (const float*)q, (float*)o, (float*)kc,
                      (float*)vc, t_q, (long long)cap_tokens, seg, ext, io, c, bh, n_qtiles);
   return hipGetLastError();

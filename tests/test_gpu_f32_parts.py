@@ -16,7 +16,7 @@ FAST = dict(layout=amskv.AMSKV_LAYOUT_PLANNED, borrow=True, fuse=True)
 
 @pytest.mark.parametrize("flags", [{}, FAST], ids=["plain", "fast"])
 @pytest.mark.parametrize("tokens", [(31, 97, 129, 64, 256, 255, 33, 160, 1), (127, 65, 225, 257, 63)])
-@pytest.mark.parametrize("B,H", [(13, 8), (19, 8), (19, 16)])
+@pytest.mark.parametrize("B,H", [(13, 8), (19, 8), (19, 16), (37, 7)])   # (the last: no multiple of the eight XCDs)
 @pytest.mark.parametrize("D", [64, 128])
 def test_forms(D, B, H, tokens, flags):
     sides = ((1,) * len(tokens), tokens)
