@@ -140,19 +140,26 @@ __device__ __forceinline__ long long unit_offset(const RowMap& m, long long bh, 
   return (long long)b * m.batch + (long long)((unsigned)bh - b * (unsigned)heads) * m.head;
 }
 
-// Workgroup id -> unit (b,h) and query tile; bh == n_bh: none (the grid is rounded up to whole rows of eight).  Consecutive ids go
-// round-robin to the 8 XCDs, each with its own L2, so every XCD takes an equal share of the list of tiles, unit by unit: the tiles of
-// one (b,h) run on one XCD back to back and find K~ and V~ in its L2 (a share's first and last unit may reach over to a neighbour).
-// Whole units per XCD leave XCDs idle where the (b,h) are few and no multiple of 8; us: bf16, 4 (b,h), 1600 x 4240 47 -> 27, 9 (b,h), 576 x
-// 1152 16.5 -> 10.0; fp32, head dim 128, 1 (b,h), 1600 x 1612 170 -> 44, 9 (b,h), 1600 x 1600 274 -> 144.  Multiples of 8: as before.
+// Workgroup id -> unit (b,h) and query tile; bh == n_bh: none.  Consecutive ids go round-robin to the 8 XCDs, each with its own L2,
+// so the query tiles of one (b,h) are given ids 8 apart: they run on one XCD back to back, the second one finds K~ and V~ in that
+// L2 -- and so does the first what the append in front of the launch left there, whose workgroups are dealt to the XCDs in the same
+// way.  The units that are left when n_bh is no multiple of 8 would keep as many XCDs busy: their tiles are dealt to all 8 in equal
+// shares.  us: bf16, 4 (b,h), 1600 x 4240 47 -> 27, 9 (b,h), 576 x 1152 16.5 -> 10.0; fp32, head dim 128, 1 (b,h), 1600 x 1612 170 -> 44, 9
+// (b,h), 1600 x 1600 274 -> 144.  (Equal shares of all units: as fast, but a layer of fp32 on one image loses what the append left,
+// 113 -> 118 us.)
 struct Place {
   int bh, tile;
 };
 __device__ __forceinline__ Place place(unsigned id, int n_bh, int n_tiles) {
-  const unsigned all = (unsigned)n_bh * n_tiles, share = all >> 3, more = all & 7, xcd = id & 7, at = id >> 3;
-  if (at >= share + (xcd < more ? 1 : 0)) return {n_bh, 0};
-  const unsigned item = xcd * share + min(xcd, more) + at, bh = item / (unsigned)n_tiles;
-  return {(int)bh, (int)(item - bh * n_tiles)};
+  const unsigned per_group = 8u * n_tiles, group = id / per_group, within = id - group * per_group;
+  Place at{(int)(group * 8 + (within & 7)), (int)(within >> 3)};
+  if (__builtin_expect((int)(group * 8 + 8) > n_bh, 0)) {
+    const unsigned all = (n_bh - group * 8) * n_tiles, share = all >> 3, more = all & 7, xcd = within & 7, nth = within >> 3;
+    if (nth >= share + (xcd < more ? 1 : 0)) return {n_bh, 0};
+    const unsigned item = xcd * share + min(xcd, more) + nth, unit = item / (unsigned)n_tiles;
+    at = {(int)(group * 8 + unit), (int)(item - unit * n_tiles)};
+  }
+  return at;
 }
 
 // Virtual row j of K~/V~ -> row index inside the layer's cache region of this (b,h), or, for a
@@ -170,7 +177,7 @@ __device__ __forceinline__ int locate_row(const SegTable& seg, int j, bool& ext)
 #endif
 
 // workgroups of a launch that gives n_tiles of them to each (b,h) (place(), above)
-inline unsigned placed_grid(int n_bh, int n_tiles) { return (unsigned)(((long long)n_bh * n_tiles + 7) / 8 * 8); }
+inline unsigned placed_grid(int n_bh, int n_tiles) { return (unsigned)((long long)(n_bh & ~7) * n_tiles + ((long long)(n_bh & 7) * n_tiles + 7) / 8 * 8); }
 
 // ---- kernel launchers (each validates nothing: the host layer has checked shapes) ----
 // kc/vc are written only when ext.wb_off >= 0 (fused append)
