@@ -496,10 +496,11 @@ struct Choice {
   int qt, split;
   int parts;  // > 0: the kernel of attend_f32_parts.hip, with that many waves of 32 query rows
 };
-// attend_f32_parts.hip, per key block: `latency` at least, or `per` and `work` for each active wave on a SIMD
+// attend_f32_parts.hip, per key block: `latency` at least, or `per` and `work` for each active wave on a SIMD; a round that leaves CUs
+// without a workgroup is faster by up to `idle` (the clock is higher)
 struct PartsCost {
   int rows, split, resident;
-  double base, start, latency, per, work;
+  double base, start, latency, per, work, idle;
 };
 Choice choose(int head_dim, long long bh, int t_q, int t_kv) {
   static const Cost rows16{2.2, 0.55, 2.0, 1.5, 0.65, 4}, rows32{1.55, 2.45, 5.5, 2.65, 2.2, 2}, rows16_d128{1.1, 1.1, 4.6, 2.05, 1.5, 2};
@@ -521,19 +522,26 @@ Choice choose(int head_dim, long long bh, int t_q, int t_kv) {
         best = Choice{qt, split, 0};
       }
     }
-  // The kernel of bf16 parts, where it is modelled to win by 5 %: roughly from 500 blocks of 32 queries on.  Fitted to 1200 shapes (4 to
-  // 4096 (b,h), 10 to 2500 queries, 10 to 6000 keys): the choice then takes 0.86 of the time without it at head dim 64 (0.85 if it were
-  // always right; 1.00 at most), 0.92 at head dim 128 (0.92; 1.11 at most).
-  static const PartsCost parts64[] = {{8, 1, 1, 0.2, 4.4, 1.15, 0.95, 0.85}, {4, 1, 2, 0.15, 5.45, 0.85, 0.95, 0.82}, {4, 2, 1, 0.0, 6.6, 2.4, 0.0, 1.25}};
-  static const PartsCost parts128{4, 1, 1, 0.0, 8.2, 2.9, 0.0, 3.06};
-  least *= 0.95;
+  // (a wave of the other kernel holds 32 queries, and below 128 of them it has never won)
+  if (t_q <= 32 || bh * ((t_q + 31) / 32) < 128) return best;
+  // The kernel of bf16 parts, where it is modelled to be the faster one: roughly from 500 blocks of 32 queries on.  (The 16-row variants
+  // take 1.15 of their model there, which the margin makes up for in part.)  Fitted to 2000 shapes (8 to 4096 (b,h), 33 to 2500 queries,
+  // 33 to 6000 keys): the choice takes 1.007 of the best of all variants on average at head dim 64, 1.001 at 128, and 1.03 and 1.04 of what
+  // it takes without this kernel at most.  256 (b,h), us, without / with: 64 x 155 15.3 / 12.6, 100 x 255 31 / 20, 256 x 680 112 / 65.
+  static const PartsCost parts64[] = {{8, 1, 1, 0.32, 4.15, 0.1, 0.87, 0.88, 0.17}, {4, 1, 2, 0.97, 4.48, 1.58, 1.09, 0.77, 0.33},
+                                      {4, 2, 1, 0.0, 7.12, 0.81, 1.51, 0.57, 0.27}};
+  static const PartsCost parts128{4, 1, 1, 0.0, 9.0, 2.93, 0.0, 3.12, 0.1};
+  least *= head_dim == 64 && best.qt == 16 ? 1.05 : 0.95;
   for (int i = 0; i < (head_dim == 64 ? 3 : 1); ++i) {
     const PartsCost& c = head_dim == 64 ? parts64[i] : parts128;
     const int q_blocks = (t_q + 31) / 32, tiles = (q_blocks + c.rows - 1) / c.rows, walk = ((t_kv + 31) / 32 + c.split - 1) / c.split;
     const double on_simd = (double)q_blocks / tiles * c.split / 4;  // active waves of a workgroup
-    auto round = [&](long long n) { return c.start + walk * fmax(c.latency, c.per + (double)n * on_simd * c.work); };
+    auto round = [&](long long n, double busy) {
+      return (c.start + walk * fmax(c.latency, c.per + (double)n * on_simd * c.work)) * (1 - c.idle * (1 - busy));
+    };
     const long long groups = bh * tiles, per_round = 256LL * c.resident, rest = groups % per_round;
-    const double t = c.base + (double)(groups / per_round) * round(c.resident) + (rest ? round((rest + 255) / 256) : 0.0);
+    const double t = c.base + (double)(groups / per_round) * round(c.resident, 1.0) +
+                     (rest ? round((rest + 255) / 256, fmin(1.0, (double)rest / 256)) : 0.0);
     if (t < least) {
       least = t;
       best = Choice{32, c.split, c.rows};
