@@ -42,7 +42,7 @@ MIN_OCCUPANCY = [
     (re.compile(r"attend_bf16_small_kernel<64, 1, 1>"), 3),
     (re.compile(r"attend_bf16_small_kernel<128, 1, 1>"), 2),
     (re.compile(r"attend_bf16_small_kernel<\d+, [48], 1>"), 1),
-    (re.compile(r"attend_f32_kernel<\d+, \d+, \d+>"), 2),
+    (re.compile(r"attend_f32_kernel<\d+, \d+, \d+[,>]"), 2),
     (re.compile(r"attend_f32_parts_kernel<\d+, \d+, \d+, (\d+)>"), None),
 ]
 

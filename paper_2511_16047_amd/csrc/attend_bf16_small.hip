@@ -86,7 +86,7 @@ __global__ __launch_bounds__(64 * waves_of(kSplit), !kDensity ? (D == 64 ? 4 : 2
   const int lane = threadIdx.x & 63;
   const int slice = kSplit == 1 ? 0 : wave;
   // without a split: launched with one block of queries only
-  const Place place_of = kSplit == 1 ? Place{(int)(blockIdx.x * kWaves) + wave, 0} : place(blockIdx.x, n_bh, n_qblk);
+  const Place place_of = kSplit == 1 ? Place{(int)(blockIdx.x * kWaves) + wave, 0} : place<true>(blockIdx.x, n_bh, n_qblk);
   const int q_blk = place_of.tile;
   const long long bh = place_of.bh;
   if (bh >= n_bh) return;  // without a split nothing below synchronises across waves; with one, the whole workgroup leaves

@@ -89,7 +89,7 @@ __device__ __forceinline__ void wait_vmcnt() {
 // every LDS read of this wave has returned: what follows may overwrite what they read
 __device__ __forceinline__ void wait_lds_reads() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
-template <int D, int QT, int kSplit>
+template <int D, int QT, int kSplit, bool kShares>
 __global__ __launch_bounds__(64 * waves_of(kSplit), 2) void attend_f32_kernel(
     const float* __restrict__ q, float* __restrict__ o, float* __restrict__ kc, float* __restrict__ vc, int t_q,
     long long cap_tokens, SegTable seg, ExtKV ext_kv, CallerIo io, float scale_log2e, int n_bh, int n_parts) {
@@ -112,7 +112,7 @@ __global__ __launch_bounds__(64 * waves_of(kSplit), 2) void attend_f32_kernel(
   const int lane = threadIdx.x & 63;
   const int r = lane % QT, g = lane / QT;
   const int slice = wave % kSplit;
-  const Place place_of = place(blockIdx.x, n_bh, n_parts);
+  const Place place_of = place<kShares>(blockIdx.x, n_bh, n_parts);
   const int part = place_of.tile;
   const long long bh = place_of.bh;
   if (bh >= n_bh) return;  // whole workgroup
@@ -476,7 +476,8 @@ hipError_t launch(const void* q, void* o, void* kc, void* vc, int bh, int t_q, i
   constexpr int kWaves = waves_of(kSplit), kUnits = kWaves / kSplit;
   const int n_parts = ((t_q + QT - 1) / QT + kUnits - 1) / kUnits;
   dim3 grid(placed_grid(bh, n_parts)), block(64 * kWaves);
-  hipLaunchKernelGGL((attend_f32_kernel<D, QT, kSplit>), grid, block, 0, st, (const float*)q, (float*)o, (float*)kc, (float*)vc,
+  const auto kernel = uneven(bh, n_parts) ? attend_f32_kernel<D, QT, kSplit, true> : attend_f32_kernel<D, QT, kSplit, false>;
+  hipLaunchKernelGGL(kernel, grid, block, 0, st, (const float*)q, (float*)o, (float*)kc, (float*)vc,
                      t_q, (long long)cap_tokens, seg, ext, io, c, bh, n_parts);
   return hipGetLastError();
 }

@@ -600,7 +600,7 @@ __global__ __launch_bounds__(64 * kRowWaves * kSplit, kOcc) void attend_f32_part
   __shared__ __align__(1024) char lds[lds_bytes(D, kSplit)];
   __shared__ float2 stat[kSplit > 1 ? kRowWaves * kSplit : 1][32];
   __shared__ int wide_flag;
-  const Place at = place(blockIdx.x, n_bh, n_qtiles);
+  const Place at = place<true>(blockIdx.x, n_bh, n_qtiles);
   const int bh_i = at.bh, q_tile = at.tile;
   if (bh_i >= n_bh) return;  // whole workgroup
   if (threadIdx.x == 0) wide_flag = 0;  // (read and written again behind barriers only)
