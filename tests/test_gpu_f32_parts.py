@@ -70,3 +70,36 @@ def test_magnitudes(D, bh, tq, prev, eq, ek, ev, huge):
     # a rounding is 0.43 * 2^-24 of a value in rms; n / 2 of them in a sum of n terms of either sign, about 30 in the scores (a
     # channel with one huge value has its error there alone); and a channel's figure scatters by a tenth around the whole's
     assert rel <= 1.25 * 1.25 * 0.43 * 2 ** -24 * math.sqrt(n / 2 + 30)
+
+
+@pytest.mark.parametrize("fuse", [False, True], ids=["copied", "fused"])
+@pytest.mark.parametrize("D,B,H,tq,prev", [(64, 32, 8, 255, 66), (64, 38, 8, 127, 1), (64, 6, 8, 577, 2), (128, 32, 8, 200, 63)])
+def test_token_major(D, B, H, tq, prev, fuse):
+    """One projection output [B][T][3][H*D] read in place, O with a padded token stride: the bits of the head-major call."""
+    g = torch.Generator(device="cuda").manual_seed(tq)
+    x = [torch.randn(B, t, 3, H, D, device="cuda", generator=g) for t in (prev, tq)]
+    kw = dict(layout=amskv.AMSKV_LAYOUT_PLANNED, borrow_unretained=True, fuse_append=True) if fuse else {}
+    args = (1, H, D, (1, 1), (prev, tq), B, amskv.AMSKV_DTYPE_F32, [(0, 0, True)])
+    outs = []
+    for packed in (False, True):
+        arena = torch.empty(amskv.amskv_cache_required_bytes(*args, **kw), dtype=torch.uint8, device="cuda").fill_(0xFF)
+        h = amskv.amskv_cache_create(*args, arena=arena, **kw)
+        try:
+            if packed:
+                amskv.amskv_cache_set_io_layout(h, amskv.AMSKV_IO_TOKEN_MAJOR, 3 * H * D, 3 * H * D, H * D + 32)
+                q, k, v = [[y[:, :, i] for y in x] for i in range(3)]
+                o = [torch.zeros(B, y.shape[1], H * D + 32, device="cuda") for y in x]
+            else:
+                q, k, v = [[y[:, :, i].transpose(1, 2).contiguous() for y in x] for i in range(3)]
+                o = [torch.zeros_like(y) for y in q]
+            for s in range(2):
+                amskv.amskv_append_scale(h, 0, s, k[s], v[s])
+                amskv.amskv_attend(h, 0, s, q[s], o[s])
+            e = torch.empty(2, B, H, prev + tq, D, device="cuda")
+            amskv.amskv_cache_export(h, 0, e[0], e[1])
+            torch.cuda.synchronize()
+            o = o[1][:, :, : H * D].reshape(B, tq, H, D).transpose(1, 2) if packed else o[1]
+            outs.append((o.contiguous().view(torch.int32), e.view(torch.int32)))
+        finally:
+            amskv.amskv_cache_destroy(h)
+    assert torch.equal(outs[0][0], outs[1][0]) and torch.equal(outs[0][1], outs[1][1])
