@@ -106,6 +106,34 @@ struct NewRanges {
   int32_t len[2];
 };
 
+// Workgroup id -> unit (b,h) and query tile; bh == n_bh: none.  Consecutive ids go round-robin to the 8 XCDs, each with its own L2,
+// so the query tiles of one (b,h) are given ids 8 apart: they run on one XCD back to back, the second one finds K~ and V~ in that
+// L2 -- and so does the first what the append in front of the launch left there, whose workgroups are dealt to the XCDs in the same
+// way.  The units that are left when n_bh is no multiple of 8 would keep as many XCDs busy: their tiles are dealt to all 8 in equal
+// shares.  us: bf16, 4 (b,h), 1600 x 4240 47 -> 27, 9 (b,h), 576 x 1152 16.5 -> 10.0; fp32, head dim 128, 1 (b,h), 1600 x 1612 170 -> 44, 9
+// (b,h), 1600 x 1600 274 -> 144.  (Equal shares of all units: as fast, but a layer of fp32 on one image loses what the append left,
+// 113 -> 118 us.)  kShares: there may be units left over (uneven(), below); without, a multiple of 8 or one tile each.  The attention
+// kernels proper come in both forms: with the branch they lost up to 0.5 % where nothing is left over.
+struct Place {
+  int bh, tile;
+};
+template <bool kShares>
+__host__ __device__ inline Place place(unsigned id, int n_bh, int n_tiles) {
+  const unsigned per_group = 8u * n_tiles, group = id / per_group, within = id - group * per_group;
+  Place at{(int)(group * 8 + (within & 7)), (int)(within >> 3)};
+  if (kShares && __builtin_expect((int)(group * 8 + 8) > n_bh, 0)) {
+    const unsigned all = (n_bh - group * 8) * n_tiles, share = all >> 3, more = all & 7, xcd = within & 7, nth = within >> 3;
+    if (nth >= share + (xcd < more ? 1 : 0)) return {n_bh, 0};
+    const unsigned item = xcd * share + (xcd < more ? xcd : more) + nth, unit = item / (unsigned)n_tiles;
+    at = {(int)(group * 8 + unit), (int)(item - unit * n_tiles)};
+  }
+  return at;
+}
+
+inline bool uneven(int n_bh, int n_tiles) { return (n_bh & 7) != 0 && n_tiles > 1; }
+// workgroups of a launch that gives n_tiles of them to each (b,h) (place(), above)
+inline unsigned placed_grid(int n_bh, int n_tiles) { return (unsigned)((long long)(n_bh & ~7) * n_tiles + ((long long)(n_bh & 7) * n_tiles + 7) / 8 * 8); }
+
 #if defined(__HIPCC__)
 // x plus its value in the lane that the cross-lane pattern pairs with this one, on the vector ALU
 template <int kPattern>
@@ -140,30 +168,6 @@ __device__ __forceinline__ long long unit_offset(const RowMap& m, long long bh, 
   return (long long)b * m.batch + (long long)((unsigned)bh - b * (unsigned)heads) * m.head;
 }
 
-// Workgroup id -> unit (b,h) and query tile; bh == n_bh: none.  Consecutive ids go round-robin to the 8 XCDs, each with its own L2,
-// so the query tiles of one (b,h) are given ids 8 apart: they run on one XCD back to back, the second one finds K~ and V~ in that
-// L2 -- and so does the first what the append in front of the launch left there, whose workgroups are dealt to the XCDs in the same
-// way.  The units that are left when n_bh is no multiple of 8 would keep as many XCDs busy: their tiles are dealt to all 8 in equal
-// shares.  us: bf16, 4 (b,h), 1600 x 4240 47 -> 27, 9 (b,h), 576 x 1152 16.5 -> 10.0; fp32, head dim 128, 1 (b,h), 1600 x 1612 170 -> 44, 9
-// (b,h), 1600 x 1600 274 -> 144.  (Equal shares of all units: as fast, but a layer of fp32 on one image loses what the append left,
-// 113 -> 118 us.)  kShares: there may be units left over (uneven(), below); without, a multiple of 8 or one tile each.  The attention
-// kernels proper come in both forms: with the branch they lost up to 0.5 % where nothing is left over.
-struct Place {
-  int bh, tile;
-};
-template <bool kShares>
-__device__ __forceinline__ Place place(unsigned id, int n_bh, int n_tiles) {
-  const unsigned per_group = 8u * n_tiles, group = id / per_group, within = id - group * per_group;
-  Place at{(int)(group * 8 + (within & 7)), (int)(within >> 3)};
-  if (kShares && __builtin_expect((int)(group * 8 + 8) > n_bh, 0)) {
-    const unsigned all = (n_bh - group * 8) * n_tiles, share = all >> 3, more = all & 7, xcd = within & 7, nth = within >> 3;
-    if (nth >= share + (xcd < more ? 1 : 0)) return {n_bh, 0};
-    const unsigned item = xcd * share + min(xcd, more) + nth, unit = item / (unsigned)n_tiles;
-    at = {(int)(group * 8 + unit), (int)(item - unit * n_tiles)};
-  }
-  return at;
-}
-
 // Virtual row j of K~/V~ -> row index inside the layer's cache region of this (b,h), or, for a
 // row of the borrowed segment, row index inside the external tensor of this (b,h) (ext = true).
 __device__ __forceinline__ int locate_row(const SegTable& seg, int j, bool& ext) {
@@ -177,10 +181,6 @@ __device__ __forceinline__ int locate_row(const SegTable& seg, int j, bool& ext)
   return j + delta;
 }
 #endif
-
-inline bool uneven(int n_bh, int n_tiles) { return (n_bh & 7) != 0 && n_tiles > 1; }
-// workgroups of a launch that gives n_tiles of them to each (b,h) (place(), above)
-inline unsigned placed_grid(int n_bh, int n_tiles) { return (unsigned)((long long)(n_bh & ~7) * n_tiles + ((long long)(n_bh & 7) * n_tiles + 7) / 8 * 8); }
 
 // ---- kernel launchers (each validates nothing: the host layer has checked shapes) ----
 // kc/vc are written only when ext.wb_off >= 0 (fused append)
