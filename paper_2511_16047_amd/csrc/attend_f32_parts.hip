@@ -24,10 +24,11 @@
 // filled, in use, and the one whose V is still multiplied -- one barrier per tile; swizzle and transposing reads as in the streaming
 // bf16 kernel, on each part.
 //
-// A magnitude that rounds to infinity in bf16 (3.39e38 and up) or an infinity has no such parts.  Every wave keeps the largest
-// magnitudes it has split; a workgroup that met one does its work again on the fp32 matrix instructions, which give such inputs
-// what the formula has.  So does one whose share of K, V or Q lies below 2^-100 as a whole: its lower parts would be subnormal, which the
-// matrix cores take for 0.  (256 (b,h), 256 x 680, such a value in each: 214 us instead of 70.)
+// A magnitude that rounds to infinity in bf16 (3.39e38 and up) or an infinity has no such parts, and the products of parts of Q and K
+// may overflow from 2^59 on.  Every wave keeps the largest magnitudes it has split; a workgroup that met such a one does its work
+// again on the fp32 matrix instructions, which give these inputs what the formula has.  So does one whose share of K, V or Q lies
+// below 2^-100 as a whole: its lower parts would be subnormal, which the matrix cores take for 0.  (256 (b,h), 256 x 680, such a
+// value in each: 214 us instead of 70.)
 #include "amskv_internal.hpp"
 
 namespace amskv {
@@ -47,6 +48,9 @@ constexpr float kTiny = 0x1p-100f;
 constexpr float kMaxLag = 6.0f;
 constexpr float kTripSum = 1024.0f;
 constexpr float kHuge = 0x1.ffp127f;  // from here on a magnitude rounds to infinity in bf16
+// Q and K below this: no product of parts, and no sum of them, comes near fp32's largest number.  (Products of parts have either sign:
+// where they overflow, a score that is -inf, or finite, would be the sum of two opposite infinities.)
+constexpr float kLarge = 0x1p59f;
 
 #define AMSKV_LDS __attribute__((address_space(3)))
 __device__ __forceinline__ bf16x4 lds_read_tr16(const char* p) {
@@ -177,8 +181,7 @@ struct Stage {
   }
 };
 
-// The same sums on the fp32 matrix instructions, for a workgroup that has met a number that is infinite or rounds to infinity
-// in bf16.  Waves of the first slice compute, all of them fetch.
+// The same sums on the fp32 matrix instructions, for a workgroup that has met a number that its parts cannot stand for.  Waves of the first slice compute, all of them fetch.
 template <int D, int kRowWaves, int kSplit>
 __device__ __forceinline__ void attend_unit_wide(const Call& call, const SegTable& seg, const ExtKV& ext_kv, const CallerIo& io,
                                                  long long bh, int q_tile, char* lds) {
@@ -530,7 +533,7 @@ __device__ __forceinline__ bool attend_unit(const Call& call, const SegTable& se
   }
 #pragma unroll
   for (int i = 0; i < 3; ++i)
-    if (top[i] >= kHuge || __builtin_amdgcn_ballot_w64(top[i] >= kTiny) == 0 && top[i] != 0.f) *wide_flag = 1;
+    if (top[i] >= (i == 1 ? kHuge : kLarge) || __builtin_amdgcn_ballot_w64(top[i] >= kTiny) == 0 && top[i] != 0.f) *wide_flag = 1;
   __syncthreads();
   if (*wide_flag != 0) return true;
 #pragma unroll

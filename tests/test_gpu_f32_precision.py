@@ -111,3 +111,30 @@ def test_infinities(D, bh, tq, prev, fuse):
     assert torch.equal(torch.isnan(got), torch.isnan(want)) and torch.equal(torch.isinf(got), torch.isinf(want))
     fin = torch.isfinite(want)
     assert (got.double()[fin] - want[fin]).abs().max() <= 1e-4 and torch.equal(got[~fin].sign().double(), want[~fin].sign())
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("bh,tq,prev", [(16, 257, 200), (256, 65, 66), (256, 255, 3), (48, 577, 2), (64, 257, 200), (256, 200, 63)])
+def test_finite_products_that_overflow(D, bh, tq, prev):
+    """A score that is -inf because the product of a finite Q and K is too large weighs nothing, in launches of any size."""
+    g = torch.Generator().manual_seed(bh + tq)
+    q, k, v = [torch.randn(bh, 1, n, D, generator=g) for n in (tq, prev + tq, prev + tq)]
+    q[..., 5], k[..., 5] = -1.3 * 2.0 ** 68, 0.0
+    k[:, :, ::7, 5] = 1.7 * 2.0 ** 68                # 2^137, with parts whose products have either sign
+    dead = torch.zeros(prev + tq, dtype=torch.bool)
+    dead[::7] = True
+    args = (1, 1, D, (1, 1), (prev, tq), bh, amskv.AMSKV_DTYPE_F32, [(0, 0, True)])
+    arena = torch.empty(amskv.amskv_cache_required_bytes(*args), dtype=torch.uint8, device="cuda")
+    h = amskv.amskv_cache_create(*args, arena=arena)
+    try:
+        kd, vd = [x.cuda().contiguous() for x in k.split((prev, tq), 2)], [x.cuda().contiguous() for x in v.split((prev, tq), 2)]
+        qd, o = q.cuda(), torch.empty(bh, 1, tq, D, device="cuda")
+        for s in range(2):
+            amskv.amskv_append_scale(h, 0, s, kd[s], vd[s])
+        amskv.amskv_attend(h, 0, 1, qd, o)
+        got = o.cpu()
+    finally:
+        amskv.amskv_cache_destroy(h)
+    q[..., 5] = 0
+    p = torch.softmax((q.double() @ k.double().transpose(-1, -2) / D ** 0.5).masked_fill(dead, -float("inf")), -1)
+    assert (got.double() - p @ v.double()).abs().max() <= 1e-5  # (fp32 attention's is below 3e-6 on ordinary inputs)
