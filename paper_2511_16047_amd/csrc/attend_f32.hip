@@ -503,7 +503,7 @@ struct PartsCost {
   int rows, split, resident;
   double base, start, latency, per, work, idle;
 };
-Choice choose(int head_dim, long long bh, int t_q, int t_kv) {
+Choice choose(int head_dim, long long bh, int t_q, int t_kv, float softmax_scale) {
   static const Cost rows16{2.2, 0.55, 2.0, 1.5, 0.65, 4}, rows32{1.55, 2.45, 5.5, 2.65, 2.2, 2}, rows16_d128{1.1, 1.1, 4.6, 2.05, 1.5, 2};
   Choice best{16, 1, 0};
   double least = 1e300;
@@ -525,6 +525,8 @@ Choice choose(int head_dim, long long bh, int t_q, int t_kv) {
     }
   // (a wave of the other kernel holds 32 queries, and below 128 of them it has never won)
   if (t_q <= 32 || bh * ((t_q + 31) / 32) < 128) return best;
+  // (its scores are exact to 2^-67 beside their roundings, which a scale this large would bring up)
+  if (softmax_scale > 0x1p30f) return best;
   // The kernel of bf16 parts, where it is modelled to be the faster one: roughly from 500 blocks of 32 queries on.  (The 16-row variants
   // take 1.15 of their model there, which the margin makes up for in part.)  Fitted to 2000 shapes (8 to 4096 (b,h), 33 to 2500 queries,
   // 33 to 6000 keys): the choice takes 1.007 of the best of all variants on average at head dim 64, 1.001 at 128, and 1.03 and 1.04 of what
@@ -568,7 +570,7 @@ hipError_t launch_attend_f32(const void* q, void* o, void* kc, void* vc, int bh,
                              int head_dim, int64_t cap_tokens, const SegTable& seg, const ExtKV& ext,
                              const CallerIo& io, float softmax_scale, hipStream_t st) {
   const float c = softmax_scale * 1.4426950408889634f;
-  const Choice x = choose(head_dim, bh, t_q, seg.total);
+  const Choice x = choose(head_dim, bh, t_q, seg.total, softmax_scale);
   if (x.parts) return launch_attend_f32_parts(x.parts, x.split, q, o, kc, vc, bh, t_q, head_dim, cap_tokens, seg, ext, io, softmax_scale, st);
   if (head_dim == 128) return launch_split<128, 16>(x.split, q, o, kc, vc, bh, t_q, cap_tokens, seg, ext, io, c, st);
   return x.qt == 32 ? launch_split<64, 32>(x.split, q, o, kc, vc, bh, t_q, cap_tokens, seg, ext, io, c, st)

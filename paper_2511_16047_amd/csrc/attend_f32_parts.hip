@@ -24,11 +24,14 @@
 // filled, in use, and the one whose V is still multiplied -- one barrier per tile; swizzle and transposing reads as in the streaming
 // bf16 kernel, on each part.
 //
-// A magnitude that rounds to infinity in bf16 (3.39e38 and up) or an infinity has no such parts, and the products of parts of Q and K
-// may overflow from 2^59 on.  Every wave keeps the largest magnitudes it has split; a workgroup that met such a one does its work
-// again on the fp32 matrix instructions, which give these inputs what the formula has.  So does one whose share of K, V or Q lies
-// below 2^-100 as a whole: its lower parts would be subnormal, which the matrix cores take for 0.  (256 (b,h), 256 x 680, such a
-// value in each: 214 us instead of 70.)
+// Large numbers.  From 3.39e38 on a magnitude rounds to infinity in bf16, and from 2^59 on the products of parts of Q and K may
+// overflow.  Every wave keeps the largest magnitude it has split; a workgroup that met one of 2^59 or more does its work again on
+// the fp32 matrix instructions, which give such inputs, infinities too, what the formula has.  (256 (b,h), 256 x 680, such a value in
+// each: 214 us instead of 70.)
+// Small numbers.  bf16 has subnormals, in steps of 2^-133, and the matrix cores take them: a part is off by 2^-134 at most.  V is split
+// scaled, which keeps all bits of every normal number.  In a score that error, times 2^59 and 2 D, is below 2^-66, nothing next to
+// the rounding of the exponential unless the softmax scale is huge (the dispatch leaves those to attend_f32.hip).  In a probability it is
+// less than what every kernel here loses where the exponential falls below 2^-126, which the instruction gives as 0.
 #include "amskv_internal.hpp"
 
 namespace amskv {
@@ -42,15 +45,15 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
-// The largest magnitude of a wave's share below this: parts that count are subnormal in bf16, which the matrix cores take for 0.
-constexpr float kTiny = 0x1p-100f;
 // lag of the softmax reference and the sum that has it looked at again: as in attend_f32.hip
 constexpr float kMaxLag = 6.0f;
 constexpr float kTripSum = 1024.0f;
-constexpr float kHuge = 0x1.ffp127f;  // from here on a magnitude rounds to infinity in bf16
-// Q and K below this: no product of parts, and no sum of them, comes near fp32's largest number.  (Products of parts have either sign:
-// where they overflow, a score that is -inf, or finite, would be the sum of two opposite infinities.)
+// Magnitudes that go in as parts lie below this: no product of parts, and no sum of them, comes near fp32's largest number.  (Products of
+// parts have either sign: where they overflow, a score that is -inf, or finite, would be the sum of two opposite infinities.)
 constexpr float kLarge = 0x1p59f;
+// V is split times this, and O divided by it: bf16 goes down in steps of 2^-133, so that the parts of a number below 2^-109 would be short
+// of bits.  (2^59 * 2^32 * the sum of the weights stays finite.)
+constexpr float kScaleV = 0x1p32f;
 
 #define AMSKV_LDS __attribute__((address_space(3)))
 __device__ __forceinline__ bf16x4 lds_read_tr16(const char* p) {
@@ -299,18 +302,19 @@ __device__ __forceinline__ bool attend_unit(const Call& call, const SegTable& se
   Stage<D, kRowWaves * kSplit, kSplit> stage(call, seg, ext_kv, io, bh, q_tile);
   f32x4 (&raw)[2][kLoads] = stage.raw;
   const int row0 = stage.row0, pos = stage.pos;
-  // ---- registers -> parts in LDS
-  float top[3] = {0.f, 0.f, 0.f};  // largest magnitudes in K, V and Q that this wave has split
+  // ---- registers -> parts in LDS (V's scaled)
+  float top = 0.f;  // largest magnitude that this lane has split
   constexpr int kPieces = 2 * kLoads;
   auto put_piece = [&](int slot, int piece) __attribute__((always_inline)) {
     const int k = piece >> 1, t = piece & 1;
     const int row = (k * kWaves + wave) * kRowsPerLoad + row0;
     char* dst = lds + slot + (kSplit == 1 ? 0 : (row >> 5) * kBlk) + (row & 31) * PB + 16 * ((pos >> 1) ^ swizzle<D>(row & 31)) + 8 * (pos & 1);
-    const f32x4 x = raw[t][k];
+    f32x4 x = raw[t][k];
     u32x2 p[3];
     unsigned a, b, c, d, e, f;
-    top[t] = max3_abs(top[t], x[0], x[1]);
-    top[t] = max3_abs(top[t], x[2], x[3]);
+    top = max3_abs(top, x[0], x[1]);
+    top = max3_abs(top, x[2], x[3]);
+    if (t == 1) x *= kScaleV;
     split2(x[0], x[1], a, b, c);
     split2(x[2], x[3], d, e, f);
     p[0] = u32x2{a, d}, p[1] = u32x2{b, e}, p[2] = u32x2{c, f};
@@ -339,7 +343,7 @@ __device__ __forceinline__ bool attend_unit(const Call& call, const SegTable& se
       for (int i = 0; i < 4; ++i) {
         unsigned a, b, c;
         const float x0 = x[t][i >> 1][2 * (i & 1)], x1 = x[t][i >> 1][2 * (i & 1) + 1];
-        top[2] = max3_abs(top[2], x0, x1);
+        top = max3_abs(top, x0, x1);
         split2(x0, x1, a, b, c);
         w[0][i] = a, w[1][i] = b, w[2][i] = c;
       }
@@ -531,9 +535,7 @@ __device__ __forceinline__ bool attend_unit(const Call& call, const SegTable& se
     multiply_v(lds + before + slice * kBlk, 0);
     multiply_v(lds + before + slice * kBlk, 1);
   }
-#pragma unroll
-  for (int i = 0; i < 3; ++i)
-    if (top[i] >= (i == 1 ? kHuge : kLarge) || __builtin_amdgcn_ballot_w64(top[i] >= kTiny) == 0 && top[i] != 0.f) *wide_flag = 1;
+  if (top >= kLarge) *wide_flag = 1;
   __syncthreads();
   if (*wide_flag != 0) return true;
 #pragma unroll
@@ -544,7 +546,7 @@ __device__ __forceinline__ bool attend_unit(const Call& call, const SegTable& se
   char* o_row = (char*)call.o + unit_offset(io.o, bh, io.heads) + (long long)(q_base + r) * io.o.tok;
   const bool row_ok = q_base + r < t_q;
   if constexpr (kSplit == 1) {
-    const float inv = 1.0f / total;
+    const float inv = 1.0f / total * (1.0f / kScaleV);
     if (!active) return false;
 #pragma unroll
     for (int d = 0; d < DB; ++d)
@@ -578,7 +580,7 @@ __device__ __forceinline__ bool attend_unit(const Call& call, const SegTable& se
       weight[p] = __builtin_amdgcn_exp2f((y.x - best) * scale_log2e);
       sum = fmaf(weight[p], y.y, sum);
     }
-    const float inv = 1.0f / sum;
+    const float inv = 1.0f / sum * (1.0f / kScaleV);
 #pragma unroll
     for (int c0 = 0; c0 < kChunks; c0 += kSplit) {
       const int c = c0 + slice;

@@ -32,14 +32,14 @@ def test_forms(D, B, H, tokens, flags):
         r.close()
 
 
-def _attend(q, k, v):
+def _attend(q, k, v, scale=0.0):
     B, H, t, D = q.shape
-    args = (1, H, D, (1, 1), (k[0].shape[2], t), B, amskv.AMSKV_DTYPE_F32, [(0, 0, True)])
+    args = (1, H, D, (1, 1), (k[0].shape[2], t), B, amskv.AMSKV_DTYPE_F32, [(0, 0, True)], scale)
     arena = torch.empty(amskv.amskv_cache_required_bytes(*args), dtype=torch.uint8, device="cuda")
     h = amskv.amskv_cache_create(*args, arena=arena)
     try:
         for s in range(2):
-            amskv.amskv_append_scale(h, 0, s, k[s], v[s])
+            amskv.amskv_append_scale(h, 0, s, k[s].contiguous(), v[s].contiguous())
         o = torch.empty_like(q)
         amskv.amskv_attend(h, 0, 1, q, o)
         torch.cuda.synchronize()
@@ -70,6 +70,42 @@ def test_magnitudes(D, bh, tq, prev, eq, ek, ev, huge):
     # a rounding is 0.43 * 2^-24 of a value in rms; n / 2 of them in a sum of n terms of either sign, about 30 in the scores (a
     # channel with one huge value has its error there alone); and a channel's figure scatters by a tenth around the whole's
     assert rel <= 1.25 * 1.25 * 0.43 * 2 ** -24 * math.sqrt(n / 2 + 30)
+
+
+# Tiny values beside ordinary ones.  v: one channel; keys: every V of the keys that weigh anything; qk: a channel of K that Q makes up
+# for; scale: tiny K beside a channel that Q leaves out, and a softmax scale that makes up for it
+@pytest.mark.parametrize("what", ["v", "v_least", "keys", "qk", "kq", "scale"])
+@pytest.mark.parametrize("D,bh,tq,prev", [(64, 256, 255, 66), (64, 300, 127, 1), (64, 48, 577, 2), (128, 256, 200, 63)])
+def test_tiny_beside_ordinary(D, bh, tq, prev, what):
+    g = torch.Generator(device="cuda").manual_seed(tq)
+    n, scale = prev + tq, 1 / math.sqrt(D)
+    q, k, v = [torch.randn(bh // 4, 4, t, D, device="cuda", generator=g) for t in (tq, n, n)]
+    if what[0] == "v":
+        v[..., 9] = (v[..., 9] + v[..., 9].sign()) * 2.0 ** (-116 if what == "v" else -125)  # (normal numbers)
+    elif what == "keys":
+        q[..., 3], k[..., 3] = 64.0, 0.0
+        k[:, :, ::2, 3] = -64.0                      # scores of about -360 and less
+        v[:, :, 1::2] *= 2.0 ** -116
+    elif what == "scale":
+        k, scale = k * 2.0 ** -116, scale * 2.0 ** 116
+        q[..., 9], k[..., 9] = 0.0, 1.0
+    else:
+        e = 118 if what == "qk" else -118
+        q[..., 9] *= 2.0 ** e
+        k[..., 9] *= 2.0 ** -e
+    o = _attend(q, list(k.split((prev, tq), 2)), list(v.split((prev, tq), 2)), scale).view(bh, tq, D)
+    kk, vv = k.view(bh, n, D), v.view(bh, n, D)
+    off, size = torch.zeros(D, dtype=torch.float64, device="cuda"), torch.zeros(D, dtype=torch.float64, device="cuda")
+    for u in range(0, bh, bh // 16):
+        p = torch.softmax(q.view(bh, tq, D)[u].double() @ kk[u].double().t().contiguous() * scale, -1) @ vv[u].double()
+        off += (o[u].double() - p).pow(2).sum(0)
+        size += p.pow(2).sum(0)
+    rel = (off / size).sqrt()
+    # as above; results of 2^-125 may come out in steps of 2^-149, half a step off: n of them average sqrt(n) less
+    allowed = torch.full_like(rel, 1.25 * 1.25 * 0.43 * 2 ** -24 * math.sqrt(n / 2 + 30))
+    if what == "v_least":
+        allowed[9] += 2.0 ** -149 / (size[9] / (16 * tq)).sqrt()
+    assert (rel <= allowed).all(), "%.2f of the bound" % (rel / allowed).max()
 
 
 @pytest.mark.parametrize("fuse", [False, True], ids=["copied", "fused"])
