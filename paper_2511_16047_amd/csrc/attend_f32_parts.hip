@@ -24,10 +24,11 @@
 // filled, in use, and the one whose V is still multiplied -- one barrier per tile; swizzle and transposing reads as in the streaming
 // bf16 kernel, on each part.
 //
-// Large numbers.  From 3.39e38 on a magnitude rounds to infinity in bf16, and from 2^59 on the products of parts of Q and K may
-// overflow.  Every wave keeps the largest magnitude it has split; a workgroup that met one of 2^59 or more does its work again on
-// the fp32 matrix instructions, which give such inputs, infinities too, what the formula has.  (256 (b,h), 256 x 680, such a value in
-// each: 214 us instead of 70.)
+// Large numbers.  From 2^59 on the products of parts of Q and K may overflow; every lane keeps the largest magnitude of theirs that it
+// has split.  In V a magnitude from 2^95 on, scaled (below), or a sum that overflows, leaves sums in O that are not finite, in all rows.  A
+// workgroup that sees either does its work again on the fp32 matrix instructions, which give such inputs, infinities too, what the
+// formula has.  (256 (b,h), 256 x 680, such a value in each: 214 us instead of 70.  A maximum over V too, beside the scaling: 0.4 %
+// of a stack of layers on 16 images.)
 // Small numbers.  bf16 has subnormals, in steps of 2^-133, and the matrix cores take them: a part is off by 2^-134 at most.  V is split
 // scaled, which keeps all bits of every normal number.  In a score that error, times 2^59 and 2 D, is below 2^-66, nothing next to
 // the rounding of the exponential unless the softmax scale is huge (the dispatch leaves those to attend_f32.hip).  In a probability it is
@@ -48,11 +49,11 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 // lag of the softmax reference and the sum that has it looked at again: as in attend_f32.hip
 constexpr float kMaxLag = 6.0f;
 constexpr float kTripSum = 1024.0f;
-// Magnitudes that go in as parts lie below this: no product of parts, and no sum of them, comes near fp32's largest number.  (Products of
-// parts have either sign: where they overflow, a score that is -inf, or finite, would be the sum of two opposite infinities.)
+// Q and K lie below this: no product of parts, and no sum of them, comes near fp32's largest number.  (Products of parts have either
+// sign: where they overflow, a score that is -inf, or finite, would be the sum of two opposite infinities.)
 constexpr float kLarge = 0x1p59f;
 // V is split times this, and O divided by it: bf16 goes down in steps of 2^-133, so that the parts of a number below 2^-109 would be short
-// of bits.  (2^59 * 2^32 * the sum of the weights stays finite.)
+// of bits.
 constexpr float kScaleV = 0x1p32f;
 
 #define AMSKV_LDS __attribute__((address_space(3)))
@@ -303,7 +304,7 @@ __device__ __forceinline__ bool attend_unit(const Call& call, const SegTable& se
   f32x4 (&raw)[2][kLoads] = stage.raw;
   const int row0 = stage.row0, pos = stage.pos;
   // ---- registers -> parts in LDS (V's scaled)
-  float top = 0.f;  // largest magnitude that this lane has split
+  float top = 0.f;  // largest magnitude in K and Q that this lane has split
   constexpr int kPieces = 2 * kLoads;
   auto put_piece = [&](int slot, int piece) __attribute__((always_inline)) {
     const int k = piece >> 1, t = piece & 1;
@@ -312,9 +313,12 @@ __device__ __forceinline__ bool attend_unit(const Call& call, const SegTable& se
     f32x4 x = raw[t][k];
     u32x2 p[3];
     unsigned a, b, c, d, e, f;
-    top = max3_abs(top, x[0], x[1]);
-    top = max3_abs(top, x[2], x[3]);
-    if (t == 1) x *= kScaleV;
+    if (t == 0) {
+      top = max3_abs(top, x[0], x[1]);
+      top = max3_abs(top, x[2], x[3]);
+    } else {
+      x *= kScaleV;
+    }
     split2(x[0], x[1], a, b, c);
     split2(x[2], x[3], d, e, f);
     p[0] = u32x2{a, d}, p[1] = u32x2{b, e}, p[2] = u32x2{c, f};
@@ -535,13 +539,17 @@ __device__ __forceinline__ bool attend_unit(const Call& call, const SegTable& se
     multiply_v(lds + before + slice * kBlk, 0);
     multiply_v(lds + before + slice * kBlk, 1);
   }
-  if (top >= kLarge) *wide_flag = 1;
-  __syncthreads();
-  if (*wide_flag != 0) return true;
+  float finite = 0.f;  // stays 0 if they all are
 #pragma unroll
   for (int d = 0; d < DB; ++d)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) oacc[d][v] += osml[d][v];
+    for (int v = 0; v < 16; ++v) {
+      oacc[d][v] += osml[d][v];
+      finite = fmaf(oacc[d][v], 0.f, finite);
+    }
+  if (top >= kLarge || !(finite == 0.f)) *wide_flag = 1;
+  __syncthreads();
+  if (*wide_flag != 0) return true;
   float total = run_sum + __shfl_xor(run_sum, 32, 64);
   char* o_row = (char*)call.o + unit_offset(io.o, bh, io.heads) + (long long)(q_base + r) * io.o.tok;
   const bool row_ok = q_base + r < t_q;
