@@ -296,7 +296,7 @@ struct Flag {
 // The work of one workgroup.  kDensity: also leave, per 32-row query block, the softmax mass that lands on each
 // group of keys (Section 4.1's attention density as a by-product of the step's own attention; `groups` holds the
 // first virtual row past each group, `partial` one float per (b, h, query block, group)).
-template <int D, int NQ, int kWaves, int kTileKeys, bool kDensity, bool kShares, int kSplit>
+template <int D, int NQ, int kWaves, int kTileKeys, bool kDensity, int kSplit>
 __device__ __forceinline__ void attend_unit(
     const __bf16* __restrict__ q, __bf16* __restrict__ o, char* __restrict__ kc, char* __restrict__ vc,
     int t_q, long long cap_tokens, const SegTable& seg, const ExtKV& ext_kv, const CallerIo& io, float scale_log2e, int n_bh,
@@ -341,7 +341,7 @@ __device__ __forceinline__ void attend_unit(
     bh_i = blockIdx.x;
     q_tile = 0;
   } else {
-    const Place at = place<kShares>(blockIdx.x, n_bh, n_qtiles);
+    const Place at = place<true>(blockIdx.x, n_bh, n_qtiles);
     bh_i = at.bh;
     q_tile = at.tile;
   }
@@ -880,11 +880,11 @@ __device__ __forceinline__ void attend_unit(
   }
 }
 
-template <int D, int NQ, int kWaves, int kTileKeys, int kMinWavesPerSimd, int kSplit, bool kShares>
+template <int D, int NQ, int kWaves, int kTileKeys, int kMinWavesPerSimd, int kSplit>
 __global__ __launch_bounds__(64 * kWaves, kMinWavesPerSimd) void attend_bf16_kernel(
     const __bf16* __restrict__ q, __bf16* __restrict__ o, char* __restrict__ kc, char* __restrict__ vc,
     int t_q, long long cap_tokens, SegTable seg, ExtKV ext_kv, CallerIo io, float scale_log2e, int n_bh, int n_qtiles) {
-  attend_unit<D, NQ, kWaves, kTileKeys, false, kShares, kSplit>(q, o, kc, vc, t_q, cap_tokens, seg, chosen(ext_kv), io, scale_log2e, n_bh,
+  attend_unit<D, NQ, kWaves, kTileKeys, false, kSplit>(q, o, kc, vc, t_q, cap_tokens, seg, chosen(ext_kv), io, scale_log2e, n_bh,
                                                n_qtiles, GroupEnds{}, nullptr);
 }
 
@@ -894,7 +894,7 @@ __global__ __launch_bounds__(64 * kWaves, kMinWavesPerSimd) void attend_density_
     const __bf16* __restrict__ q, __bf16* __restrict__ o, char* __restrict__ kc, char* __restrict__ vc,
     int t_q, long long cap_tokens, SegTable seg, ExtKV ext_kv, CallerIo io, float scale_log2e, int n_bh, int n_qtiles,
     GroupEnds groups, float* __restrict__ partial) {
-  attend_unit<D, NQ, kWaves, kTileKeys, true, true, kSplit>(q, o, kc, vc, t_q, cap_tokens, seg, chosen(ext_kv), io, scale_log2e, n_bh,
+  attend_unit<D, NQ, kWaves, kTileKeys, true, kSplit>(q, o, kc, vc, t_q, cap_tokens, seg, chosen(ext_kv), io, scale_log2e, n_bh,
                                               n_qtiles, groups, partial);
 }
 
@@ -904,9 +904,8 @@ hipError_t launch(const void* q, void* o, void* kc, void* vc, int bh, int t_q, i
   constexpr int BM = kWaves / kSplit * 32 * NQ;
   const int n_qtiles = (t_q + BM - 1) / BM;
   dim3 grid(placed_grid(bh, n_qtiles)), block(64 * kWaves);
-  const auto kernel = uneven(bh, n_qtiles) ? attend_bf16_kernel<D, NQ, kWaves, kTileKeys, kMinWavesPerSimd, kSplit, true>
-                                           : attend_bf16_kernel<D, NQ, kWaves, kTileKeys, kMinWavesPerSimd, kSplit, false>;
-  hipLaunchKernelGGL(kernel, grid, block, 0, st, (const __bf16*)q, (__bf16*)o, (char*)kc, (char*)vc, t_q, (long long)cap_tokens, seg, ext, io, c,
+  hipLaunchKernelGGL((attend_bf16_kernel<D, NQ, kWaves, kTileKeys, kMinWavesPerSimd, kSplit>), grid, block, 0, st,
+                     (const __bf16*)q, (__bf16*)o, (char*)kc, (char*)vc, t_q, (long long)cap_tokens, seg, ext, io, c,
                      bh, n_qtiles);
   return hipGetLastError();
 }
