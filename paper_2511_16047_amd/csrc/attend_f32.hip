@@ -1,12 +1,12 @@
 // fp32 per-scale attention over the resident segments (Section 3.1: the queries of scale s attend to the cached
 // scales and to their own scale; no mask inside a step), everything in fp32.  Launches with little work; the others go to
-// attend_f32_parts.hip (choose(), below).
+// attend_f32_parts.hip (attend_f32_choice.hpp).
 //
 // What bounds it: all query rows of a (b,h) share its keys, so wherever there are enough units the fp32 matrix pipe
-// (v_mfma_f32_32x32x2_f32 and 16x16x4: 157 TFLOP/s nominal, 154 measured on a large product) is the limit, not memory.
-// Measured: 256 (b,h) x 256 queries x 680 keys 264 -> 113 us (43 -> 101 TFLOP/s) against a kernel that kept four lanes
-// to a query row and fed the vector ALUs from LDS; 16 (b,h), the same lengths: 124 -> 14 us (one image, where that
-// kernel had 64 workgroups with one serial chain of keys each).
+// (v_mfma_f32_32x32x2_f32 and 16x16x4: 157 TFLOP/s nominal, 154 measured on a large product) is the limit, not memory;
+// with few units it is the chain of a wave's key blocks.  Measured: 16 (b,h), 256 queries x 680 keys 124 -> 14 us (one image)
+// against a kernel that kept four lanes to a query row and fed the vector ALUs from LDS and had one serial chain of keys for
+// each of 64 workgroups.
 //
 // Formulation.  A unit is (b, h, block of QT query rows), QT = 32 or 16.  Per block of QT keys the transposed scores
 // S^T = K Q^T (M = keys, N = queries) leave every lane with the scores of ONE query, so the softmax is in-lane plus an
@@ -20,15 +20,16 @@
 // from memory into registers touches 16 lines per quarter wave and instruction and kept the matrix pipe at half its rate.)
 // The four waves of a workgroup that each hold a block of query rows of one (b,h) walk the same keys and fetch each block
 // once, a quarter per wave, into a ring: two blocks on the way, one in use, one whose V is still multiplied, one barrier per
-// block.  Against a stream per wave (four times the traffic from L2 and one block of slack): 256 (b,h), 256 x 680 118 -> 108
-// us, 169 x 424 65 -> 61; 1024 (b,h), 256 x 680 409 -> 383; head dim 128, 32 (b,h), 1024 x 1621 269 -> 241 (all before a dot product
-// was 16 partial sums, which cost 5 to 10 %).
+// block.  Against a stream per wave (four times the traffic from L2 and one block of slack), on launches that attend_f32_parts.hip has
+// taken over since and before a dot product was 16 partial sums (which cost 5 to 10 %): 256 (b,h), 256 x 680 118 -> 108 us, 169 x 424
+// 65 -> 61; head dim 128, 32 (b,h), 1024 x 1621 269 -> 241.
 // Where a unit's keys are split over waves every wave has a stream of its own: K of its next block is requested behind the
 // score products, V behind the second product, each half a block ahead of its use, and nothing in the loop synchronises waves.
 //
 // Few units (one image): the keys of a unit are dealt block by block to kSplit waves of a workgroup, each with its
 // own online softmax; their partial results meet in LDS once, behind one barrier.
 #include "amskv_internal.hpp"
+#include "attend_f32_choice.hpp"
 
 namespace amskv {
 namespace {
@@ -59,7 +60,6 @@ struct Mfma<16> {
   __device__ static __forceinline__ Acc mul(float a, float b, Acc c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
 };
 
-constexpr int waves_of(int split) { return split == 8 ? 8 : 4; }
 // split: per wave a block of K and one of V (the K piece later holds the wave's partial result), and its softmax statistics;
 // else a ring of blocks for the workgroup
 constexpr int kRing = 4;
@@ -475,89 +475,22 @@ hipError_t launch(const void* q, void* o, void* kc, void* vc, int bh, int t_q, i
                   const ExtKV& ext, const CallerIo& io, float c, hipStream_t st) {
   constexpr int kWaves = waves_of(kSplit), kUnits = kWaves / kSplit;
   const int n_parts = ((t_q + QT - 1) / QT + kUnits - 1) / kUnits;
+  constexpr bool kOnePart = D == 64 && kSplit == 1;  // at most 64 queries (choose_f32())
+  if (kOnePart && n_parts > 1) return hipErrorInvalidValue;
   dim3 grid(placed_grid(bh, n_parts)), block(64 * kWaves);
-  const auto kernel = uneven(bh, n_parts) ? attend_f32_kernel<D, QT, kSplit, true> : attend_f32_kernel<D, QT, kSplit, false>;
+  const auto kernel = !kOnePart && uneven(bh, n_parts) ? attend_f32_kernel<D, QT, kSplit, !kOnePart> : attend_f32_kernel<D, QT, kSplit, false>;
   hipLaunchKernelGGL(kernel, grid, block, 0, st, (const float*)q, (float*)o, (float*)kc, (float*)vc,
                      t_q, (long long)cap_tokens, seg, ext, io, c, bh, n_parts);
   return hipGetLastError();
-}
-
-// Which variant: the one with the least modelled time.  A workgroup serves one (b,h), so a launch has as many of them per (b,h) as
-// its query blocks fill, and they go to the CUs in rounds of what fits there (LDS).  A round takes a start, and per key block
-// that a wave walks either the latency of one block's chain or, with more waves on a SIMD, what the matrix pipe needs for
-// all of theirs, whichever is longer (a wave without query rows counts too: it fetches and waits at the barriers).  us, fitted to the
-// eight variants on 1600 shapes (1 to 4096 (b,h), 1 to 2500 queries, 1 to 6000 keys): the choice loses 0.5 % against the best
-// of the eight on average and 21 % at most.  (Counted as though several (b,h) shared a workgroup it lost 4.4 % and 92 %: 4096 (b,h), 64
-// x 65 keys 134 us against 75.)
-struct Cost {
-  double base, start, start_split, latency, work;
-  int resident;  // workgroups of four waves on a CU
-};
-struct Choice {
-  int qt, split;
-  int parts;  // > 0: the kernel of attend_f32_parts.hip, with that many waves of 32 query rows
-};
-// attend_f32_parts.hip, per key block: `latency` at least, or `per` and `work` for each active wave on a SIMD; a round that leaves CUs
-// without a workgroup is faster by up to `idle` (the clock is higher)
-struct PartsCost {
-  int rows, split, resident;
-  double base, start, latency, per, work, idle;
-};
-Choice choose(int head_dim, long long bh, int t_q, int t_kv, float softmax_scale) {
-  static const Cost rows16{2.2, 0.55, 2.0, 1.5, 0.65, 4}, rows32{1.55, 2.45, 5.5, 2.65, 2.2, 2}, rows16_d128{1.1, 1.1, 4.6, 2.05, 1.5, 2};
-  Choice best{16, 1, 0};
-  double least = 1e300;
-  for (int qt = head_dim == 64 ? 32 : 16; qt >= 16; qt /= 2)
-    for (int split = 1; split <= 8; split *= 2) {
-      const Cost& c = head_dim == 128 ? rows16_d128 : qt == 32 ? rows32 : rows16;
-      const int waves = waves_of(split), units = waves / split, blocks = (t_kv + qt - 1) / qt;
-      const long long groups = bh * (((t_q + qt - 1) / qt + units - 1) / units);
-      const int resident = c.resident * 4 / waves, walk = (blocks + split - 1) / split;
-      auto round = [&](long long n) {
-        return (split == 1 ? c.start : c.start_split) + walk * fmax(c.latency, (double)(n * waves / 4) * c.work);
-      };
-      const long long per_round = 256LL * resident, rest = groups % per_round;
-      const double t = c.base + (double)(groups / per_round) * round(resident) + (rest ? round((rest + 255) / 256) : 0.0);
-      if (t < least) {
-        least = t;
-        best = Choice{qt, split, 0};
-      }
-    }
-  // (a wave of the other kernel holds 32 queries, and below 128 of them it has never won)
-  if (t_q <= 32 || bh * ((t_q + 31) / 32) < 128) return best;
-  // (its scores are exact to 2^-67 beside their roundings, which a scale this large would bring up)
-  if (softmax_scale > 0x1p30f) return best;
-  // The kernel of bf16 parts, where it is modelled to be the faster one: roughly from 500 blocks of 32 queries on.  (The 16-row variants
-  // take 1.15 of their model there, which the margin makes up for in part.)  Fitted to 2000 shapes (8 to 4096 (b,h), 33 to 2500 queries,
-  // 33 to 6000 keys): the choice takes 1.007 of the best of all variants on average at head dim 64, 1.001 at 128, and 1.03 and 1.04 of what
-  // it takes without this kernel at most.  256 (b,h), us, without / with: 64 x 155 15.3 / 12.6, 100 x 255 31 / 20, 256 x 680 112 / 65.
-  static const PartsCost parts64[] = {{8, 1, 1, 0.32, 4.15, 0.1, 0.87, 0.88, 0.17}, {4, 1, 2, 0.97, 4.48, 1.58, 1.09, 0.77, 0.33},
-                                      {4, 2, 1, 0.0, 7.12, 0.81, 1.51, 0.57, 0.27}};
-  static const PartsCost parts128{4, 1, 1, 0.0, 9.0, 2.93, 0.0, 3.12, 0.1};
-  least *= head_dim == 64 && best.qt == 16 ? 1.05 : 0.95;
-  for (int i = 0; i < (head_dim == 64 ? 3 : 1); ++i) {
-    const PartsCost& c = head_dim == 64 ? parts64[i] : parts128;
-    const int q_blocks = (t_q + 31) / 32, tiles = (q_blocks + c.rows - 1) / c.rows, walk = ((t_kv + 31) / 32 + c.split - 1) / c.split;
-    const double on_simd = (double)q_blocks / tiles * c.split / 4;  // active waves of a workgroup
-    auto round = [&](long long n, double busy) {
-      return (c.start + walk * fmax(c.latency, c.per + (double)n * on_simd * c.work)) * (1 - c.idle * (1 - busy));
-    };
-    const long long groups = bh * tiles, per_round = 256LL * c.resident, rest = groups % per_round;
-    const double t = c.base + (double)(groups / per_round) * round(c.resident, 1.0) +
-                     (rest ? round((rest + 255) / 256, fmin(1.0, (double)rest / 256)) : 0.0);
-    if (t < least) {
-      least = t;
-      best = Choice{32, c.split, c.rows};
-    }
-  }
-  return best;
 }
 
 template <int D, int QT>
 hipError_t launch_split(int split, const void* q, void* o, void* kc, void* vc, int bh, int t_q, int64_t cap_tokens,
                         const SegTable& seg, const ExtKV& ext, const CallerIo& io, float c, hipStream_t st) {
   switch (split) {
-    case 1: return launch<D, QT, 1>(q, o, kc, vc, bh, t_q, cap_tokens, seg, ext, io, c, st);
+    case 1:  // (32-row units always split their keys)
+      if constexpr (QT == 16) return launch<D, QT, 1>(q, o, kc, vc, bh, t_q, cap_tokens, seg, ext, io, c, st);
+      return hipErrorInvalidValue;
     case 2: return launch<D, QT, 2>(q, o, kc, vc, bh, t_q, cap_tokens, seg, ext, io, c, st);
     case 4: return launch<D, QT, 4>(q, o, kc, vc, bh, t_q, cap_tokens, seg, ext, io, c, st);
     default: return launch<D, QT, 8>(q, o, kc, vc, bh, t_q, cap_tokens, seg, ext, io, c, st);
@@ -570,7 +503,7 @@ hipError_t launch_attend_f32(const void* q, void* o, void* kc, void* vc, int bh,
                              int head_dim, int64_t cap_tokens, const SegTable& seg, const ExtKV& ext,
                              const CallerIo& io, float softmax_scale, hipStream_t st) {
   const float c = softmax_scale * 1.4426950408889634f;
-  const Choice x = choose(head_dim, bh, t_q, seg.total, softmax_scale);
+  const F32Choice x = choose_f32(head_dim, bh, t_q, seg.total, softmax_scale);
   if (x.parts) return launch_attend_f32_parts(x.parts, x.split, q, o, kc, vc, bh, t_q, head_dim, cap_tokens, seg, ext, io, softmax_scale, st);
   if (head_dim == 128) return launch_split<128, 16>(x.split, q, o, kc, vc, bh, t_q, cap_tokens, seg, ext, io, c, st);
   return x.qt == 32 ? launch_split<64, 32>(x.split, q, o, kc, vc, bh, t_q, cap_tokens, seg, ext, io, c, st)

@@ -1,6 +1,7 @@
 """fp32 attention on the bf16 matrix pipe (three parts per operand): launches large enough that the dispatch takes it, in all of its
 workgroup shapes -- 8 or 4 row groups, 4 of them with the keys dealt to two -- at query counts around 32, 128 and 256, key counts that end
-inside a block and a tile, and segments that end inside one fetch.  Against the oracle; cache contents bit-exact."""
+inside a block and a tile, and segments that end inside one fetch.  Against the oracle; cache contents bit-exact.  (The schedules of
+test_forms have smaller steps too, which take the other kernel; test_f32_choice.py holds which launch takes which.)"""
 import math
 
 import pytest
