@@ -106,24 +106,29 @@ struct NewRanges {
   int32_t len[2];
 };
 
-// Workgroup id -> unit (b,h) and query tile; bh == n_bh: none.  Consecutive ids go round-robin to the 8 XCDs, each with its own L2,
+// Workgroup id -> unit (b,h) and query tile; bh >= n_bh: none.  Consecutive ids go round-robin to the 8 XCDs, each with its own L2,
 // so the query tiles of one (b,h) are given ids 8 apart: they run on one XCD back to back, the second one finds K~ and V~ in that
 // L2 -- and so does the first what the append in front of the launch left there, whose workgroups are dealt to the XCDs in the same
-// way.  The units that are left when n_bh is no multiple of 8 would keep as many XCDs busy: their tiles are dealt to all 8 in equal
-// shares.  us: bf16, 4 (b,h), 1600 x 4240 47 -> 27, 9 (b,h), 576 x 1152 16.5 -> 10.0; fp32, head dim 128, 1 (b,h), 1600 x 1612 170 -> 44, 9
-// (b,h), 1600 x 1600 274 -> 144.  (Equal shares of all units: as fast, but a layer of fp32 on one image loses what the append left,
-// 113 -> 118 us.)  kShares: there may be units left over (uneven(), below); without, a multiple of 8 or one tile each.  The fp32 kernel
-// of small launches comes in both forms: one layer on one image takes 112.5 us with the branch and 112.0 without, whose runs differ by
-// 0.2.  (bf16 in both forms: nothing that goes beyond what runs differ by, 1.000 of the time at 16 layers on 1 and on 32 images, 1.001 at
-// six layers on 256.)
+// way.  The units that are left when n_bh is no multiple of 8 would keep as many XCDs busy: if that puts more than `most` tiles on
+// an XCD, which has 32 CUs, their tiles are dealt to all 8 in equal shares.  us: bf16, 4 (b,h), 1600 x 4240 47 -> 27, 9 (b,h), 576 x 1152
+// 16.5 -> 10.0; fp32, head dim 128, 1 (b,h), 1600 x 1612 170 -> 44, 9 (b,h), 1600 x 1600 274 -> 144.  (Equal shares of all units: as fast,
+// but a layer of fp32 on one image loses what the append left, 113 -> 118 us.)  With few tiles the L2 counts for more; each kernel has
+// its own `most`, measured beside it.
 struct Place {
   int bh, tile;
 };
+// units that stay on one XCD each: all of them, rounded up to whole groups of 8, or the whole groups only
+inline int whole_units(int n_bh, int n_tiles, int most) {
+  return n_tiles > 1 && ((long long)n_bh + 7) / 8 * n_tiles > most ? n_bh & ~7 : (int)(((long long)n_bh + 7) / 8 * 8);
+}
+// kShares: n_whole < n_bh is possible.  (The fp32 kernel of small launches comes in both forms: one layer on one image takes 112.5 us
+// with the branch and 112.0 without, whose runs differ by 0.2.  bf16 in both forms: nothing that goes beyond what runs differ by, 1.000 of
+// the time at 16 layers on 1 and on 32 images, 1.001 at six layers on 256.)
 template <bool kShares>
-__host__ __device__ inline Place place(unsigned id, int n_bh, int n_tiles) {
+__host__ __device__ inline Place place(unsigned id, int n_bh, int n_tiles, int n_whole) {
   const unsigned per_group = 8u * n_tiles, group = id / per_group, within = id - group * per_group;
   Place at{(int)(group * 8 + (within & 7)), (int)(within >> 3)};
-  if (kShares && __builtin_expect((int)(group * 8 + 8) > n_bh, 0)) {
+  if (kShares && __builtin_expect((int)(group * 8 + 8) > n_whole, 0)) {
     const unsigned all = (n_bh - group * 8) * n_tiles, share = all >> 3, more = all & 7, xcd = within & 7, nth = within >> 3;
     if (nth >= share + (xcd < more ? 1 : 0)) return {n_bh, 0};
     const unsigned item = xcd * share + (xcd < more ? xcd : more) + nth, unit = item / (unsigned)n_tiles;
@@ -131,10 +136,11 @@ __host__ __device__ inline Place place(unsigned id, int n_bh, int n_tiles) {
   }
   return at;
 }
-
-inline bool uneven(int n_bh, int n_tiles) { return (n_bh & 7) != 0 && n_tiles > 1; }
-// workgroups of a launch that gives n_tiles of them to each (b,h) (place(), above)
-inline unsigned placed_grid(int n_bh, int n_tiles) { return (unsigned)((long long)(n_bh & ~7) * n_tiles + ((long long)(n_bh & 7) * n_tiles + 7) / 8 * 8); }
+// workgroups of a launch that gives n_tiles of them to each (b,h)
+inline unsigned placed_grid(int n_bh, int n_tiles, int n_whole) {
+  const long long left = n_bh > n_whole ? n_bh - n_whole : 0;
+  return (unsigned)((long long)n_whole * n_tiles + (left * n_tiles + 7) / 8 * 8);
+}
 
 #if defined(__HIPCC__)
 // x plus its value in the lane that the cross-lane pattern pairs with this one, on the vector ALU

@@ -70,6 +70,9 @@ constexpr int kSmallTq = 32;
 constexpr float kMaxLag = 6.0f;
 // sum of a lane's 16 new probabilities above which the reference is looked at again: 16 * 2^kMaxLag
 constexpr float kTripSum = 1024.0f;
+// query tiles on the fullest XCD up to which a (b,h) stays on one (place()).  Equal shares over whole (b,h): up to 8 1.00 to 1.04 of the
+// time (15 to 37 us a launch, head dim 128 only), 12 to 32 0.94 to 1.03, 48 0.77 to 0.59.
+constexpr int kMostWhole = 8;
 
 #define AMSKV_LDS __attribute__((address_space(3)))
 
@@ -300,7 +303,7 @@ template <int D, int NQ, int kWaves, int kTileKeys, bool kDensity, int kSplit>
 __device__ __forceinline__ void attend_unit(
     const __bf16* __restrict__ q, __bf16* __restrict__ o, char* __restrict__ kc, char* __restrict__ vc,
     int t_q, long long cap_tokens, const SegTable& seg, const ExtKV& ext_kv, const CallerIo& io, float scale_log2e, int n_bh,
-    int n_qtiles, const GroupEnds& groups, float* __restrict__ partial) {
+    int n_qtiles, int n_whole, const GroupEnds& groups, float* __restrict__ partial) {
   using Loader = TileLoader<D, kWaves, kTileKeys>;
   constexpr int RB = D * 2;   // bytes per token row
   constexpr int KS = D / 16;  // K-steps of the first product
@@ -341,7 +344,7 @@ __device__ __forceinline__ void attend_unit(
     bh_i = blockIdx.x;
     q_tile = 0;
   } else {
-    const Place at = place<true>(blockIdx.x, n_bh, n_qtiles);
+    const Place at = place<true>(blockIdx.x, n_bh, n_qtiles, n_whole);
     bh_i = at.bh;
     q_tile = at.tile;
   }
@@ -883,19 +886,19 @@ __device__ __forceinline__ void attend_unit(
 template <int D, int NQ, int kWaves, int kTileKeys, int kMinWavesPerSimd, int kSplit>
 __global__ __launch_bounds__(64 * kWaves, kMinWavesPerSimd) void attend_bf16_kernel(
     const __bf16* __restrict__ q, __bf16* __restrict__ o, char* __restrict__ kc, char* __restrict__ vc,
-    int t_q, long long cap_tokens, SegTable seg, ExtKV ext_kv, CallerIo io, float scale_log2e, int n_bh, int n_qtiles) {
+    int t_q, long long cap_tokens, SegTable seg, ExtKV ext_kv, CallerIo io, float scale_log2e, int n_bh, int n_qtiles, int n_whole) {
   attend_unit<D, NQ, kWaves, kTileKeys, false, kSplit>(q, o, kc, vc, t_q, cap_tokens, seg, chosen(ext_kv), io, scale_log2e, n_bh,
-                                               n_qtiles, GroupEnds{}, nullptr);
+                                               n_qtiles, n_whole, GroupEnds{}, nullptr);
 }
 
 // The same step with the attention density of its own queries as a by-product (no second pass over Q and K).
 template <int D, int NQ, int kWaves, int kTileKeys, int kMinWavesPerSimd, int kSplit = 1>
 __global__ __launch_bounds__(64 * kWaves, kMinWavesPerSimd) void attend_density_bf16_kernel(
     const __bf16* __restrict__ q, __bf16* __restrict__ o, char* __restrict__ kc, char* __restrict__ vc,
-    int t_q, long long cap_tokens, SegTable seg, ExtKV ext_kv, CallerIo io, float scale_log2e, int n_bh, int n_qtiles,
+    int t_q, long long cap_tokens, SegTable seg, ExtKV ext_kv, CallerIo io, float scale_log2e, int n_bh, int n_qtiles, int n_whole,
     GroupEnds groups, float* __restrict__ partial) {
   attend_unit<D, NQ, kWaves, kTileKeys, true, kSplit>(q, o, kc, vc, t_q, cap_tokens, seg, chosen(ext_kv), io, scale_log2e, n_bh,
-                                              n_qtiles, groups, partial);
+                                              n_qtiles, n_whole, groups, partial);
 }
 
 template <int D, int NQ, int kWaves, int kTileKeys, int kMinWavesPerSimd, int kSplit = 1>
@@ -903,10 +906,11 @@ hipError_t launch(const void* q, void* o, void* kc, void* vc, int bh, int t_q, i
                   const SegTable& seg, const ExtKV& ext, const CallerIo& io, float c, hipStream_t st) {
   constexpr int BM = kWaves / kSplit * 32 * NQ;
   const int n_qtiles = (t_q + BM - 1) / BM;
-  dim3 grid(placed_grid(bh, n_qtiles)), block(64 * kWaves);
+  const int n_whole = whole_units(bh, n_qtiles, kMostWhole);
+  dim3 grid(placed_grid(bh, n_qtiles, n_whole)), block(64 * kWaves);
   hipLaunchKernelGGL((attend_bf16_kernel<D, NQ, kWaves, kTileKeys, kMinWavesPerSimd, kSplit>), grid, block, 0, st,
                      (const __bf16*)q, (__bf16*)o, (char*)kc, (char*)vc, t_q, (long long)cap_tokens, seg, ext, io, c,
-                     bh, n_qtiles);
+                     bh, n_qtiles, n_whole);
   return hipGetLastError();
 }
 
@@ -916,10 +920,11 @@ hipError_t launch_density_variant(const void* q, void* o, void* kc, void* vc, in
                                   float* partial, hipStream_t st) {
   constexpr int BM = kWaves / kSplit * 32 * NQ;
   const int n_qtiles = (t_q + BM - 1) / BM;
-  dim3 grid(placed_grid(bh, n_qtiles)), block(64 * kWaves);
+  const int n_whole = whole_units(bh, n_qtiles, kMostWhole);
+  dim3 grid(placed_grid(bh, n_qtiles, n_whole)), block(64 * kWaves);
   hipLaunchKernelGGL((attend_density_bf16_kernel<D, NQ, kWaves, kTileKeys, kMinWavesPerSimd, kSplit>), grid, block, 0, st,
                      (const __bf16*)q, (__bf16*)o, (char*)kc, (char*)vc, t_q, (long long)cap_tokens, seg, ext, io, c,
-                     bh, n_qtiles, groups, partial);
+                     bh, n_qtiles, n_whole, groups, partial);
   return hipGetLastError();
 }
 

@@ -31,6 +31,9 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 // waves of a workgroup: four units, or the four or eight slices of one
 constexpr int waves_of(int split) { return split == 8 ? 8 : 4; }
+// query blocks on the fullest XCD up to which a (b,h) stays on one (place()).  Equal shares over whole (b,h): fewer than 8 (b,h), up to 4
+// blocks 1.03 of the time (6 us a launch), 8 1.08, 16 1.01, 20 to 28 0.99, 32 0.96, 64 0.66; more (b,h): 0.99 to 1.01 up to 32, 48 0.72.
+constexpr int kMostWhole = 8;
 
 #define AMSKV_LDS __attribute__((address_space(3)))
 
@@ -65,7 +68,7 @@ __device__ __forceinline__ void settle_mfma(f32x16& acc) { asm volatile("s_nop 1
 template <int D, int kSplit, bool kDensity>
 __global__ __launch_bounds__(64 * waves_of(kSplit), !kDensity ? (D == 64 ? 4 : 2) : kSplit > 1 ? 1 : D == 64 ? 3 : 2) void attend_bf16_small_kernel(
     const __bf16* __restrict__ q, __bf16* __restrict__ o, char* __restrict__ kc, char* __restrict__ vc,
-    int t_q, long long cap_tokens, SegTable seg, ExtKV ext_in, CallerIo io, float scale_log2e, int n_qblk, int n_bh,
+    int t_q, long long cap_tokens, SegTable seg, ExtKV ext_in, CallerIo io, float scale_log2e, int n_qblk, int n_bh, int n_whole,
     GroupEnds groups, float* __restrict__ partial) {
   const ExtKV ext_kv = chosen(ext_in);
   constexpr int kWaves = waves_of(kSplit);
@@ -86,7 +89,7 @@ __global__ __launch_bounds__(64 * waves_of(kSplit), !kDensity ? (D == 64 ? 4 : 2
   const int lane = threadIdx.x & 63;
   const int slice = kSplit == 1 ? 0 : wave;
   // without a split: launched with one block of queries only
-  const Place place_of = kSplit == 1 ? Place{(int)(blockIdx.x * kWaves) + wave, 0} : place<true>(blockIdx.x, n_bh, n_qblk);
+  const Place place_of = kSplit == 1 ? Place{(int)(blockIdx.x * kWaves) + wave, 0} : place<true>(blockIdx.x, n_bh, n_qblk, n_whole);
   const int q_blk = place_of.tile;
   const long long bh = place_of.bh;
   if (bh >= n_bh) return;  // without a split nothing below synchronises across waves; with one, the whole workgroup leaves
@@ -370,11 +373,12 @@ hipError_t launch_one(const void* q, void* o, void* kc, void* vc, int bh, int t_
                       const ExtKV& ext, const CallerIo& io, float c, const GroupEnds& groups, float* partial, hipStream_t st) {
   const int n_qblk = (t_q + 31) / 32;
   constexpr int kWaves = waves_of(kSplit);
+  const int n_whole = whole_units(bh, n_qblk, kMostWhole);
   if (kSplit == 1 && n_qblk != 1) return hipErrorInvalidValue;  // (the dispatch splits wherever a unit has more queries)
   const unsigned grid = kSplit == 1 ? (unsigned)(((long long)bh * n_qblk + kWaves - 1) / kWaves)
-                                    : placed_grid(bh, n_qblk);
+                                    : placed_grid(bh, n_qblk, n_whole);
   hipLaunchKernelGGL((attend_bf16_small_kernel<D, kSplit, kDensity>), dim3(grid), dim3(64 * kWaves), 0, st, (const __bf16*)q,
-                     (__bf16*)o, (char*)kc, (char*)vc, t_q, (long long)cap_tokens, seg, ext, io, c, n_qblk, bh, groups, partial);
+                     (__bf16*)o, (char*)kc, (char*)vc, t_q, (long long)cap_tokens, seg, ext, io, c, n_qblk, bh, n_whole, groups, partial);
   return hipGetLastError();
 }
 

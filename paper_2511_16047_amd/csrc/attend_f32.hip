@@ -63,6 +63,9 @@ struct Mfma<16> {
 // split: per wave a block of K and one of V (the K piece later holds the wave's partial result), and its softmax statistics;
 // else a ring of blocks for the workgroup
 constexpr int kRing = 4;
+// workgroups on the fullest XCD up to which a (b,h) stays on one (place()).  Equal shares over whole (b,h): up to 4 1.03 to 1.06 of the
+// time (7 to 11 us a launch), 8 1.01 to 1.05, 12 to 32 0.99 to 1.04, 48 0.84 to 0.53.
+constexpr int kMostWhole = 32;
 constexpr int lds_bytes(int D, int QT, int split) {
   return split > 1 ? waves_of(split) * (2 * QT * D * 4 + QT * 8) : kRing * 2 * QT * D * 4;
 }
@@ -92,7 +95,7 @@ __device__ __forceinline__ void wait_lds_reads() { asm volatile("s_waitcnt lgkmc
 template <int D, int QT, int kSplit, bool kShares>
 __global__ __launch_bounds__(64 * waves_of(kSplit), 2) void attend_f32_kernel(
     const float* __restrict__ q, float* __restrict__ o, float* __restrict__ kc, float* __restrict__ vc, int t_q,
-    long long cap_tokens, SegTable seg, ExtKV ext_kv, CallerIo io, float scale_log2e, int n_bh, int n_parts) {
+    long long cap_tokens, SegTable seg, ExtKV ext_kv, CallerIo io, float scale_log2e, int n_bh, int n_parts, int n_whole) {
   typedef Mfma<QT> M;
   constexpr int H = 64 / QT;         // lane groups
   constexpr int DL = D / H;          // channels of a K or Q row one lane holds
@@ -112,7 +115,7 @@ __global__ __launch_bounds__(64 * waves_of(kSplit), 2) void attend_f32_kernel(
   const int lane = threadIdx.x & 63;
   const int r = lane % QT, g = lane / QT;
   const int slice = wave % kSplit;
-  const Place place_of = place<kShares>(blockIdx.x, n_bh, n_parts);
+  const Place place_of = place<kShares>(blockIdx.x, n_bh, n_parts, n_whole);
   const int part = place_of.tile;
   const long long bh = place_of.bh;
   if (bh >= n_bh) return;  // whole workgroup
@@ -477,10 +480,11 @@ hipError_t launch(const void* q, void* o, void* kc, void* vc, int bh, int t_q, i
   const int n_parts = ((t_q + QT - 1) / QT + kUnits - 1) / kUnits;
   constexpr bool kOnePart = D == 64 && kSplit == 1;  // at most 64 queries (choose_f32())
   if (kOnePart && n_parts > 1) return hipErrorInvalidValue;
-  dim3 grid(placed_grid(bh, n_parts)), block(64 * kWaves);
-  const auto kernel = !kOnePart && uneven(bh, n_parts) ? attend_f32_kernel<D, QT, kSplit, !kOnePart> : attend_f32_kernel<D, QT, kSplit, false>;
+  const int n_whole = whole_units(bh, n_parts, kMostWhole);
+  dim3 grid(placed_grid(bh, n_parts, n_whole)), block(64 * kWaves);
+  const auto kernel = !kOnePart && n_whole < bh ? attend_f32_kernel<D, QT, kSplit, !kOnePart> : attend_f32_kernel<D, QT, kSplit, false>;
   hipLaunchKernelGGL(kernel, grid, block, 0, st, (const float*)q, (float*)o, (float*)kc, (float*)vc,
-                     t_q, (long long)cap_tokens, seg, ext, io, c, bh, n_parts);
+                     t_q, (long long)cap_tokens, seg, ext, io, c, bh, n_parts, n_whole);
   return hipGetLastError();
 }
 

@@ -1,6 +1,6 @@
 """The rule that places query tiles on workgroups (place() of csrc/amskv_internal.hpp, the same code the kernels run) built for the CPU:
-every tile of every (b,h) exactly once, XCDs with equal numbers of them, whole (b,h) per XCD up to the last multiple of eight, and
-the form without left-over units where there are none."""
+every tile of every (b,h) exactly once; whole (b,h) per XCD up to the last multiple of eight, and beyond it while no XCD has more than a
+given number of tiles; else XCDs with equal numbers of them; and the form without left-over units where there are none."""
 import os
 import shutil
 import subprocess
@@ -20,25 +20,29 @@ static void check(bool ok, const char* what, int n, int t) {
 }
 int main() {
   const int tiles[] = {1, 2, 3, 5, 7, 8, 9, 13, 32, 79};
+  for (int most : {0, 8, 24, 32})
   for (int n = 1; n <= 130; ++n)
     for (int t : tiles) {
+      const bool few = (n + 7) / 8 * t <= most, even = n % 8 == 0 || t == 1;
+      const int whole = whole_units(n, t, most);
+      check((whole < n) == !(few || even) && whole % 8 == 0, "the rule", n, t);
       std::vector<int> seen(n * t, 0), per_xcd(8, 0);
-      for (unsigned id = 0; id < placed_grid(n, t); ++id) {
-        const Place p = uneven(n, t) ? place<true>(id, n, t) : place<false>(id, n, t);
+      for (unsigned id = 0; id < placed_grid(n, t, whole); ++id) {
+        const Place p = whole < n ? place<true>(id, n, t, whole) : place<false>(id, n, t, whole);
         check(p.bh >= 0 && p.tile >= 0 && p.tile < t, "in range", n, t);
         if (p.bh >= n) continue;
         ++seen[p.bh * t + p.tile];
         ++per_xcd[id & 7];
-        check(p.bh >= (n & ~7) || (p.bh & 7) == (int)(id & 7), "whole units on one XCD", n, t);
-        if (!uneven(n, t)) {
-          const Place q = place<true>(id, n, t);
+        check((p.bh >= (n & ~7) && !few) || (p.bh & 7) == (int)(id & 7), "whole units on one XCD", n, t);
+        if (whole >= n) {
+          const Place q = place<true>(id, n, t, whole);
           check(q.bh == p.bh && q.tile == p.tile, "both forms agree", n, t);
         }
       }
       for (int x : seen) check(x == 1, "every tile once", n, t);
       int lo = n * t, hi = 0;
       for (int x : per_xcd) lo = x < lo ? x : lo, hi = x > hi ? x : hi;
-      check(hi - lo <= 1, "equal shares", n, t);
+      check(hi - lo <= (few ? t : 1), "equal shares", n, t);
     }
   std::puts("all placed");
 }
