@@ -191,7 +191,7 @@ __device__ __forceinline__ int locate_row(const SegTable& seg, int j, bool& ext)
 #endif
 
 // ---- kernel launchers (each validates nothing: the host layer has checked shapes) ----
-// kc/vc are written only when ext.wb_off >= 0 (fused append)
+// kc/vc are written only where writes_back() says so (fused append, moves of cached rows)
 hipError_t launch_attend_bf16(const void* q, void* o, void* kc, void* vc, int bh,
                               int t_q, int head_dim, int64_t cap_tokens, const SegTable& seg,
                               const ExtKV& ext, const CallerIo& io, float softmax_scale, hipStream_t st);

@@ -58,7 +58,7 @@ inline F32Choice choose_f32(int head_dim, long long bh, int t_q, int t_kv, float
   // The kernel of bf16 parts, where it is modelled to be the faster one: roughly from 500 blocks of 32 queries on.  (The 16-row variants
   // take 1.15 of their model there, which the margin makes up for in part.)  Fitted to 2000 shapes (8 to 4096 (b,h), 33 to 2500 queries,
   // 33 to 6000 keys): the choice takes 1.007 of the best of all variants on average at head dim 64, 1.001 at 128, and 1.03 and 1.04 of what
-  // it takes without this kernel at most.  256 (b,h), us, without / with: 64 x 155 15.3 / 12.6, 100 x 255 31 / 20, 256 x 680 112 / 65.
+  // it takes without this kernel at most.  256 (b,h), us, without / with: 64 x 155 14.6 / 12.0, 100 x 255 30 / 19, 256 x 680 110 / 65.
   static const F32PartsCost parts64[] = {{8, 1, 1, 0.32, 4.15, 0.1, 0.87, 0.88, 0.17}, {4, 1, 2, 0.97, 4.48, 1.58, 1.09, 0.77, 0.33},
                                       {4, 2, 1, 0.0, 7.12, 0.81, 1.51, 0.57, 0.27}};
   static const F32PartsCost parts128{4, 1, 1, 0.0, 9.0, 2.93, 0.0, 3.12, 0.1};

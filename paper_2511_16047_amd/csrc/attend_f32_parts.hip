@@ -4,14 +4,15 @@
 // 2^-24 of it.  Sums stay in fp32, probabilities are formed in fp32 and split like the inputs.
 //
 // Why: v_mfma_f32_32x32x16_bf16 has 16 times the rate of v_mfma_f32_32x32x2_f32, and it adds eight products exactly before it rounds
-// its accumulator (to nearest): faster, and closer to the exact sums.  Against the kernel of attend_f32.hip, us (rel error against
-// 64 bits): 256 (b,h), 256 x 680 112 -> 70 (4.8e-7 -> 2.0e-7), 169 x 424 65 -> 41 (3.9 -> 1.7e-7), 100 x 255 32 -> 21 (2.0 -> 1.3e-7); 64 (b,h),
-// 1024 x 2645 389 -> 221 (9.3 -> 3.6e-7); head dim 128, 256 (b,h), 256 x 680 219 -> 164 (4.9 -> 2.0e-7), 32 (b,h), 1024 x 1621 256 -> 175
-// (7.4 -> 3.0e-7).  One accumulator for all of a score's large products is 4 % faster, and less exact than that kernel where one channel
-// outweighs the others (1.6e-6 for 1.5e-6; as it is 1.1e-6).
-// What bounds it at the large sizes is the matrix pipe next to the power limit: busy 60 % of the time at 1.9 GHz (1.23 PFLOP/s of bf16
-// products; a loop of nothing but these instructions on random data runs at 1.6 PFLOP/s and 1.6 GHz).  A second tile in flight and a raised
-// wave priority for half of the waves changed nothing (+-2 %).
+// its accumulator (to nearest): faster, and closer to the exact sums.  Against the kernel of attend_f32.hip in the form that took these
+// launches before, us in a long run of launches (rel error against 64 bits): 256 (b,h), 256 x 680 110 -> 65 (4.8e-7 -> 2.0e-7), 169 x 424
+// 64 -> 38 (3.9 -> 1.7e-7), 100 x 255 30 -> 19 (2.0 -> 1.3e-7); 64 (b,h), 1024 x 2645 389 -> 219 (9.3 -> 3.6e-7); head dim 128, 256 (b,h), 256 x 680
+// 221 -> 151 (4.9 -> 2.0e-7), 32 (b,h), 1024 x 1621 256 -> 159 (7.4 -> 3.0e-7).  (The first few launches after a pause, and those between
+// smaller ones in a pass, take a tenth more: 256 x 680 73.)  One accumulator for all of a score's large products is 4 % faster, and less
+// exact than that kernel where one channel outweighs the others (1.6e-6 for 1.5e-6; as it is 1.1e-6).
+// What bounds it at the large sizes is the matrix pipe next to the power limit: busy 51 % of the SIMD cycles at 256 x 680 and 59 % at 1024 x
+// 2645, at 1.8 GHz (1.05 and 1.2 PFLOP/s of bf16 products; a loop of nothing but these instructions on random data runs at 1.6 PFLOP/s
+// and 1.6 GHz), vector ALUs 44 and 47 %.  A second tile in flight and a raised wave priority for half of the waves changed nothing (+-2 %).
 //
 // Work.  A workgroup has kRowWaves * kSplit waves: kRowWaves of them hold 32 query rows of one (b,h) each, kSplit of them share a
 // row group and take the blocks of a tile (kSplit * 32 keys) in turn, with softmax statistics of their own that meet in LDS at the end.
@@ -27,7 +28,7 @@
 // Large numbers.  From 2^59 on the products of parts of Q and K may overflow; every lane keeps the largest magnitude of theirs that it
 // has split.  In V a magnitude from 2^95 on, scaled (below), or a sum that overflows, leaves sums in O that are not finite, in all rows.  A
 // workgroup that sees either does its work again on the fp32 matrix instructions, which give such inputs, infinities too, what the
-// formula has.  (256 (b,h), 256 x 680, such a value in each: 214 us instead of 70.  A maximum over V too, beside the scaling: 0.4 %
+// formula has.  (256 (b,h), 256 x 680, such a value in each: 196 us instead of 65.  A maximum over V too, beside the scaling: 0.4 %
 // of a stack of layers on 16 images.)
 // Small numbers.  bf16 has subnormals, in steps of 2^-133, and the matrix cores take them: a part is off by 2^-134 at most.  V is split
 // scaled, which keeps all bits of every normal number.  In a score that error, times 2^59 and 2 D, is below 2^-66, nothing next to
