@@ -49,9 +49,10 @@ def _attend(q, k, v, scale=0.0):
     return o
 
 
-# magnitudes whose parts leave bf16's range on either side: powers of two on Q, K, V; one value that rounds to infinity in bf16
+# magnitudes whose parts leave bf16's range on either side: powers of two on Q, K, V; one value that rounds to infinity in bf16; V whose
+# sums do and do not overflow where they are formed
 @pytest.mark.parametrize("eq,ek,ev,huge", [(0, 0, 0, False), (0, 0, 0, True), (0, 0, -118, False), (-118, 118, 0, False), (118, -118, 0, False),
-                                           (-90, 90, 90, False), (0, 0, -118, True)])
+                                           (-90, 90, 90, False), (0, 0, -118, True), (0, 0, 84, False), (0, 0, 94, False)])
 @pytest.mark.parametrize("D,bh,tq,prev", [(64, 256, 255, 66), (64, 300, 127, 1), (64, 48, 577, 2), (128, 256, 200, 63)])
 def test_magnitudes(D, bh, tq, prev, eq, ek, ev, huge):
     g = torch.Generator(device="cuda").manual_seed(tq)
