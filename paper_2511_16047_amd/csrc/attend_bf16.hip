@@ -887,6 +887,7 @@ template <int D, int NQ, int kWaves, int kTileKeys, int kMinWavesPerSimd, int kS
 __global__ __launch_bounds__(64 * kWaves, kMinWavesPerSimd) void attend_bf16_kernel(
     const __bf16* __restrict__ q, __bf16* __restrict__ o, char* __restrict__ kc, char* __restrict__ vc,
     int t_q, long long cap_tokens, SegTable seg, ExtKV ext_kv, CallerIo io, float scale_log2e, int n_bh, int n_qtiles, int n_whole) {
+  fetch_arguments<kAttentionArguments>();
   attend_unit<D, NQ, kWaves, kTileKeys, false, kSplit>(q, o, kc, vc, t_q, cap_tokens, seg, chosen(ext_kv), io, scale_log2e, n_bh,
                                                n_qtiles, n_whole, GroupEnds{}, nullptr);
 }
@@ -897,6 +898,7 @@ __global__ __launch_bounds__(64 * kWaves, kMinWavesPerSimd) void attend_density_
     const __bf16* __restrict__ q, __bf16* __restrict__ o, char* __restrict__ kc, char* __restrict__ vc,
     int t_q, long long cap_tokens, SegTable seg, ExtKV ext_kv, CallerIo io, float scale_log2e, int n_bh, int n_qtiles, int n_whole,
     GroupEnds groups, float* __restrict__ partial) {
+  fetch_arguments<kAttentionArguments>();
   attend_unit<D, NQ, kWaves, kTileKeys, true, kSplit>(q, o, kc, vc, t_q, cap_tokens, seg, chosen(ext_kv), io, scale_log2e, n_bh,
                                               n_qtiles, n_whole, groups, partial);
 }

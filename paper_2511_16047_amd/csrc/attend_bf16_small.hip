@@ -70,6 +70,7 @@ __global__ __launch_bounds__(64 * waves_of(kSplit), !kDensity ? (D == 64 ? 4 : 2
     const __bf16* __restrict__ q, __bf16* __restrict__ o, char* __restrict__ kc, char* __restrict__ vc,
     int t_q, long long cap_tokens, SegTable seg, ExtKV ext_in, CallerIo io, float scale_log2e, int n_qblk, int n_bh, int n_whole,
     GroupEnds groups, float* __restrict__ partial) {
+  fetch_arguments<kAttentionArguments>();
   const ExtKV ext_kv = chosen(ext_in);
   constexpr int kWaves = waves_of(kSplit);
   constexpr int RB = D * 2;

@@ -96,6 +96,7 @@ template <int D, int QT, int kSplit, bool kShares>
 __global__ __launch_bounds__(64 * waves_of(kSplit), 2) void attend_f32_kernel(
     const float* __restrict__ q, float* __restrict__ o, float* __restrict__ kc, float* __restrict__ vc, int t_q,
     long long cap_tokens, SegTable seg, ExtKV ext_kv, CallerIo io, float scale_log2e, int n_bh, int n_parts, int n_whole) {
+  fetch_arguments<kAttentionArguments>();
   typedef Mfma<QT> M;
   constexpr int H = 64 / QT;         // lane groups
   constexpr int DL = D / H;          // channels of a K or Q row one lane holds

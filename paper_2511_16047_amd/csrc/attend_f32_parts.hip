@@ -612,6 +612,7 @@ template <int D, int kRowWaves, int kSplit, int kOcc>
 __global__ __launch_bounds__(64 * kRowWaves * kSplit, kOcc) void attend_f32_parts_kernel(
     const float* __restrict__ q, float* __restrict__ o, float* __restrict__ kc, float* __restrict__ vc, int t_q,
     long long cap_tokens, SegTable seg, ExtKV ext_kv, CallerIo io, float scale_log2e, int n_bh, int n_qtiles, int n_whole) {
+  fetch_arguments<kAttentionArguments>();
   __shared__ __align__(1024) char lds[lds_bytes(D, kSplit)];
   __shared__ float2 stat[kSplit > 1 ? kRowWaves * kSplit : 1][32];
   __shared__ int wide_flag;

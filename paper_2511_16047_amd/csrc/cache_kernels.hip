@@ -39,6 +39,7 @@ __global__ __launch_bounds__(kBlock) void roll_kernel(char* __restrict__ kc, cha
                                                       const char* __restrict__ k_new, const char* __restrict__ v_new,
                                                       int row_shift, long long cap_tokens, CopyList cl, RowMap src_map,
                                                       int heads) {
+  fetch_arguments<4 * 8 + 16 + sizeof(CopyList) + sizeof(RowMap)>();
   const long long bh = blockIdx.x;
   char* base = (blockIdx.y ? vc : kc) + ((bh * cap_tokens) << row_shift);
   const char* ext = (blockIdx.y ? v_new : k_new) + unit_offset(src_map, bh, heads);
@@ -95,6 +96,7 @@ __global__ __launch_bounds__(kThreads) void append_kernel(char* __restrict__ kc,
                                                           int row_shift, long long cap_tokens, int chunks, unsigned inv,
                                                           int rows, int parts, int dst_new, int src_first, RowMap src_map,
                                                           int heads, int n_bh) {
+  fetch_arguments<4 * 8 + 16 + 24 + sizeof(RowMap)>();
   char* cache = blockIdx.y ? vc : kc;
   const char* src = blockIdx.y ? v_new : k_new;
   const int cpr_shift = row_shift - 4;

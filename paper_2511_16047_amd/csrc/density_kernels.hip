@@ -25,6 +25,7 @@ template <int D>
 __global__ __launch_bounds__(64 * kWavesPerGroup) void density_partial_kernel(
     const __bf16* __restrict__ q, const char* __restrict__ kc, int t_q, long long cap_tokens, SegTable seg,
     ExtKV ext_kv, CallerIo io, float scale_log2e, int n_qblk, int n_units, float* __restrict__ partial) {
+  fetch_arguments<2 * 8 + 16 + sizeof(SegTable) + sizeof(ExtKV) + sizeof(CallerIo)>();
   constexpr int RB = D * 2;
   constexpr int KS = D / 16;
   __shared__ float park_sum[kWavesPerGroup][AMSKV_MAX_SCALES][64];

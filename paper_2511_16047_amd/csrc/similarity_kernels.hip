@@ -60,6 +60,7 @@ template <bool BF16, int kLanes, int kThreads>
 __global__ __launch_bounds__(kThreads) void similarity_partial_kernel(
     ScaleRef cur_ref, ScaleRef prev_ref, int heads, int h_cur, int w_cur, int h_prev, int w_prev, float scale_h, float scale_w,
     int di, int dj, float* __restrict__ partial) {
+  fetch_arguments<2 * sizeof(ScaleRef) + 36>();
   const long long bh = blockIdx.x;
   const char* cur = (const char*)(blockIdx.y ? cur_ref.v : cur_ref.k) + unit_offset(cur_ref.map, bh, heads) +
                     cur_ref.off_tokens * cur_ref.map.tok;
