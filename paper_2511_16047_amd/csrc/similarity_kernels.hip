@@ -49,26 +49,41 @@ __device__ __forceinline__ void taps(int dst, int n_in, float scale, int& i0, in
   lam = src - f;
 }
 
-// grid: (B*H, tensors); one workgroup per (b,h) of one tensor (0 = keys, 1 = values).
+// Sum over the lanes of a wave, in every one of them: lane l takes l^32, then l^16, l^8, ... l^1, each step on the vector ALU.  (Lanes that
+// agree modulo 8 may take the one four lanes back in their row of 16 for l^4.)
+__device__ __forceinline__ float wave_sum(float x) {
+  x = half_sum(x);
+  const auto sw = __builtin_amdgcn_permlane16_swap(__float_as_int(x), __float_as_int(x), false, false);
+  x = __int_as_float(sw[0]) + __int_as_float(sw[1]);
+  x = add_lane<0x128>(x);  // row_ror:8
+  x = add_lane<0x124>(x);  // row_ror:4
+  x = add_lane<0x4E>(x);   // quad_perm 2 3 0 1
+  return add_lane<0xB1>(x);  // quad_perm 1 0 3 2
+}
+
+// grid: (B*H / kUnits, tensors); kThreads threads per (b,h) of one tensor (0 = keys, 1 = values), kUnits (b,h) to a workgroup.
 // partial[(tensor*BH + bh)*4 + {0,1,2,3}] = sum_t cos_t, sum a.b, sum |a|^2, sum |b|^2.
 // Bound: HBM at the fine scales (the rows of scale s once, those of s-1 once and from L2 after that), next to the vector
 // ALU, so what a token costs beside its multiply-adds is kept down: the four bilinear weights are formed once per token,
 // sums over its lanes run on the ALU, and the cosine's square roots and quotient, which every lane of a wave would execute
 // for the one lane that needs them, run once for kLanes passes, each lane of a token keeping the sums of one of them.
 // (di, dj): how far one pass moves a thread's token on the grid.
-template <bool BF16, int kLanes, int kThreads>
-__global__ __launch_bounds__(kThreads) void similarity_partial_kernel(
-    ScaleRef cur_ref, ScaleRef prev_ref, int heads, int h_cur, int w_cur, int h_prev, int w_prev, float scale_h, float scale_w,
+template <bool BF16, int kLanes, int kThreads, int kUnits>
+__global__ __launch_bounds__(kThreads * kUnits) void similarity_partial_kernel(
+    ScaleRef cur_ref, ScaleRef prev_ref, int n_bh, int heads, int h_cur, int w_cur, int h_prev, int w_prev, float scale_h, float scale_w,
     int di, int dj, float* __restrict__ partial) {
-  fetch_arguments<2 * sizeof(ScaleRef) + 36>();
-  const long long bh = blockIdx.x;
+  static_assert(kUnits == 1 || kThreads == 64, "a (b,h) of several to a workgroup has one wave: nothing synchronises them");
+  fetch_arguments<2 * sizeof(ScaleRef) + 40>();
+  const int thread = kUnits == 1 ? threadIdx.x : threadIdx.x & 63;
+  const long long bh = kUnits == 1 ? blockIdx.x : blockIdx.x * kUnits + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (kUnits > 1 && bh >= n_bh) return;
   const char* cur = (const char*)(blockIdx.y ? cur_ref.v : cur_ref.k) + unit_offset(cur_ref.map, bh, heads) +
                     cur_ref.off_tokens * cur_ref.map.tok;
   const char* prev = (const char*)(blockIdx.y ? prev_ref.v : prev_ref.k) + unit_offset(prev_ref.map, bh, heads) +
                      prev_ref.off_tokens * prev_ref.map.tok;
   const long long cur_tok = cur_ref.map.tok, prev_tok = prev_ref.map.tok;
-  const int sub = threadIdx.x % kLanes;    // which 16-byte piece of the row
-  const int slot = threadIdx.x / kLanes;
+  const int sub = thread % kLanes;  // which 16-byte piece of the row
+  const int slot = thread / kLanes;
   constexpr int kPerPass = kThreads / kLanes;
   const int t_cur = h_cur * w_cur;
   cur += sub << 4;
@@ -131,9 +146,12 @@ __global__ __launch_bounds__(kThreads) void similarity_partial_kernel(
   // workgroup sum in a fixed order: xor tree over the lanes of a wave, then the waves in ascending order
   float acc[4] = {acc_cos, acc_ab, acc_aa, acc_bb};
 #pragma unroll
-  for (int m = 32; m > 0; m >>= 1)
-#pragma unroll
-    for (int q = 0; q < 4; ++q) acc[q] += __shfl_xor(acc[q], m, 64);
+  for (int q = 0; q < 4; ++q) acc[q] = wave_sum(acc[q]);
+  float* out = partial + ((long long)blockIdx.y * n_bh + bh) * 4;
+  if constexpr (kThreads == 64) {
+    if (thread == 0) *reinterpret_cast<float4*>(out) = make_float4(acc[0], acc[1], acc[2], acc[3]);
+    return;
+  }
   __shared__ float red[kThreads / 64][4];
   if ((threadIdx.x & 63) == 0)
     for (int q = 0; q < 4; ++q) red[threadIdx.x >> 6][q] = acc[q];
@@ -141,16 +159,16 @@ __global__ __launch_bounds__(kThreads) void similarity_partial_kernel(
   if (threadIdx.x < 4) {
     float total = red[0][threadIdx.x];
     for (int w = 1; w < kThreads / 64; ++w) total += red[w][threadIdx.x];
-    partial[((long long)blockIdx.y * gridDim.x + bh) * 4 + threadIdx.x] = total;
+    out[threadIdx.x] = total;
   }
 }
 
-template <bool BF16, int kLanes, int kThreads>
+template <bool BF16, int kLanes, int kThreads, int kUnits = 1>
 hipError_t launch_partial(const ScaleRef& cur, const ScaleRef& prev, int bh, int heads, int h_cur, int w_cur, int h_prev, int w_prev,
                           float* partial_ws, hipStream_t st) {
   constexpr int kPerPass = kThreads / kLanes;
-  hipLaunchKernelGGL((similarity_partial_kernel<BF16, kLanes, kThreads>), dim3(bh, cur.v && prev.v ? 2 : 1), dim3(kThreads), 0, st, cur,
-                     prev, heads, h_cur, w_cur, h_prev, w_prev, (float)h_prev / (float)h_cur, (float)w_prev / (float)w_cur,
+  hipLaunchKernelGGL((similarity_partial_kernel<BF16, kLanes, kThreads, kUnits>), dim3((bh + kUnits - 1) / kUnits, cur.v && prev.v ? 2 : 1),
+                     dim3(kThreads * kUnits), 0, st, cur, prev, bh, heads, h_cur, w_cur, h_prev, w_prev, (float)h_prev / (float)h_cur, (float)w_prev / (float)w_cur,
                      kPerPass / w_cur, kPerPass % w_cur, partial_ws);
   return hipGetLastError();
 }
@@ -167,9 +185,7 @@ __global__ __launch_bounds__(64) void similarity_total_kernel(const float* __res
     acc[0] += x.x; acc[1] += x.y; acc[2] += x.z; acc[3] += x.w;
   }
 #pragma unroll
-  for (int m = 32; m > 0; m >>= 1)
-#pragma unroll
-    for (int q = 0; q < 4; ++q) acc[q] += __shfl_xor(acc[q], m, 64);
+  for (int q = 0; q < 4; ++q) acc[q] = wave_sum(acc[q]);
   if (threadIdx.x == 0)
     *reinterpret_cast<float4*>(totals + ((long long)tn * heads + h) * 4) = make_float4(acc[0], acc[1], acc[2], acc[3]);
 }
@@ -246,16 +262,22 @@ hipError_t launch_similarity(const ScaleRef& cur, const ScaleRef& prev, int batc
   // 0.93-1.1 at 448; 128 KB and more 0.4-0.65 / 0.4-0.84, 0.7-0.83 / 0.9-1.0; up to 8 KB 1.07-1.3 / 1.07-1.7 everywhere.
   const long long row = (long long)h_cur * w_cur * head_dim * (dtype == AMSKV_DTYPE_BF16 ? 2 : 4);
   const bool few = bh < (row >= 32 << 10 ? 512 : row >= 16 << 10 ? 256 : 0);
-  auto go = [&](auto f_many, auto f_few) {
-    return (few ? f_few : f_many)(cur, prev, bh, heads, h_cur, w_cur, h_prev, w_prev, partial_ws, st);
+  // Many (b,h) with few rows: a wave each, four to a workgroup; with four waves to a (b,h) the launch takes as long as its waves take to
+  // start.  A pass of the wave takes 1 KB: up to four of them, and as many (b,h) as make up for the longer chain.  us, keys and values and
+  // their totals, four waves / one, by bytes of scale s: 7680 (b,h) 512 23.2 / 11.8, 1152 24.8 / 15.2, 2048 26.4 / 17.9, 3200 30.9 / 29.8, 4608
+  // 40.5 / 40.8; 1920 (b,h) 9.7 / 6.3, 10.1 / 7.5, 10.2 / 7.8, 11.3 / 10.4, 13.4 / 12.5, 6272 15.6 / 15.8, 8192 17.2 / 18.7; 576 (b,h) 6.9 / 5.9,
+  // 7.0 / 6.4, 7.1 / 6.5, 7.4 / 7.9; 128 (b,h) 6.0 / 5.5, 6.1 / 6.3, 6.0 / 6.1, 6.1 / 7.6.
+  const bool waves = row <= 4096 && row <= 4ll * bh;
+  auto go = [&](auto f_many, auto f_few, auto f_waves) {
+    return (waves ? f_waves : few ? f_few : f_many)(cur, prev, bh, heads, h_cur, w_cur, h_prev, w_prev, partial_ws, st);
   };
   hipError_t e;
   if (dtype == AMSKV_DTYPE_BF16)
-    e = head_dim == 64 ? go(launch_partial<true, 8, 256>, launch_partial<true, 8, 1024>)
-                       : go(launch_partial<true, 16, 256>, launch_partial<true, 16, 1024>);
+    e = head_dim == 64 ? go(launch_partial<true, 8, 256>, launch_partial<true, 8, 1024>, launch_partial<true, 8, 64, 4>)
+                       : go(launch_partial<true, 16, 256>, launch_partial<true, 16, 1024>, launch_partial<true, 16, 64, 4>);
   else
-    e = head_dim == 64 ? go(launch_partial<false, 16, 256>, launch_partial<false, 16, 1024>)
-                       : go(launch_partial<false, 32, 256>, launch_partial<false, 32, 1024>);
+    e = head_dim == 64 ? go(launch_partial<false, 16, 256>, launch_partial<false, 16, 1024>, launch_partial<false, 16, 64, 4>)
+                       : go(launch_partial<false, 32, 256>, launch_partial<false, 32, 1024>, launch_partial<false, 32, 64, 4>);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(similarity_total_kernel, dim3(tensors * heads), dim3(64), 0, st, (const float*)partial_ws, batch,
                      heads, out_dev);
