@@ -63,7 +63,7 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
-// query-token count up to which the latency-oriented kernel of attend_bf16_small.hip is always used
+// query-token count up to which a wave of the latency-oriented kernel of attend_bf16_small.hip may own a (b,h)
 constexpr int kSmallTq = 32;
 // the online softmax lets the running max lag by up to this many powers of two before the
 // accumulators are rescaled; probabilities then stay below 2^kMaxLag, far inside fp32/bf16 range
@@ -975,29 +975,45 @@ Choice choose(int head_dim, int bh, int t_q, const SegTable& seg, const ExtKV& e
   const bool moves = moves_rows(seg, ext);
   const long long units = (long long)bh * ((t_q + 31) / 32);
   const int blocks = (seg.total + 31) / 32;
+  // Few queries.  A workgroup of the streaming kernel to a (b,h) has idle waves, but they fetch the keys, all at once and to addresses that
+  // the scalar unit finds: it is ahead of waves that walk alone wherever the chip takes all workgroups together (wide: 1 on a CU, 2 at
+  // head dim 64; narrow: 3 and 4).  us, by (b,h), the form that is taken else / this one.  Wide, head dim 64: 16 x 30 keys 16 4.3 / 3.7,
+  // 256 4.7 / 4.2, 512 5.1 / 5.0; 25 x 55 16 4.4 / 4.0, 256 5.1 / 4.7, 512 6.4 / 5.8; 25 x 75 256 5.8 / 5.6, 512 6.8 / 6.8; 25 x 209 256 7.1 / 7.7; 4 x 5
+  // 4.5 / 4.5.  Head dim 128: 4 x 5 64 5.6 / 5.2; 16 x 30 16 5.9 / 4.6, 128 6.4 / 5.0; 25 x 209 64 9.5 / 8.1, 256 11.7 / 11.3; 25 x 526 24.2 / 23.0; 32 x 722
+  // 23.9 / 25.3.  Narrow, head dim 64, 768: 9 x 22 5.2 / 5.2, 16 x 38 7.0 / 6.4, 25 x 209 17.4 / 14.6, 32 x 722 37.4 / 30.8; 1920 16 x 38 10.7 / 12.6.
+  // Head dim 128: 16 x 30 512 7.4 / 6.8, 8 x 13 6.2 / 6.3; 25 x 75 512 10.7 / 10.0, 768 14.8 / 12.3; 1920 16 x 38 17.9 / 23.3.
+  // A launch that moves cached rows needs one owner of them: one of these, or else a single wave (25 x 209 64 12.2 / 6.5).
+  const int fit_wide = head_dim == 64 ? 512 : 256, fit_narrow = head_dim == 64 ? 1024 : 768;
   if (t_q <= kSmallTq) {
-    // One wave per unit where the chip is full of them, else as many slices as leave every wave a few blocks.  A launch that
-    // moves cached rows needs one wave to fetch them all.  us, 1 / 4 / 8 slices, head dim 64, 25 queries: 16 units x 55 keys
-    // 6.4 / 5.2 / 5.4, 128 x 625 30.6 / 10.8 / 8.2, 512 x 625 30.4 / 15.8 / 16.0; one block 4.7 / 5.5 / 5.7.  Head dim 128,
-    // 16 queries: 32 units x 37 keys 8.9 / 6.5, 128 x 416 33.0 / 13.3.
+    if (bh <= fit_wide && (blocks == 1 ? bh <= 256 && (head_dim == 128 || seg.total > 8) : moves || blocks <= (head_dim == 64 ? 3 : 20)))
+      return {Shape::kWide, 1};
+    if (bh > fit_wide && bh <= fit_narrow && (blocks > 1 || (head_dim == 128 && bh <= 512 && seg.total > 16))) return {Shape::kNarrow, 1};
+    // One wave per unit where the chip is full of them, else as many slices as leave every wave a few blocks.  us, 1 / 4 / 8 slices, head
+    // dim 64, 25 queries: 128 units x 625 keys 30.6 / 10.8 / 8.2, 512 x 625 30.4 / 15.8 / 16.0.  Head dim 128, 16 queries: 128 x 416 33.0 / 13.3.
     if (moves || blocks < 2 || units > 512) return {Shape::kStreams, 1};
-    return {Shape::kStreams, head_dim == 128 || blocks == 2 || units > 256 ? 4 : 8};
+    return {Shape::kStreams, head_dim == 128 || units > 256 ? 4 : 8};
   }
   // More queries, few units, head dim 64: 16 (b,h), 256 x 680 12.1 (split workgroups) -> 9.2 us, 64 units of 100 x 255 7.4 ->
-  // 6.2, 256 units of 256 x 680 12.3 -> 9.5; 512 units 12.6 -> 14.3.  (Head dim 128: four slices never won by 5 %.)
-  if (head_dim == 64 && !moves && units <= 256) return {Shape::kStreams, 8};
+  // 6.2, 256 units of 256 x 680 12.3 -> 9.5; 512 units 12.6 -> 14.3.  (Head dim 128: four slices never won by 5 %.)  With up to three blocks
+  // there is nothing to share: 36 x 91 5.2 / 4.9 wide, 49 x 50 5.9 / 5.0; 64 x 155 5.6 / 5.7, 100 x 184 6.2 / 6.6.
+  if (head_dim == 64 && !moves && units <= 256 && blocks > 3) return {Shape::kStreams, 8};
   const long long n128 = (long long)bh * ((t_q + 127) / 128), n256 = (long long)bh * ((t_q + 255) / 256);
   if (head_dim == 128) {
+    // Up to 128 queries: four waves of a wide workgroup fetch only.  us, 100 x 184 keys 24 (b,h) 9.1 (split) / 8.3, 256 14.5 / 13.3; 36 x 91 16
+    // (b,h) 7.0 / 6.3; 100 x 690 24 (b,h) 15.9 / 16.6, 64 17.4 / 17.6, 192 26.0 / 24.7, 256 30.4 / 29.0.
+    if (t_q <= 128 && bh <= fit_wide && (blocks <= 12 || bh > 128)) return {Shape::kWide, 1};
     static const Cost narrow[] = {{0.83, 3}, {1.05, 5}, {1.35, 7}}, three{1.40, 6}, wide{0.88, 6}, split{0.53, 4};
     const double tn = rounds(n128, 3, blocks, three, narrow), ts = rounds(n128, 1, blocks, split, &split);
     const double tw = t_q > 128 ? rounds(n256, 1, blocks, wide, &wide) : 1e30;
     return {fmin(ts, tw) >= 0.97 * tn ? Shape::kNarrow : ts <= tw ? Shape::kSplit : Shape::kWide, 1};
   }
   // Head dim 64 at up to 256 queries lives from reading K~ and V~ once, and a launch that moves cached rows relies on it
-  // (attend_owns_unit); beyond 256 workgroups of the split kind a CU has waves enough (512 of them: 100 queries x 255
-  // keys 12.9 -> 12.6, 64 x 119 7.5 -> 8.1, 169 x 424 13.0 -> 15.0 us; 256 of them: 9.8 -> 8.0, 6.5 -> 5.9, 11.8 -> 10.0).
-  if (n128 <= 256 && (t_q <= 128 || !moves)) return {Shape::kSplit, 1};
-  return {t_q > 128 ? Shape::kWide : Shape::kNarrow, 1};
+  // (attend_owns_unit).  Up to 128 queries: wide while about three halves of a workgroup fall to a CU (us, narrow / wide: 384 (b,h) 100 x 184 12.4 / 11.6, 100
+  // x 690 25.2 / 24.1; 512 13.5 / 13.0, 64 x 155 11.5 / 12.1, 100 x 255 16.3 / 17.0; 768 17.8 / 19.1.  Split: 256 100 x 184 9.3 / 8.7, 100 x 690 17.4 / 16.0).
+  // More of them: up to 256 workgroups of the split kind, beyond which a CU has waves enough (512 of them: 169 x 424 13.0 -> 15.0 us; 256 of
+  // them: 11.8 -> 10.0).
+  if (t_q <= 128) return {bh <= 384 ? Shape::kWide : Shape::kNarrow, 1};
+  return {n128 <= 256 && !moves ? Shape::kSplit : Shape::kWide, 1};
 }
 
 }  // namespace
