@@ -299,7 +299,10 @@ struct Flag {
 // The work of one workgroup.  kDensity: also leave, per 32-row query block, the softmax mass that lands on each
 // group of keys (Section 4.1's attention density as a by-product of the step's own attention; `groups` holds the
 // first virtual row past each group, `partial` one float per (b, h, query block, group)).
-template <int D, int NQ, int kWaves, int kTileKeys, bool kDensity, int kSplit>
+// kRounded: O is divided by the sum of the probabilities as the second product has them, rounded to bf16, like in the kernel of
+// attend_bf16_small.hip whose launches of few queries these are: with few keys the roundings of the two cancel in part (rel against 64 bits, 4 x
+// 5 keys at head dim 128 1.70e-3, by the unrounded sum 1.79e-3; 25 x 55 1.68 and 1.71; from 200 keys on the same).
+template <int D, int NQ, int kWaves, int kTileKeys, bool kDensity, int kSplit, bool kRounded>
 __device__ __forceinline__ void attend_unit(
     const __bf16* __restrict__ q, __bf16* __restrict__ o, char* __restrict__ kc, char* __restrict__ vc,
     int t_q, long long cap_tokens, const SegTable& seg, const ExtKV& ext_kv, const CallerIo& io, float scale_log2e, int n_bh,
@@ -327,7 +330,9 @@ __device__ __forceinline__ void attend_unit(
   // 128, where the eight-wave shapes have them: two waves per SIMD).  Not in the narrow shape, whose one-block tiles would need
   // a fifth ring slot: it keeps the plain loop, one block at a time, the tile barrier in front of a tile's first block.
   constexpr bool kPrefetchK = (D == 64 || kWaves == 8) && kBlocksPerTile == 2;
-  static_assert(kSplit == 1 || (kSplit == 2 && kPrefetchK && NQ == 1), "a split workgroup deals the two blocks of a tile");
+  static_assert(kSplit == 1 || (kSplit == 2 && kPrefetchK && NQ == 1 && !kRounded), "a split workgroup deals the two blocks of a tile");
+  // the sum of the probabilities as they are is needed: for O, or for the groups
+  constexpr bool kSumPlain = !kRounded || kDensity;
 
   __shared__ __align__(1024) char lds_k[kRing];
   __shared__ __align__(1024) char lds_v[kRing];
@@ -467,6 +472,7 @@ __device__ __forceinline__ void attend_unit(
 #pragma unroll
       for (int v = 0; v < 16; ++v) oacc[n][d][v] = 0.f;
   float run_mc[NQ], run_sum[NQ];  // softmax reference times c = softmax scale * log2(e); sum of 2^(s*c - reference)
+  float run_plain[NQ];            // kRounded and density: the same of the probabilities as they are
   // density: this lane's sum over the keys of the group being walked, the group, its end, the block's first row
   float seg_acc[NQ];
   int cur_group = 0, next_end = kDensity ? groups.end[0] : 0, blk_start = 32 * slice;
@@ -474,7 +480,7 @@ __device__ __forceinline__ void attend_unit(
 #pragma unroll
   for (int n = 0; n < NQ; ++n) {
     run_mc[n] = -INFINITY;
-    run_sum[n] = 0.f;
+    run_sum[n] = run_plain[n] = 0.f;
     seg_acc[n] = 0.f;
 #pragma unroll
     for (int u = 0; u < 2; ++u)
@@ -576,9 +582,10 @@ __device__ __forceinline__ void attend_unit(
     // far inside the range of fp32 and bf16, and the block costs no maximum at all.
     // The first block of a unit has no reference yet and nothing to multiply (pf = 0): it goes straight to the
     // path that takes the maximum.
-    float sum[NQ][2];
+    const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
+    float sum[NQ][2], rounded[NQ];
 #pragma unroll
-    for (int n = 0; n < NQ; ++n) sum[n][0] = sum[n][1] = 0.f;
+    for (int n = 0; n < NQ; ++n) sum[n][0] = sum[n][1] = rounded[n] = 0.f;
     const bool first = first_block;
     first_block = false;
     bool trip = true;
@@ -602,10 +609,14 @@ __device__ __forceinline__ void attend_unit(
           for (int v = 8 * u; v < 8 * u + 8; v += 2) {
             const float p0 = __builtin_amdgcn_exp2f(fmaf(sacc[n][v], scale_log2e, -run_mc[n]));
             const float p1 = __builtin_amdgcn_exp2f(fmaf(sacc[n][v + 1], scale_log2e, -run_mc[n]));
-            sum[n][0] += p0;
-            sum[n][1] += p1;
-            pf[n][u][v & 7] = (__bf16)p0;
-            pf[n][u][(v & 7) + 1] = (__bf16)p1;
+            if constexpr (kSumPlain) {
+              sum[n][0] += p0;
+              sum[n][1] += p1;
+            }
+            const bf16x2 pk = {(__bf16)p0, (__bf16)p1};
+            if constexpr (kRounded) rounded[n] = __builtin_amdgcn_fdot2_f32_bf16(pk, ones, rounded[n], false);
+            pf[n][u][v & 7] = pk[0];
+            pf[n][u][(v & 7) + 1] = pk[1];
             if constexpr (kDensity) {  // kept for the groups that end in this block
               sacc[n][v] = p0;
               sacc[n][v + 1] = p1;
@@ -617,8 +628,8 @@ __device__ __forceinline__ void attend_unit(
       trip = false;
 #pragma unroll
       for (int n = 0; n < NQ; ++n) {
-        sum[n][0] += sum[n][1];
-        trip |= __builtin_amdgcn_ballot_w64(!(sum[n][0] <= kTripSum)) != 0;
+        if constexpr (kSumPlain) sum[n][0] += sum[n][1];
+        trip |= __builtin_amdgcn_ballot_w64(!((kRounded ? rounded[n] : sum[n][0]) <= kTripSum)) != 0;
       }
     }
     any_rescale = trip && !first;  // the first block leaves zeros in the accumulators: nothing to rescale
@@ -656,6 +667,7 @@ __device__ __forceinline__ void attend_unit(
         const float new_mc = full - run_mc[n] > kMaxLag ? full : run_mc[n];
         alpha[n] = __builtin_amdgcn_exp2f(run_mc[n] - new_mc);  // 1 when unchanged, 0 on the first block
         run_sum[n] *= alpha[n];
+        run_plain[n] *= alpha[n];
         if constexpr (kDensity) {  // what was summed against the old reference moves with it
           seg_acc[n] *= alpha[n];
           if (h == 0)
@@ -663,14 +675,17 @@ __device__ __forceinline__ void attend_unit(
         }
         run_mc[n] = new_mc;
         float s0 = 0.f, s1 = 0.f;
+        rounded[n] = 0.f;
 #pragma unroll
         for (int v = 0; v < 16; v += 2) {
           const float p0 = __builtin_amdgcn_exp2f(fmaf(sacc[n][v], scale_log2e, -new_mc));
           const float p1 = __builtin_amdgcn_exp2f(fmaf(sacc[n][v + 1], scale_log2e, -new_mc));
           s0 += p0;
           s1 += p1;
-          pf[n][v >> 3][v & 7] = (__bf16)p0;
-          pf[n][v >> 3][(v & 7) + 1] = (__bf16)p1;
+          const bf16x2 pk = {(__bf16)p0, (__bf16)p1};
+          if constexpr (kRounded) rounded[n] = __builtin_amdgcn_fdot2_f32_bf16(pk, ones, rounded[n], false);
+          pf[n][v >> 3][v & 7] = pk[0];
+          pf[n][v >> 3][(v & 7) + 1] = pk[1];
           if constexpr (kDensity) {
             sacc[n][v] = p0;
             sacc[n][v + 1] = p1;
@@ -717,7 +732,10 @@ __device__ __forceinline__ void attend_unit(
       blk_start += 32 * kSplit;
     }
 #pragma unroll
-    for (int n = 0; n < NQ; ++n) run_sum[n] += sum[n][0];
+    for (int n = 0; n < NQ; ++n) {
+      run_sum[n] += kRounded ? rounded[n] : sum[n][0];
+      if (kRounded && kDensity) run_plain[n] += sum[n][0];
+    }
     off_prev = off_cur;
     off_cur = off_next;
     if constexpr (kSplit == 1) {
@@ -846,7 +864,7 @@ __device__ __forceinline__ void attend_unit(
 #pragma unroll
   for (int n = 0; n < NQ; ++n) {
     const float total = kSplit > 1 ? run_sum[n] : run_sum[n] + __shfl_xor(run_sum[n], 32, 64);
-    const float inv = 1.0f / total;
+    const float inv = 1.0f / total, inv_mass = kRounded && kDensity ? 1.0f / half_sum(run_plain[n]) : inv;
     const int row = q_base + 32 * n + r;
     // The lane halves hold alternate 8-byte pieces of a row (columns 8g + 4h ..); one lane swap per register
     // pairs them up, so that every lane stores 16 bytes and the two lanes of a row 32 contiguous bytes (half as
@@ -876,30 +894,30 @@ __device__ __forceinline__ void attend_unit(
         const int p = p0 + h, at = min(p, groups.n - 1);
         float gsum = park[wave * NQ + n][at][r];
         if (kSplit > 1) gsum = fmaf(w_theirs, park[other][at][r], w_mine * gsum);
-        const float m = group_sum<32>(row < t_q ? gsum * inv : 0.f);  // over the 32 query rows
+        const float m = group_sum<32>(row < t_q ? gsum * inv_mass : 0.f);  // over the 32 query rows
         if (r == 0 && p < groups.n) partial[qblk * AMSKV_MAX_SCALES + p] = m;
       }
     }
   }
 }
 
-template <int D, int NQ, int kWaves, int kTileKeys, int kMinWavesPerSimd, int kSplit>
+template <int D, int NQ, int kWaves, int kTileKeys, int kMinWavesPerSimd, int kSplit, bool kRounded>
 __global__ __launch_bounds__(64 * kWaves, kMinWavesPerSimd) void attend_bf16_kernel(
     const __bf16* __restrict__ q, __bf16* __restrict__ o, char* __restrict__ kc, char* __restrict__ vc,
     int t_q, long long cap_tokens, SegTable seg, ExtKV ext_kv, CallerIo io, float scale_log2e, int n_bh, int n_qtiles, int n_whole) {
   fetch_arguments<kAttentionArguments>();
-  attend_unit<D, NQ, kWaves, kTileKeys, false, kSplit>(q, o, kc, vc, t_q, cap_tokens, seg, chosen(ext_kv), io, scale_log2e, n_bh,
+  attend_unit<D, NQ, kWaves, kTileKeys, false, kSplit, kRounded>(q, o, kc, vc, t_q, cap_tokens, seg, chosen(ext_kv), io, scale_log2e, n_bh,
                                                n_qtiles, n_whole, GroupEnds{}, nullptr);
 }
 
 // The same step with the attention density of its own queries as a by-product (no second pass over Q and K).
-template <int D, int NQ, int kWaves, int kTileKeys, int kMinWavesPerSimd, int kSplit = 1>
+template <int D, int NQ, int kWaves, int kTileKeys, int kMinWavesPerSimd, int kSplit, bool kRounded>
 __global__ __launch_bounds__(64 * kWaves, kMinWavesPerSimd) void attend_density_bf16_kernel(
     const __bf16* __restrict__ q, __bf16* __restrict__ o, char* __restrict__ kc, char* __restrict__ vc,
     int t_q, long long cap_tokens, SegTable seg, ExtKV ext_kv, CallerIo io, float scale_log2e, int n_bh, int n_qtiles, int n_whole,
     GroupEnds groups, float* __restrict__ partial) {
   fetch_arguments<kAttentionArguments>();
-  attend_unit<D, NQ, kWaves, kTileKeys, true, kSplit>(q, o, kc, vc, t_q, cap_tokens, seg, chosen(ext_kv), io, scale_log2e, n_bh,
+  attend_unit<D, NQ, kWaves, kTileKeys, true, kSplit, kRounded>(q, o, kc, vc, t_q, cap_tokens, seg, chosen(ext_kv), io, scale_log2e, n_bh,
                                               n_qtiles, n_whole, groups, partial);
 }
 
@@ -910,7 +928,10 @@ hipError_t launch(const void* q, void* o, void* kc, void* vc, int bh, int t_q, i
   const int n_qtiles = (t_q + BM - 1) / BM;
   const int n_whole = whole_units(bh, n_qtiles, kMostWhole);
   dim3 grid(placed_grid(bh, n_qtiles, n_whole)), block(64 * kWaves);
-  hipLaunchKernelGGL((attend_bf16_kernel<D, NQ, kWaves, kTileKeys, kMinWavesPerSimd, kSplit>), grid, block, 0, st,
+  auto kernel = attend_bf16_kernel<D, NQ, kWaves, kTileKeys, kMinWavesPerSimd, kSplit, false>;
+  if constexpr (kSplit == 1)
+    if (t_q <= kSmallTq) kernel = attend_bf16_kernel<D, NQ, kWaves, kTileKeys, kMinWavesPerSimd, kSplit, true>;
+  hipLaunchKernelGGL(kernel, grid, block, 0, st,
                      (const __bf16*)q, (__bf16*)o, (char*)kc, (char*)vc, t_q, (long long)cap_tokens, seg, ext, io, c,
                      bh, n_qtiles, n_whole);
   return hipGetLastError();
@@ -924,7 +945,10 @@ hipError_t launch_density_variant(const void* q, void* o, void* kc, void* vc, in
   const int n_qtiles = (t_q + BM - 1) / BM;
   const int n_whole = whole_units(bh, n_qtiles, kMostWhole);
   dim3 grid(placed_grid(bh, n_qtiles, n_whole)), block(64 * kWaves);
-  hipLaunchKernelGGL((attend_density_bf16_kernel<D, NQ, kWaves, kTileKeys, kMinWavesPerSimd, kSplit>), grid, block, 0, st,
+  auto kernel = attend_density_bf16_kernel<D, NQ, kWaves, kTileKeys, kMinWavesPerSimd, kSplit, false>;
+  if constexpr (kSplit == 1)
+    if (t_q <= kSmallTq) kernel = attend_density_bf16_kernel<D, NQ, kWaves, kTileKeys, kMinWavesPerSimd, kSplit, true>;
+  hipLaunchKernelGGL(kernel, grid, block, 0, st,
                      (const __bf16*)q, (__bf16*)o, (char*)kc, (char*)vc, t_q, (long long)cap_tokens, seg, ext, io, c,
                      bh, n_qtiles, n_whole, groups, partial);
   return hipGetLastError();
