@@ -301,7 +301,8 @@ struct Flag {
 // first virtual row past each group, `partial` one float per (b, h, query block, group)).
 // kRounded: O is divided by the sum of the probabilities as the second product has them, rounded to bf16, like in the kernel of
 // attend_bf16_small.hip whose launches of few queries these are: with few keys the roundings of the two cancel in part (rel against 64 bits, 4 x
-// 5 keys at head dim 128 1.70e-3, by the unrounded sum 1.79e-3; 25 x 55 1.68 and 1.71; from 200 keys on the same).
+// 5 keys at head dim 128 1.70e-3, by the unrounded sum 1.79e-3; 25 x 55 1.68 and 1.71; from 200 keys on the same).  And the reference is
+// the maximum so far, not a lagging one: the largest weight is 1 then, which bf16 has.
 template <int D, int NQ, int kWaves, int kTileKeys, bool kDensity, int kSplit, bool kRounded>
 __device__ __forceinline__ void attend_unit(
     const __bf16* __restrict__ q, __bf16* __restrict__ o, char* __restrict__ kc, char* __restrict__ vc,
@@ -629,7 +630,7 @@ __device__ __forceinline__ void attend_unit(
 #pragma unroll
       for (int n = 0; n < NQ; ++n) {
         if constexpr (kSumPlain) sum[n][0] += sum[n][1];
-        trip |= __builtin_amdgcn_ballot_w64(!((kRounded ? rounded[n] : sum[n][0]) <= kTripSum)) != 0;
+        trip |= __builtin_amdgcn_ballot_w64(!((kRounded ? rounded[n] : sum[n][0]) <= (kRounded ? 1.0f : kTripSum))) != 0;
       }
     }
     any_rescale = trip && !first;  // the first block leaves zeros in the accumulators: nothing to rescale
@@ -664,7 +665,7 @@ __device__ __forceinline__ void attend_unit(
         const float a4 = max3(sacc[n][12], sacc[n][13], sacc[n][14]);
         const float b0 = max3(a0, a1, a2), b1 = max3(a3, a4, sacc[n][15]);
         const float full = half_max(max3(b0, b1, b1)) * scale_log2e;  // finite: key 0 of the block is valid for every query
-        const float new_mc = full - run_mc[n] > kMaxLag ? full : run_mc[n];
+        const float new_mc = full - run_mc[n] > (kRounded ? 0.f : kMaxLag) ? full : run_mc[n];
         alpha[n] = __builtin_amdgcn_exp2f(run_mc[n] - new_mc);  // 1 when unchanged, 0 on the first block
         run_sum[n] *= alpha[n];
         run_plain[n] *= alpha[n];
@@ -1002,7 +1003,7 @@ Choice choose(int head_dim, int bh, int t_q, const SegTable& seg, const ExtKV& e
   // Few queries.  A workgroup of the streaming kernel to a (b,h) has idle waves, but they fetch the keys, all at once and to addresses that
   // the scalar unit finds: it is ahead of waves that walk alone wherever the chip takes all workgroups together (wide: 1 on a CU, 2 at
   // head dim 64; narrow: 3 and 4).  us, by (b,h), the form that is taken else / this one.  Wide, head dim 64: 16 x 30 keys 16 4.3 / 3.7,
-  // 256 4.7 / 4.2, 512 5.1 / 5.0; 25 x 55 16 4.4 / 4.0, 256 5.1 / 4.7, 512 6.4 / 5.8; 25 x 75 256 5.8 / 5.6, 512 6.8 / 6.8; 25 x 209 256 7.1 / 7.7; 4 x 5
+  // 256 4.7 / 4.2, 512 5.1 / 5.0; 25 x 55 16 4.4 / 4.2, 256 5.2 / 5.1, 512 6.5 / 6.2; 25 x 75 256 5.8 / 5.6, 512 6.8 / 6.8; 25 x 209 256 7.1 / 7.7; 4 x 5
   // 4.5 / 4.5.  Head dim 128: 4 x 5 64 5.6 / 5.2; 16 x 30 16 5.9 / 4.6, 128 6.4 / 5.0; 25 x 209 64 9.5 / 8.1, 256 11.7 / 11.3; 25 x 526 24.2 / 23.0; 32 x 722
   // 23.9 / 25.3.  Narrow, head dim 64, 768: 9 x 22 5.2 / 5.2, 16 x 38 7.0 / 6.4, 25 x 209 17.4 / 14.6, 32 x 722 37.4 / 30.8; 1920 16 x 38 10.7 / 12.6.
   // Head dim 128: 16 x 30 512 7.4 / 6.8, 8 x 13 6.2 / 6.3; 25 x 75 512 10.7 / 10.0, 768 14.8 / 12.3; 1920 16 x 38 17.9 / 23.3.
