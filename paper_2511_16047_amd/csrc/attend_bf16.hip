@@ -1020,26 +1020,26 @@ Choice choose(int head_dim, int bh, int t_q, const SegTable& seg, const ExtKV& e
     return {Shape::kStreams, head_dim == 128 || units > 256 ? 4 : 8};
   }
   // More queries, few units, head dim 64: 16 (b,h), 256 x 680 12.1 (split workgroups) -> 9.2 us, 64 units of 100 x 255 7.4 ->
-  // 6.2, 256 units of 256 x 680 12.3 -> 9.5; 512 units 12.6 -> 14.3.  (Head dim 128: four slices never won by 5 %.)  With up to three blocks
-  // there is nothing to share: 36 x 91 5.2 / 4.9 wide, 49 x 50 5.9 / 5.0; 64 x 155 5.6 / 5.7, 100 x 184 6.2 / 6.6.
-  if (head_dim == 64 && !moves && units <= 256 && blocks > 3) return {Shape::kStreams, 8};
+  // 6.2, 256 units of 256 x 680 12.3 -> 9.5; 512 units 12.6 -> 14.3.  (Head dim 128: four slices never won by 5 %.)  Also where a slice has one block or none:
+  // wide is 0.3 to 0.9 us ahead of slices up to three blocks, and up to 0.7 of split at 100 x 184, but with one reference for all keys its error
+  // is the larger one (16 (b,h), 36 x 91 rel 2.23e-3 instead of 2.04e-3, 49 x 50 2.16 / 2.03; split, 256 (b,h), 100 x 184 2.30 / 2.24).
+  if (head_dim == 64 && !moves && units <= 256) return {Shape::kStreams, 8};
   const long long n128 = (long long)bh * ((t_q + 127) / 128), n256 = (long long)bh * ((t_q + 255) / 256);
   if (head_dim == 128) {
-    // Up to 128 queries: four waves of a wide workgroup fetch only.  us, 100 x 184 keys 24 (b,h) 9.1 (split) / 8.3, 256 14.5 / 13.3; 36 x 91 16
-    // (b,h) 7.0 / 6.3; 100 x 690 24 (b,h) 15.9 / 16.6, 64 17.4 / 17.6, 192 26.0 / 24.7, 256 30.4 / 29.0.
-    if (t_q <= 128 && bh <= fit_wide && (blocks <= 12 || bh > 128)) return {Shape::kWide, 1};
     static const Cost narrow[] = {{0.83, 3}, {1.05, 5}, {1.35, 7}}, three{1.40, 6}, wide{0.88, 6}, split{0.53, 4};
     const double tn = rounds(n128, 3, blocks, three, narrow), ts = rounds(n128, 1, blocks, split, &split);
     const double tw = t_q > 128 ? rounds(n256, 1, blocks, wide, &wide) : 1e30;
-    return {fmin(ts, tw) >= 0.97 * tn ? Shape::kNarrow : ts <= tw ? Shape::kSplit : Shape::kWide, 1};
+    // (up to 128 queries the same O comes from wide workgroups, half of whose waves fetch only, where they all fit: 36 x 91, 16 (b,h) 7.0 / 6.3 us)
+    if (fmin(ts, tw) >= 0.97 * tn) return {t_q <= 128 && bh <= fit_wide ? Shape::kWide : Shape::kNarrow, 1};
+    return {ts <= tw ? Shape::kSplit : Shape::kWide, 1};
   }
   // Head dim 64 at up to 256 queries lives from reading K~ and V~ once, and a launch that moves cached rows relies on it
-  // (attend_owns_unit).  Up to 128 queries: wide while about three halves of a workgroup fall to a CU (us, narrow / wide: 384 (b,h) 100 x 184 12.4 / 11.6, 100
-  // x 690 25.2 / 24.1; 512 13.5 / 13.0, 64 x 155 11.5 / 12.1, 100 x 255 16.3 / 17.0; 768 17.8 / 19.1.  Split: 256 100 x 184 9.3 / 8.7, 100 x 690 17.4 / 16.0).
-  // More of them: up to 256 workgroups of the split kind, beyond which a CU has waves enough (512 of them: 169 x 424 13.0 -> 15.0 us; 256 of
-  // them: 11.8 -> 10.0).
-  if (t_q <= 128) return {bh <= 384 ? Shape::kWide : Shape::kNarrow, 1};
-  return {n128 <= 256 && !moves ? Shape::kSplit : Shape::kWide, 1};
+  // (attend_owns_unit); beyond 256 workgroups of the split kind a CU has waves enough (512 of them: 100 queries x 255
+  // keys 12.9 -> 12.6, 64 x 119 7.5 -> 8.1, 169 x 424 13.0 -> 15.0 us; 256 of them: 9.8 -> 8.0, 6.5 -> 5.9, 11.8 -> 10.0).  Wide up to 128
+  // queries, with the O of narrow, while three halves of a workgroup fall to a CU (us, narrow / wide: 384 (b,h) 100 x 184 12.4 / 11.6, 100 x 690
+  // 25.2 / 24.1; 512 13.5 / 13.0, 64 x 155 11.5 / 12.1, 100 x 255 16.3 / 17.0; 768 17.8 / 19.1).
+  if (n128 <= 256 && (t_q <= 128 || !moves)) return {Shape::kSplit, 1};
+  return {t_q > 128 || bh <= 384 ? Shape::kWide : Shape::kNarrow, 1};
 }
 
 }  // namespace
