@@ -1001,23 +1001,24 @@ Choice choose(int head_dim, int bh, int t_q, const SegTable& seg, const ExtKV& e
   const long long units = (long long)bh * ((t_q + 31) / 32);
   const int blocks = (seg.total + 31) / 32;
   // Few queries.  A workgroup of the streaming kernel to a (b,h) has idle waves, but they fetch the keys, all at once and to addresses that
-  // the scalar unit finds: it is ahead of waves that walk alone wherever the chip takes all workgroups together (wide: 1 on a CU, 2 at
-  // head dim 64; narrow: 3 and 4), and of slices of one or two key blocks.  us, by (b,h), the form that is taken else / this one.  Wide, head
-  // dim 64: 16 x 30 keys 16 4.3 / 3.8, 256 4.8 / 4.4; 16 x 38 256 5.1 / 5.0, 512 5.9 / 5.6; 25 x 55 512 6.5 / 6.2; 25 x 75 256 5.8 / 6.1, 512 6.7 / 7.2; 4 x 5
-  // 4.5 / 4.5.  Head dim 128: 4 x 5 64 5.6 / 5.1; 9 x 22 64 6.1 / 5.1, 256 6.3 / 5.3; 16 x 38 64 6.1 / 5.7, 256 6.5 / 6.2; 25 x 75 64 6.7 / 7.2.  Narrow, head
-  // dim 64, 768: 9 x 22 5.2 / 5.2, 16 x 38 6.9 / 6.8, 25 x 75 9.2 / 8.8, 25 x 209 17.3 / 15.4, 32 x 722 36.5 / 32.6; 1920 16 x 38 10.7 / 12.6.  Head
-  // dim 128: 9 x 22 512 6.6 / 6.1, 8 x 13 6.2 / 6.4; 25 x 75 512 10.6 / 10.6, 768 14.7 / 13.0; 25 x 209 512 20.0 / 20.9, 768 28.8 / 27.6; 1920 16 x 38 17.9 / 23.3.
+  // the scalar unit finds: it is ahead of a wave that walks alone, whose arithmetic it has, wherever the chip takes all workgroups together
+  // (wide: 1 on a CU, 2 at head dim 64; narrow: 3 and 4).  us, by (b,h), single waves / this form.  Wide, head dim 64: 16 x 30 keys 16 4.3 / 3.8, 256
+  // 4.8 / 4.4; 4 x 5 4.5 / 4.5.  Head dim 128: 4 x 5 64 5.6 / 5.1; 9 x 22 64 6.1 / 5.1, 256 6.3 / 5.3.  Narrow, head dim 64, 768: 9 x 22 5.2 / 5.2, 16 x
+  // 38 6.9 / 6.8, 25 x 75 9.2 / 8.8, 25 x 209 17.3 / 15.4, 32 x 722 36.5 / 32.6; 1920 16 x 38 10.7 / 12.6.  Head dim 128: 9 x 22 512 6.6 / 6.1, 8 x 13 6.2 /
+  // 6.4; 25 x 75 768 14.7 / 13.0; 25 x 209 768 28.8 / 27.6; 1920 16 x 38 17.9 / 23.3.
   // A launch that moves cached rows needs one owner of them: one of these, or else a single wave (25 x 209 256 13.5 / 9.0, head dim 128 512
   // 24.5 / 20.9).
   const int fit_wide = head_dim == 64 ? 512 : 256, fit_narrow = head_dim == 64 ? 1024 : 768;
   if (t_q <= kSmallTq) {
-    if (bh <= fit_wide && (blocks == 1 ? bh <= 256 && (head_dim == 128 || seg.total > 8) : moves || blocks == 2)) return {Shape::kWide, 1};
+    if (bh <= fit_wide && (blocks == 1 ? bh <= 256 && (head_dim == 128 || seg.total > 8) : moves)) return {Shape::kWide, 1};
     if (bh > fit_wide && bh <= fit_narrow && (blocks > 1 ? moves || bh > 512 : head_dim == 128 && bh <= 512 && seg.total > 16))
       return {Shape::kNarrow, 1};
     // One wave per unit where the chip is full of them, else as many slices as leave every wave a few blocks.  us, 1 / 4 / 8 slices, head
-    // dim 64, 25 queries: 128 units x 625 keys 30.6 / 10.8 / 8.2, 512 x 625 30.4 / 15.8 / 16.0.  Head dim 128, 16 queries: 128 x 416 33.0 / 13.3.
+    // dim 64, 25 queries: 16 units x 55 keys 6.4 / 5.2 / 5.4, 128 x 625 30.6 / 10.8 / 8.2, 512 x 625 30.4 / 15.8 / 16.0.  Head dim 128, 16 queries: 32 x
+    // 37 8.9 / 6.5, 128 x 416 33.0 / 13.3.  (Wide is 0.1 to 0.4 us ahead of four slices where they have one block each or none, 256 (b,h), 16 x 38
+    // 5.1 / 5.0, but has one reference for all keys and the larger error: 2.04e-3 instead of 2.01e-3.)
     if (moves || blocks < 2 || units > 512) return {Shape::kStreams, 1};
-    return {Shape::kStreams, head_dim == 128 || units > 256 ? 4 : 8};
+    return {Shape::kStreams, head_dim == 128 || blocks == 2 || units > 256 ? 4 : 8};
   }
   // More queries, few units, head dim 64: 16 (b,h), 256 x 680 12.1 (split workgroups) -> 9.2 us, 64 units of 100 x 255 7.4 ->
   // 6.2, 256 units of 256 x 680 12.3 -> 9.5; 512 units 12.6 -> 14.3.  (Head dim 128: four slices never won by 5 %.)  Also where a slice has one block or none:

@@ -13,6 +13,7 @@ pytestmark = pytest.mark.gpu
 # head dim, queries, keys before them, waves that share the keys, are the weights summed as rounded?, counts of (b,h) that take this form
 FORMS = [(64, 36, 55, 8, False, (16, 128)), (64, 36, 55, 2, False, (129, 256)), (64, 49, 1, 8, False, (16, 128)), (64, 49, 1, 2, False, (256,)),
          (64, 64, 91, 2, False, (256,)), (64, 100, 84, 8, False, (16, 64)), (64, 100, 84, 2, False, (128, 256)),
+         (64, 16, 22, 4, True, (16, 512)), (64, 25, 30, 4, True, (16, 256, 512)), (128, 16, 22, 4, True, (16, 256)), (128, 25, 30, 4, True, (16, 256)),
          (128, 64, 91, 2, False, (16, 256)), (128, 100, 84, 2, False, (16, 128, 256))]
 
 
