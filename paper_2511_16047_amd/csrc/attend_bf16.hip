@@ -28,7 +28,8 @@
 // when the sum of a lane's new probabilities shows that some score lay far above it (more than
 // 2^kMaxLag times) is the block's maximum taken, the reference moved and the block redone; the
 // accumulator rescale this requires is applied one step later.  The common block takes no maximum.  A unit's
-// first block, which has no reference and nothing to multiply yet, goes straight to the maximum path.
+// first block, which has no reference and nothing to multiply yet, goes straight to the maximum path.  Launches of up to 32
+// queries take the maximum of every block instead (kRounded below).
 //
 // Split form (few units): workgroup of eight waves over 128 query rows and 64-key tiles; waves w and w + 4 hold the same
 // rows and take one of the two blocks of every tile each, with statistics of their own, so a SIMD that would have had one
@@ -299,10 +300,11 @@ struct Flag {
 // The work of one workgroup.  kDensity: also leave, per 32-row query block, the softmax mass that lands on each
 // group of keys (Section 4.1's attention density as a by-product of the step's own attention; `groups` holds the
 // first virtual row past each group, `partial` one float per (b, h, query block, group)).
-// kRounded: O is divided by the sum of the probabilities as the second product has them, rounded to bf16, like in the kernel of
-// attend_bf16_small.hip whose launches of few queries these are: with few keys the roundings of the two cancel in part (rel against 64 bits, 4 x
-// 5 keys at head dim 128 1.70e-3, by the unrounded sum 1.79e-3; 25 x 55 1.68 and 1.71; from 200 keys on the same).  And the reference is
-// the maximum so far, not a lagging one: the largest weight is 1 then, which bf16 has.
+// kRounded: the arithmetic of a single wave of attend_bf16_small.hip, in its order, so that O has the same bits.  The reference is the maximum so far,
+// not a lagging one: the largest weight is 1 then, which bf16 has.  And O is divided by the sum of the probabilities as the second product
+// has them, rounded to bf16: with few keys the roundings of the two cancel in part (rel against 64 bits, 4 x 5 keys at head dim 128 1.70e-3,
+// by the unrounded sum 1.79e-3; from 200 keys on the same).  Sixteen weights of a lane sum to several, so the maximum is looked for in every block
+// and not behind a look at the sum.
 template <int D, int NQ, int kWaves, int kTileKeys, bool kDensity, int kSplit, bool kRounded>
 __device__ __forceinline__ void attend_unit(
     const __bf16* __restrict__ q, __bf16* __restrict__ o, char* __restrict__ kc, char* __restrict__ vc,
@@ -331,9 +333,8 @@ __device__ __forceinline__ void attend_unit(
   // 128, where the eight-wave shapes have them: two waves per SIMD).  Not in the narrow shape, whose one-block tiles would need
   // a fifth ring slot: it keeps the plain loop, one block at a time, the tile barrier in front of a tile's first block.
   constexpr bool kPrefetchK = (D == 64 || kWaves == 8) && kBlocksPerTile == 2;
-  static_assert(kSplit == 1 || (kSplit == 2 && kPrefetchK && NQ == 1 && !kRounded), "a split workgroup deals the two blocks of a tile");
-  // the sum of the probabilities as they are is needed: for O, or for the groups
-  constexpr bool kSumPlain = !kRounded || kDensity;
+  static_assert(kSplit == 1 || (kSplit == 2 && kPrefetchK && NQ == 1), "a split workgroup deals the two blocks of a tile");
+  static_assert(!kRounded || (kSplit == 1 && !kDensity), "a single wave's arithmetic; its density is the single wave's own affair");
 
   __shared__ __align__(1024) char lds_k[kRing];
   __shared__ __align__(1024) char lds_v[kRing];
@@ -473,15 +474,15 @@ __device__ __forceinline__ void attend_unit(
 #pragma unroll
       for (int v = 0; v < 16; ++v) oacc[n][d][v] = 0.f;
   float run_mc[NQ], run_sum[NQ];  // softmax reference times c = softmax scale * log2(e); sum of 2^(s*c - reference)
-  float run_plain[NQ];            // kRounded and density: the same of the probabilities as they are
+  float run_max[NQ];              // kRounded: the reference without c
   // density: this lane's sum over the keys of the group being walked, the group, its end, the block's first row
   float seg_acc[NQ];
   int cur_group = 0, next_end = kDensity ? groups.end[0] : 0, blk_start = 32 * slice;
   bf16x8 pf[NQ][2];  // probabilities of the previous block, two K-steps of 16 keys
 #pragma unroll
   for (int n = 0; n < NQ; ++n) {
-    run_mc[n] = -INFINITY;
-    run_sum[n] = run_plain[n] = 0.f;
+    run_mc[n] = run_max[n] = -INFINITY;
+    run_sum[n] = 0.f;
     seg_acc[n] = 0.f;
 #pragma unroll
     for (int u = 0; u < 2; ++u)
@@ -537,8 +538,8 @@ __device__ __forceinline__ void attend_unit(
   //   has_next: a block g+1 exists (K prefetch)
   //   ragged: g is the last block and t_kv is not a multiple of 32: keys past the end get zero weight
   auto block_step = [&](auto sync_next, auto steady, auto has_next, bool ragged) {
-    // ---- (rarely) move the accumulators to the reference chosen in the previous step
-    if (__builtin_expect(any_rescale, 0)) {
+    // ---- (rarely, but for kRounded) move the accumulators to the reference chosen in the previous step
+    if (__builtin_expect(any_rescale, kRounded)) {
 #pragma unroll
       for (int n = 0; n < NQ; ++n)
 #pragma unroll
@@ -583,14 +584,54 @@ __device__ __forceinline__ void attend_unit(
     // far inside the range of fp32 and bf16, and the block costs no maximum at all.
     // The first block of a unit has no reference yet and nothing to multiply (pf = 0): it goes straight to the
     // path that takes the maximum.
-    const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
-    float sum[NQ][2], rounded[NQ];
+    float sum[NQ][2];
 #pragma unroll
-    for (int n = 0; n < NQ; ++n) sum[n][0] = sum[n][1] = rounded[n] = 0.f;
+    for (int n = 0; n < NQ; ++n) sum[n][0] = sum[n][1] = 0.f;
     const bool first = first_block;
     first_block = false;
-    bool trip = true;
-    if (!first) {
+    bool trip = !kRounded;
+    any_rescale = false;
+    if constexpr (kRounded) {
+      // (the maximum, the scale and the sums exactly as attend_bf16_small.hip has them)
+      if (!first) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+          for (int d = 0; d < DB; ++d) {
+            const char* vp = lds_v + off_prev + v_base[d];
+            const bf16x4 lo = lds_read_tr16(vp + (16 * u) * RB);
+            const bf16x4 hi = lds_read_tr16(vp + (16 * u) * RB + hi_off(d));
+            bf16x8 a;
+            a[0] = lo[0]; a[1] = lo[1]; a[2] = lo[2]; a[3] = lo[3];
+            a[4] = hi[0]; a[5] = hi[1]; a[6] = hi[2]; a[7] = hi[3];
+#pragma unroll
+            for (int n = 0; n < NQ; ++n) oacc[n][d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pf[n][u], oacc[n][d], 0, 0, 0);
+          }
+      }
+      const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
+#pragma unroll
+      for (int n = 0; n < NQ; ++n) {
+        settle_mfma(sacc[n]);
+        float mx = max3(sacc[n][0], sacc[n][1], sacc[n][2]);
+#pragma unroll
+        for (int v = 3; v < 15; v += 2) mx = max3(mx, sacc[n][v], sacc[n][v + 1]);
+        const float new_max = fmaxf(run_max[n], half_max(max3(mx, sacc[n][15], sacc[n][15])));
+        alpha[n] = __builtin_amdgcn_exp2f((run_max[n] - new_max) * scale_log2e);
+        const float mc = new_max * scale_log2e;
+        run_max[n] = new_max;
+        any_rescale |= !first && __builtin_amdgcn_ballot_w64(alpha[n] != 1.f) != 0;
+        run_sum[n] *= alpha[n];
+#pragma unroll
+        for (int v = 0; v < 16; v += 2) {
+          const float p0 = __builtin_amdgcn_exp2f(fmaf(sacc[n][v], scale_log2e, -mc));
+          const float p1 = __builtin_amdgcn_exp2f(fmaf(sacc[n][v + 1], scale_log2e, -mc));
+          const bf16x2 pk = {(__bf16)p0, (__bf16)p1};
+          run_sum[n] = __builtin_amdgcn_fdot2_f32_bf16(pk, ones, run_sum[n], false);
+          pf[n][v >> 3][v & 7] = pk[0];
+          pf[n][v >> 3][(v & 7) + 1] = pk[1];
+        }
+      }
+    } else if (!first) {
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
 #pragma unroll
@@ -610,14 +651,10 @@ __device__ __forceinline__ void attend_unit(
           for (int v = 8 * u; v < 8 * u + 8; v += 2) {
             const float p0 = __builtin_amdgcn_exp2f(fmaf(sacc[n][v], scale_log2e, -run_mc[n]));
             const float p1 = __builtin_amdgcn_exp2f(fmaf(sacc[n][v + 1], scale_log2e, -run_mc[n]));
-            if constexpr (kSumPlain) {
-              sum[n][0] += p0;
-              sum[n][1] += p1;
-            }
-            const bf16x2 pk = {(__bf16)p0, (__bf16)p1};
-            if constexpr (kRounded) rounded[n] = __builtin_amdgcn_fdot2_f32_bf16(pk, ones, rounded[n], false);
-            pf[n][u][v & 7] = pk[0];
-            pf[n][u][(v & 7) + 1] = pk[1];
+            sum[n][0] += p0;
+            sum[n][1] += p1;
+            pf[n][u][v & 7] = (__bf16)p0;
+            pf[n][u][(v & 7) + 1] = (__bf16)p1;
             if constexpr (kDensity) {  // kept for the groups that end in this block
               sacc[n][v] = p0;
               sacc[n][v + 1] = p1;
@@ -629,11 +666,11 @@ __device__ __forceinline__ void attend_unit(
       trip = false;
 #pragma unroll
       for (int n = 0; n < NQ; ++n) {
-        if constexpr (kSumPlain) sum[n][0] += sum[n][1];
-        trip |= __builtin_amdgcn_ballot_w64(!((kRounded ? rounded[n] : sum[n][0]) <= (kRounded ? 1.0f : kTripSum))) != 0;
+        sum[n][0] += sum[n][1];
+        trip |= __builtin_amdgcn_ballot_w64(!(sum[n][0] <= kTripSum)) != 0;
       }
     }
-    any_rescale = trip && !first;  // the first block leaves zeros in the accumulators: nothing to rescale
+    if constexpr (!kRounded) any_rescale = trip && !first;  // the first block leaves zeros in the accumulators: nothing to rescale
     if (__builtin_expect(trip, 0)) {
       // Some query of the wave needs a new reference (or this is the first block).  Now the maximum of the block
       // is taken, per query over both lane halves; a query moves its reference to it only if it lies more than
@@ -665,10 +702,9 @@ __device__ __forceinline__ void attend_unit(
         const float a4 = max3(sacc[n][12], sacc[n][13], sacc[n][14]);
         const float b0 = max3(a0, a1, a2), b1 = max3(a3, a4, sacc[n][15]);
         const float full = half_max(max3(b0, b1, b1)) * scale_log2e;  // finite: key 0 of the block is valid for every query
-        const float new_mc = full - run_mc[n] > (kRounded ? 0.f : kMaxLag) ? full : run_mc[n];
+        const float new_mc = full - run_mc[n] > kMaxLag ? full : run_mc[n];
         alpha[n] = __builtin_amdgcn_exp2f(run_mc[n] - new_mc);  // 1 when unchanged, 0 on the first block
         run_sum[n] *= alpha[n];
-        run_plain[n] *= alpha[n];
         if constexpr (kDensity) {  // what was summed against the old reference moves with it
           seg_acc[n] *= alpha[n];
           if (h == 0)
@@ -676,17 +712,14 @@ __device__ __forceinline__ void attend_unit(
         }
         run_mc[n] = new_mc;
         float s0 = 0.f, s1 = 0.f;
-        rounded[n] = 0.f;
 #pragma unroll
         for (int v = 0; v < 16; v += 2) {
           const float p0 = __builtin_amdgcn_exp2f(fmaf(sacc[n][v], scale_log2e, -new_mc));
           const float p1 = __builtin_amdgcn_exp2f(fmaf(sacc[n][v + 1], scale_log2e, -new_mc));
           s0 += p0;
           s1 += p1;
-          const bf16x2 pk = {(__bf16)p0, (__bf16)p1};
-          if constexpr (kRounded) rounded[n] = __builtin_amdgcn_fdot2_f32_bf16(pk, ones, rounded[n], false);
-          pf[n][v >> 3][v & 7] = pk[0];
-          pf[n][v >> 3][(v & 7) + 1] = pk[1];
+          pf[n][v >> 3][v & 7] = (__bf16)p0;
+          pf[n][v >> 3][(v & 7) + 1] = (__bf16)p1;
           if constexpr (kDensity) {
             sacc[n][v] = p0;
             sacc[n][v + 1] = p1;
@@ -733,10 +766,8 @@ __device__ __forceinline__ void attend_unit(
       blk_start += 32 * kSplit;
     }
 #pragma unroll
-    for (int n = 0; n < NQ; ++n) {
-      run_sum[n] += kRounded ? rounded[n] : sum[n][0];
-      if (kRounded && kDensity) run_plain[n] += sum[n][0];
-    }
+    for (int n = 0; n < NQ; ++n)
+      if constexpr (!kRounded) run_sum[n] += sum[n][0];
     off_prev = off_cur;
     off_cur = off_next;
     if constexpr (kSplit == 1) {
@@ -865,7 +896,7 @@ __device__ __forceinline__ void attend_unit(
 #pragma unroll
   for (int n = 0; n < NQ; ++n) {
     const float total = kSplit > 1 ? run_sum[n] : run_sum[n] + __shfl_xor(run_sum[n], 32, 64);
-    const float inv = 1.0f / total, inv_mass = kRounded && kDensity ? 1.0f / half_sum(run_plain[n]) : inv;
+    const float inv = 1.0f / total;
     const int row = q_base + 32 * n + r;
     // The lane halves hold alternate 8-byte pieces of a row (columns 8g + 4h ..); one lane swap per register
     // pairs them up, so that every lane stores 16 bytes and the two lanes of a row 32 contiguous bytes (half as
@@ -895,7 +926,7 @@ __device__ __forceinline__ void attend_unit(
         const int p = p0 + h, at = min(p, groups.n - 1);
         float gsum = park[wave * NQ + n][at][r];
         if (kSplit > 1) gsum = fmaf(w_theirs, park[other][at][r], w_mine * gsum);
-        const float m = group_sum<32>(row < t_q ? gsum * inv_mass : 0.f);  // over the 32 query rows
+        const float m = group_sum<32>(row < t_q ? gsum * inv : 0.f);  // over the 32 query rows
         if (r == 0 && p < groups.n) partial[qblk * AMSKV_MAX_SCALES + p] = m;
       }
     }
@@ -912,13 +943,13 @@ __global__ __launch_bounds__(64 * kWaves, kMinWavesPerSimd) void attend_bf16_ker
 }
 
 // The same step with the attention density of its own queries as a by-product (no second pass over Q and K).
-template <int D, int NQ, int kWaves, int kTileKeys, int kMinWavesPerSimd, int kSplit, bool kRounded>
+template <int D, int NQ, int kWaves, int kTileKeys, int kMinWavesPerSimd, int kSplit = 1>
 __global__ __launch_bounds__(64 * kWaves, kMinWavesPerSimd) void attend_density_bf16_kernel(
     const __bf16* __restrict__ q, __bf16* __restrict__ o, char* __restrict__ kc, char* __restrict__ vc,
     int t_q, long long cap_tokens, SegTable seg, ExtKV ext_kv, CallerIo io, float scale_log2e, int n_bh, int n_qtiles, int n_whole,
     GroupEnds groups, float* __restrict__ partial) {
   fetch_arguments<kAttentionArguments>();
-  attend_unit<D, NQ, kWaves, kTileKeys, true, kSplit, kRounded>(q, o, kc, vc, t_q, cap_tokens, seg, chosen(ext_kv), io, scale_log2e, n_bh,
+  attend_unit<D, NQ, kWaves, kTileKeys, true, kSplit, false>(q, o, kc, vc, t_q, cap_tokens, seg, chosen(ext_kv), io, scale_log2e, n_bh,
                                               n_qtiles, n_whole, groups, partial);
 }
 
@@ -946,10 +977,7 @@ hipError_t launch_density_variant(const void* q, void* o, void* kc, void* vc, in
   const int n_qtiles = (t_q + BM - 1) / BM;
   const int n_whole = whole_units(bh, n_qtiles, kMostWhole);
   dim3 grid(placed_grid(bh, n_qtiles, n_whole)), block(64 * kWaves);
-  auto kernel = attend_density_bf16_kernel<D, NQ, kWaves, kTileKeys, kMinWavesPerSimd, kSplit, false>;
-  if constexpr (kSplit == 1)
-    if (t_q <= kSmallTq) kernel = attend_density_bf16_kernel<D, NQ, kWaves, kTileKeys, kMinWavesPerSimd, kSplit, true>;
-  hipLaunchKernelGGL(kernel, grid, block, 0, st,
+  hipLaunchKernelGGL((attend_density_bf16_kernel<D, NQ, kWaves, kTileKeys, kMinWavesPerSimd, kSplit>), grid, block, 0, st,
                      (const __bf16*)q, (__bf16*)o, (char*)kc, (char*)vc, t_q, (long long)cap_tokens, seg, ext, io, c,
                      bh, n_qtiles, n_whole, groups, partial);
   return hipGetLastError();
@@ -1056,7 +1084,12 @@ hipError_t launch_attend_density_bf16(const void* q, void* o, void* kc, void* vc
   // The shape is the attention's, so that O comes out with the same bits.  Wide against narrow, which has them too, us: 1920 (b,h),
   // 256 x 680 147 / 159, 169 x 424 92 / 102; 512 (b,h), 256 x 680 41 / 46; head dim 128, 512 (b,h), 256 x 680 66 / 71, 32 (b,h), 1600 x
   // 2645 78 / 91, 128 (b,h), 4096 x 6421 1533 / 1658.  (Without K prefetch wide was the slower one.)
-  const Choice x = choose(head_dim, bh, t_q, seg, ext);
+  // Up to 32 queries stay on single waves where the attention takes workgroups of the streaming kernel, whose O they have: those form a group's sum
+  // as the difference of two sums of a key block, and the many short groups of a coarse step lose their digits beside a large weight (off by up to
+  // 1e-3 of themselves, here 2e-6); with 513 to 768 (b,h) at head dim 128 they are slower too (us, 25 x 155 29.7 -> 38.3; 16 (b,h), 16 x 30 the
+  // other way, 8.1 -> 7.2).
+  Choice x = choose(head_dim, bh, t_q, seg, ext);
+  if (t_q <= kSmallTq && x.shape != Shape::kStreams) x = {Shape::kStreams, 1};
   auto go = [&](auto f) { return f(q, o, kc, vc, bh, t_q, cap_tokens, seg, ext, io, c, groups, partial_ws, st); };
   hipError_t e;
   switch (x.shape) {
