@@ -44,7 +44,8 @@ def test_window_over_cached_rows(sides, window, n_sink, D):
 COARSE = ((8, 16, 1, 1, 3, 29, 20, 1, 5), (5, 20, 1, 7, 11, 1, 25, 16, 6))
 
 
-@pytest.mark.parametrize("B,H", [(1, 1), (3, 5), (9, 32), (35, 16)])   # eight, four and one wave per unit
+# eight slices (head dim 64; four at 128), four, narrow workgroups, single waves
+@pytest.mark.parametrize("B,H", [(1, 1), (3, 5), (9, 32), (35, 16), (65, 16)])
 @pytest.mark.parametrize("D", [64, 128])
 def test_few_queries_many_keys(D, B, H):
     pols = [(0, 0, True), (1, 1, False)]
@@ -57,11 +58,11 @@ def test_few_queries_many_keys(D, B, H):
         r.close()
 
 
-@pytest.mark.parametrize("B,H", [(1, 2), (9, 32), (35, 16)])
+@pytest.mark.parametrize("B,H", [(1, 2), (9, 32), (35, 16), (65, 16)])
 @pytest.mark.parametrize("D", [64, 128])
 def test_density_of_the_same_forms(D, B, H):
-    """the density by-product on every form: O as amskv_attend leaves it, the masses as the stand-alone kernels do (fp32
-    sums of the same exponentials in another order)"""
+    """the density by-product on every form that it takes (slices and single waves; these also where the attention is narrow, (35, 16)): O as
+    amskv_attend leaves it, the masses as the stand-alone kernels do (fp32 sums of the same exponentials in another order)"""
     sides = [tuple(x[i] for i in range(9)) for x in COARSE]
     pols = [(0, 0, True)]
     args = (1, H, D, *sides, B, amskv.AMSKV_DTYPE_BF16, pols)
