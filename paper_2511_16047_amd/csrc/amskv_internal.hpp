@@ -156,7 +156,9 @@ __device__ __forceinline__ void fetch_arguments() {
   asm volatile("" ::"s"(line(0)), "s"(line(1)), "s"(line(2)), "s"(line(3)), "s"(line(4)), "s"(line(5)), "s"(line(6)), "s"(line(7)),
                "s"(line(8)));
 }
-// the arguments of an attention kernel up to its CallerIo
+// the arguments of an attention kernel up to its CallerIo: what every workgroup needs before its first load.  (The numbers behind it mostly share its
+// last line; the ends of the density's groups and `partial` are loaded where a group ends, and the kernels that copy by a table or form the fp32
+// density by itself do without this.)
 constexpr int kAttentionArguments = 4 * 8 + 16 + sizeof(SegTable) + sizeof(ExtKV) + sizeof(CallerIo);
 
 // x plus its value in the lane that the cross-lane pattern pairs with this one, on the vector ALU

@@ -1030,12 +1030,13 @@ Choice choose(int head_dim, int bh, int t_q, const SegTable& seg, const ExtKV& e
   const int blocks = (seg.total + 31) / 32;
   // Few queries.  A workgroup of the streaming kernel to a (b,h) has idle waves, but they fetch the keys, all at once and to addresses that
   // the scalar unit finds: it is ahead of a wave that walks alone, whose arithmetic it has, wherever the chip takes all workgroups together
-  // (wide: 1 on a CU, 2 at head dim 64; narrow: 3 and 4).  us, by (b,h), single waves / this form.  Wide, head dim 64: 16 x 30 keys 16 4.3 / 3.8, 256
-  // 4.8 / 4.4; 4 x 5 4.5 / 4.5.  Head dim 128: 4 x 5 64 5.6 / 5.1; 9 x 22 64 6.1 / 5.1, 256 6.3 / 5.3.  Narrow, head dim 64, 768: 9 x 22 5.2 / 5.2, 16 x
-  // 38 6.9 / 6.8, 25 x 75 9.2 / 8.8, 25 x 209 17.3 / 15.4, 32 x 722 36.5 / 32.6; 1920 16 x 38 10.7 / 12.6.  Head dim 128: 9 x 22 512 6.6 / 6.1, 8 x 13 6.2 /
-  // 6.4; 25 x 75 768 14.7 / 13.0; 25 x 209 768 28.8 / 27.6; 1920 16 x 38 17.9 / 23.3.
-  // A launch that moves cached rows needs one owner of them: one of these, or else a single wave (25 x 209 256 13.5 / 9.0, head dim 128 512
-  // 24.5 / 20.9).
+  // (wide: 1 on a CU, 2 at head dim 64; narrow: 3 and 4).  us a launch, by (b,h), single waves / this form.  Wide, head dim 64: 14 x 14 keys 16 4.1 /
+  // 3.7, 256 4.4 / 4.0; 16 x 30 256 4.0 / 3.8; 4 x 5 3.5 / 3.5.  Head dim 128: 1 x 1 64 5.2 / 4.6; 13 x 13 64 5.5 / 4.4, 256 5.8 / 4.7; 9 x 22 64 4.7 / 4.3, 256 4.9 / 4.5.  Narrow, head dim
+  // 64: 16 x 38 640 6.7 / 6.4, 1024 7.4 / 7.2, 1280 8.9 / 10.2; 25 x 75 640 8.7 / 8.1, 1024 10.2 / 9.8; 25 x 200 640 13.4 / 12.2, 768 14.3 / 14.0, 1280 20.5 / 21.6; 32 x
+  // 722 640 35.4 / 30.8, 768 38.7 / 34.3, 1024 43.8 / 44.5.  Head dim 128: 9 x 22 512 6.5 / 6.0; 16 x 38 640 9.9 / 9.4, 1024 11.4 / 15.3; 25 x 75 640 13.6 / 11.4, 768
+  // 14.8 / 12.8; 25 x 200 640 20.8 / 19.9, 768 22.7 / 22.3, 1024 27.6 / 31.0.
+  // A launch that moves cached rows needs one owner of them: one of these, or else a single wave (25 x 96 256 7.6 / 5.7, 512 8.8 / 7.5, 768 9.8 / 9.1; head dim
+  // 128 256 12.3 / 8.3, 512 14.5 / 11.2, 768 17.7 / 16.1).
   const int fit_wide = head_dim == 64 ? 512 : 256, fit_narrow = head_dim == 64 ? 1024 : 768;
   if (t_q <= kSmallTq) {
     if (bh <= fit_wide && (blocks == 1 ? bh <= 256 && (head_dim == 128 || seg.total > 8) : moves)) return {Shape::kWide, 1};
