@@ -104,10 +104,14 @@ def test_moving_rows(units, spread, D):
 
 
 @pytest.mark.parametrize("D", [64, 128])
-@pytest.mark.parametrize("spread", [1, 40])
+@pytest.mark.parametrize("spread", [1, 40, math.inf])
 def test_workgroups_of_one_b_h_give_the_bits_of_a_single_wave(spread, D):
-    """Up to 32 queries, keys not shared between waves: the same reference, sums and products in the same order, whichever kernel takes them."""
-    q, k, v = _inputs(MOST, D, spread)
+    """Up to 32 queries, keys not shared between waves: the same reference, sums and products in the same order, whichever kernel takes them; with
+    infinite elements in every eleventh key and value as well."""
+    q, k, v = _inputs(MOST, D, 1 if spread == math.inf else spread)
+    if spread == math.inf:
+        for x, sign in zip(k + v, [1, -1, -1] * len(k)):
+            x[:, :, 3::11, 5] = sign * math.inf
     for mode in {}, {"windows": [(WINDOW, SINKS)]}:
         want = _run(MOST, D, q, k, v, **mode)
         for n in LINES:
@@ -115,7 +119,8 @@ def test_workgroups_of_one_b_h_give_the_bits_of_a_single_wave(spread, D):
                 seen = sum(TOKENS[: s + 1])
                 moves = mode and s == 13            # (the others with few queries have room for their rows, and share keys between waves)
                 if TOKENS[s] <= 32 and (moves or seen <= 32 or n > 512):
-                    assert torch.equal(o.view(torch.int16), want[s][:n].view(torch.int16)), (n, s, mode)
+                    same = (o.view(torch.int16) == want[s][:n].view(torch.int16)) | (o.isnan() & want[s][:n].isnan())
+                    assert same.all(), (n, s, mode)
 
 
 @pytest.mark.parametrize("D", [64, 128])

@@ -56,3 +56,28 @@ def test_error(D, tq, prev, shares, rounded, bh):
                       (o, _of_this_arithmetic(s * math.log2(math.e), v, shares, rounded), _of_this_arithmetic(s * math.log2(math.e), v, 1, rounded))]
     print("head dim %d, %d (b,h), %d x %d: rel %.4e, this arithmetic %.4e, with one reference %.4e" % (D, bh, tq, tq + prev, rel, same, one))
     assert rel <= 1.005 * same
+
+
+@pytest.mark.parametrize("spread", [1, 40])              # 40: references move
+@pytest.mark.parametrize("D,tq,prev,wide,narrow", [(64, 33, 31, 384, 385), (64, 64, 91, 384, 385), (64, 100, 590, 384, 385), (64, 128, 1, 384, 385),
+                                                   (128, 33, 31, 256, 300), (128, 36, 55, 256, 300), (128, 49, 1, 1, 300), (128, 96, 0, 256, 300)])
+def test_wide_workgroups_give_the_bits_of_narrow_ones(D, tq, prev, wide, narrow, spread):
+    """33 to 128 queries, keys not shared: wide up to 384 (b,h) at head dim 64, and at 128 up to 256 with up to three key blocks"""
+    sides = [t for t in (prev, tq) if t]
+    g = torch.Generator(device="cuda").manual_seed(tq + prev)
+    mk = lambda t: torch.randn(narrow, 1, t, D, device="cuda", generator=g).bfloat16()
+    k, v, q = [mk(t) for t in sides], [mk(t) for t in sides], mk(tq) * spread
+    out = []
+    for n in (wide, narrow):
+        args = (1, 1, D, (1,) * len(sides), sides, n, amskv.AMSKV_DTYPE_BF16, [(0, 0, True)])
+        arena = torch.empty(amskv.amskv_cache_required_bytes(*args), dtype=torch.uint8, device="cuda")
+        h = amskv.amskv_cache_create(*args, arena=arena)
+        try:
+            for s in range(len(sides)):
+                amskv.amskv_append_scale(h, 0, s, k[s][:n].contiguous(), v[s][:n].contiguous())
+            out.append(torch.full_like(q[:n], float("nan")))
+            amskv.amskv_attend(h, 0, len(sides) - 1, q[:n].contiguous(), out[-1])
+        finally:
+            torch.cuda.synchronize()
+            amskv.amskv_cache_destroy(h)
+    assert not out[1].isnan().any() and torch.equal(out[0].view(torch.int16), out[1][:wide].view(torch.int16))
