@@ -1033,7 +1033,7 @@ Choice choose(int head_dim, int bh, int t_q, const SegTable& seg, const ExtKV& e
   // (wide: 1 on a CU, 2 at head dim 64; narrow: 3 and 4).  us a launch, by (b,h), single waves / this form.  Wide, head dim 64: 14 x 14 keys 16 4.1 /
   // 3.7, 256 4.4 / 4.0; 16 x 30 256 4.0 / 3.8; 4 x 5 3.5 / 3.5.  Head dim 128: 1 x 1 64 5.2 / 4.6; 13 x 13 64 5.5 / 4.4, 256 5.8 / 4.7; 9 x 22 64 4.7 / 4.3, 256 4.9 / 4.5.  Narrow, head dim
   // 64: 16 x 38 640 6.7 / 6.4, 1024 7.4 / 7.2, 1280 8.9 / 10.2; 25 x 75 640 8.7 / 8.1, 1024 10.2 / 9.8; 25 x 200 640 13.4 / 12.2, 768 14.3 / 14.0, 1280 20.5 / 21.6; 32 x
-  // 722 640 35.4 / 30.8, 768 38.7 / 34.3, 1024 43.8 / 44.5.  Head dim 128: 9 x 22 512 6.5 / 6.0; 16 x 38 640 9.9 / 9.4, 1024 11.4 / 15.3; 25 x 75 640 13.6 / 11.4, 768
+  // 722 640 35.4 / 30.8, 768 38.7 / 34.3, 1024 43.8 / 44.5 (beyond 768 with six blocks and more single waves are up to 5 % ahead: 25 x 175 832 14.7 / 15.5).  Head dim 128: 9 x 22 512 6.5 / 6.0; 16 x 38 640 9.9 / 9.4, 1024 11.4 / 15.3; 25 x 75 640 13.6 / 11.4, 768
   // 14.8 / 12.8; 25 x 200 640 20.8 / 19.9, 768 22.7 / 22.3, 1024 27.6 / 31.0.
   // A launch that moves cached rows needs one owner of them: one of these, or else a single wave (25 x 96 256 7.6 / 5.7, 512 8.8 / 7.5, 768 9.8 / 9.1; head dim
   // 128 256 12.3 / 8.3, 512 14.5 / 11.2, 768 17.7 / 16.1).
